@@ -137,9 +137,11 @@ struct umap_layout {
     bool col16_ok = false;
     float *eps = nullptr;
     int32_t *part = nullptr;
+    ul::WaveDesc *desc = nullptr;
     int64_t n_waves = 0;
     int64_t max_waves = 0;                  // capacity of part, rec_count and the record slots
     int64_t row_first = 0, row_last = 0;    // rows the epochs update (umap_layout_set_rows)
+    int64_t row_edges = 0;                  // their kept edges
     uint8_t *head = nullptr;       // edge's row relative to its wave's first row
     float *E[2] = {nullptr, nullptr};
     int cur = 0;
@@ -216,12 +218,17 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         const int32_t lg_phases = ul::phase_log2(h->n_table, dim);
         const size_t table_elems = table ? (size_t)n_table * (size_t)dim : 0;
         const int64_t n_phases = (int64_t)1 << lg_phases;
+        // slots for the records, unless every epoch over the entries (and so
+        // over fewer of them) is one launch
+        const int64_t record_slots = ul::one_launch_epoch(h->n_table, dim, nnz, neg_rate)
+                                         ? 0
+                                         : ul::record_offset(max_waves, nnz, neg_rate, (int32_t)n_phases);
         size_t bytes = need<int64_t>(n + 1) + need<int32_t>(nnz) + need<int16_t>(table ? 0 : nnz) + need<float>(nnz) +
-                       need<int32_t>(max_waves + 1) +
+                       need<int32_t>(max_waves + 1) + need<ul::WaveDesc>(max_waves) +
                        2 * need<float>(nd) + need<unsigned long long>(n_epochs) + need<unsigned long long>(1) +
                        need<uint8_t>(nnz) +
                        need<int32_t>((size_t)count_rows * count_stride) +
-                       need<uint32_t>(ul::record_offset(max_waves, nnz, neg_rate, (int32_t)n_phases)) +
+                       need<uint32_t>(record_slots) +
                        need<int32_t>((size_t)n_phases * max_waves) + need<long long>(nd) + need<unsigned>(1) +
                        need<float>(nd) + need<float>(table_elems);
         if (fault_alloc()) throw HipFailure{hipErrorOutOfMemory, "hipMalloc(arena) [injected]"};
@@ -232,6 +239,7 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         h->col16 = cv.take<int16_t>(table ? 0 : nnz);
         h->eps = cv.take<float>(nnz);
         h->part = cv.take<int32_t>(max_waves + 1);
+        h->desc = cv.take<ul::WaveDesc>(max_waves);
         h->E[0] = cv.take<float>(nd);
         h->E[1] = cv.take<float>(nd);
         h->active = cv.take<unsigned long long>(n_epochs);
@@ -240,7 +248,7 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         h->counts = cv.take<int32_t>((size_t)count_rows * count_stride);
         h->count_stride = count_stride;
         h->lg_phases = lg_phases;
-        h->rec = cv.take<uint32_t>(ul::record_offset(max_waves, nnz, neg_rate, (int32_t)n_phases));
+        h->rec = cv.take<uint32_t>(record_slots);
         h->rec_count = cv.take<int32_t>((size_t)n_phases * max_waves);
         h->delta = cv.take<long long>(nd);
         h->overflow = cv.take<unsigned>(1);
@@ -322,6 +330,7 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
             return rc;
         }
         h->nnz = kept;
+        h->row_edges = kept;
         h->max_degree = S.max_degree;
         memcpy(&h->w_max, &S.wmax_bits, sizeof(float));
         const int64_t units = kept + (int64_t)wgt * n;
@@ -329,15 +338,21 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         h->n_waves = (units + cost - 1) / cost;
         if (h->n_waves < 1) h->n_waves = 1;
         if (h->n_waves > max_waves) throw HipFailure{hipErrorInvalidValue, "wave count exceeds the arena"};
-        UL_HIP(ul::launch_partition(h->row_ptr, 0, n, dim, cost, h->part, h->n_waves, h->head, stream));
+        UL_HIP(ul::launch_partition(h->row_ptr, 0, n, dim, cost, h->part, h->desc, h->n_waves, h->head, stream));
         if (!table && kept > 0) {
-            // a fit's tails as 16-bit offsets from their rows, where they all fit
+            // a fit's tails as 16-bit offsets from their rows, where they all
+            // fit and at least half lie within the halo that the kernels of
+            // 1-2 components stage with them (a shuffled graph gets nothing
+            // from the halo's LDS)
             unsigned wide = 1;
+            unsigned long long near = 0;
             UL_HIP(hipMemsetAsync(h->overflow, 0, sizeof(unsigned), stream));
-            UL_HIP(ul::launch_col_delta(h->row_ptr, h->col, n, h->col16, h->overflow, stream));
+            UL_HIP(hipMemsetAsync(h->active_sum, 0, sizeof near, stream));
+            UL_HIP(ul::launch_col_delta(h->row_ptr, h->col, n, h->col16, h->overflow, h->active_sum, stream));
             UL_HIP(hipMemcpyAsync(&wide, h->overflow, sizeof wide, hipMemcpyDeviceToHost, stream));
+            UL_HIP(hipMemcpyAsync(&near, h->active_sum, sizeof near, hipMemcpyDeviceToHost, stream));
             UL_HIP(hipStreamSynchronize(stream));
-            h->col16_ok = wide == 0;
+            h->col16_ok = wide == 0 && 2 * (int64_t)near >= kept;
         }
         float ms = 0;
         UL_HIP(hipEventElapsedTime(&ms, h->ev[0], h->ev[1]));
@@ -373,10 +388,14 @@ int run_epochs_impl(umap_layout *h, uint64_t seed, int32_t first, int32_t last, 
     A.b = h->b;
     A.key_lo = (uint32_t)seed;
     A.key_hi = (uint32_t)(seed >> 32);
-    ul::WaveGraph G{h->row_ptr,     h->col,       h->eps,    h->head,      h->part,
+    // (injected record failures need the records' path)
+    const bool one_launch = h->lg_phases == 0 || (!fault_records() && ul::one_launch_epoch(h->n_table, h->dim, h->row_edges,
+                                                                                        h->neg_rate));
+    ul::WaveGraph G{h->row_ptr,     h->col,       h->eps,    h->head,      h->part,      h->desc,
                     h->n_waves,     1 << h->lg_phases,       h->lg_phases, h->rec,
                     h->rec_count,   h->overflow,  fault_records() ? (int64_t)0 : (int64_t)-1,
-                    h->delta,       h->col16_ok ? h->col16 : nullptr};
+                    h->delta,       h->col16_ok ? h->col16 : nullptr,
+                    one_launch ? 1 : 0};
     // the wave kernels store a sample's offset inside its table range and a
     // sampled edge's offset inside its wave in 24 bits (a wave holds fewer
     // than kWaveCost + max_degree edges), and address a wave's record slots
@@ -402,9 +421,9 @@ int run_epochs_impl(umap_layout *h, uint64_t seed, int32_t first, int32_t last, 
     if (kernel == kAsyncKernel && (int64_t)h->max_degree + ul::kWaveCost >= ((int64_t)1 << 24))
         return fail(UMAP_E_INVAL, "the per-edge asynchronous kernel needs rows of fewer than %d edges",
                     (1 << 24) - ul::kWaveCost);
-    // with one table range the draw kernel applies every negative itself and
+    // in a one-launch epoch the draw kernel applies every negative itself and
     // files no records, so no slot can overflow and no redo is needed
-    const bool records = kernel == 0 && h->lg_phases > 0;
+    const bool records = kernel == 0 && !one_launch;
     const int cur0 = h->cur;
     const size_t row_bytes = sizeof(float) * (size_t)h->dim;
     const size_t nd_bytes = row_bytes * (size_t)h->n;
@@ -790,12 +809,13 @@ int umap_layout_set_rows(umap_layout *h, int64_t row_first, int64_t row_last)
         int64_t waves = (units + cost - 1) / cost;
         if (waves < 1) waves = 1;
         if (waves > h->max_waves) return fail(UMAP_E_INVAL, "the range needs more waves than the handle holds");
-        UL_HIP(ul::launch_partition(h->row_ptr, row_first, row_last, h->dim, cost, h->part, waves, h->head,
+        UL_HIP(ul::launch_partition(h->row_ptr, row_first, row_last, h->dim, cost, h->part, h->desc, waves, h->head,
                                     h->stream));
         UL_HIP(hipStreamSynchronize(h->stream));
         h->n_waves = waves;
         h->row_first = row_first;
         h->row_last = row_last;
+        h->row_edges = ends[1] - ends[0];
         return UMAP_OK;
     } catch (const HipFailure &f) {
         return hip_fail(f);

@@ -85,12 +85,13 @@ hipError_t launch_prep(const PrepBuffers &B, hipStream_t s);
 // Waves over rows [r0, r1) (0 <= r0 < r1); n_waves = ceil(units / cost) for
 // the units (edges + row_weight x rows) of the range.
 hipError_t launch_partition(const int64_t *row_ptr, int64_t r0, int64_t r1, int32_t dim, int64_t cost,
-                            int32_t *part, int64_t n_waves, uint8_t *head, hipStream_t s);
+                            int32_t *part, WaveDesc *desc, int64_t n_waves, uint8_t *head, hipStream_t s);
 hipError_t launch_zero_u64(unsigned long long *p, int64_t count, hipStream_t s);
-// delta[e] = col[e] - row(e) as int16 for the n rows; *wide = 1 (it must start
-// at 0) when some delta needs more than 16 bits.
+// delta[e] = col[e] - row(e) as int16 for the n rows; *wide = 1 when some delta
+// needs more than 16 bits, *near += the deltas of at most kHalo (both must
+// start at 0).
 hipError_t launch_col_delta(const int64_t *row_ptr, const int32_t *col, int64_t n, int16_t *delta, unsigned *wide,
-                            hipStream_t s);
+                            unsigned long long *near, hipStream_t s);
 
 // ---- layout (kernels_layout.hip) ----
 hipError_t launch_init(float *E, int64_t n, int32_t dim, uint64_t seed, hipStream_t s);
@@ -103,6 +104,7 @@ struct WaveGraph {
     const float *eps;         // epochs per sample of each edge
     const uint8_t *head;      // row of each edge relative to its wave's first row
     const int32_t *part;      // n_waves + 1 wave boundaries (rows)
+    const WaveDesc *desc;     // n_waves: the same and the waves' edges, one 16-byte load per wave
     int64_t n_waves;
     // negative samples are filed by vertex-table range: P = 2^lg_phases ranges
     int32_t n_phases;
@@ -112,7 +114,8 @@ struct WaveGraph {
     unsigned *overflow;       // set when a record did not fit its range slot
     int64_t cap_limit;        // < 0: none; else record slots per range are cut to it (failure injection)
     long long *delta;         // n x dim fixed-point partial sums between launches
-    const int16_t *col16;     // col - row in 16 bits when every edge's fits (a fit), else null
+    const int16_t *col16;     // col - row in 16 bits (a fit whose tails all fit and mostly lie near), else null
+    int32_t one_launch;       // the draw launch applies the negative samples itself (no records, no range launches)
 };
 
 // First record slot of wave w (edges from e0): every wave gets
@@ -136,16 +139,8 @@ constexpr int kMaxPhases = 16;
 // whatever the row width, and never more than a 2 MB range needs.
 constexpr int64_t kPhaseTableBytes = 2 << 20;
 constexpr int64_t kPhaseRows = 2500000;
-// With one range the draw kernel applies the repulsions itself (no records,
-// no partial sums, one launch per epoch), which beats the range launches for
-// tables up to kOneRangeBytes (200 epochs of window graphs, ms, one range
-// against the split: 2 components 700K vertices 37.3 / 45.5; 3 components 500K
-// 32.6 / 38.1; 4 components 350K 26.3 / 31.3; 8 components 180K 27.8 / 28.1),
-// and up to kOneRangeBytesWide from 9 to kOneRangeMaxDim components (10
-// components 100K 21.2 / 21.5, 12 components 80K 18.5 / 19.0, 13 components
-// 75K 19.0 / 19.3).  Wider rows keep the plain rule (one range up to 2 MB):
-// 14 components 70K 19.7 / 19.4, 16 components 60K / 45K / 35K 20.0 / 18.9,
-// 15.6 / 15.1, 13.2 / 13.0.
+// A table of one range never files records (see one_launch_epoch for the
+// tables of several ranges that do not either).
 constexpr int64_t kOneRangeBytes = 6 << 20;
 constexpr int64_t kOneRangeBytesWide = 4 << 20;
 constexpr int32_t kOneRangeMaxDim = 13;
@@ -154,6 +149,32 @@ constexpr int32_t kOneRangeMaxDim = 13;
 // else min(the ranges that bring a range down to kPhaseTableBytes, 4 ranges per
 // kPhaseRows vertices rounded up to a power of two), at most kMaxPhases.
 int32_t phase_log2(int64_t n, int32_t dim);
+
+// Whether an epoch over `edges` edges runs as one launch, in which the draw
+// kernel gathers and applies each negative sample itself, instead of filing
+// records for one launch per table range.  One launch saves the records (4
+// bytes written and read per sample), the partial sums and P launches of at
+// least 7 us; the range launches gather from a slice that stays in L2.  Two
+// lines, both measured on MI355X (us per epoch, one launch / range launches):
+//  * by table size, because wide rows pay more per partial sum and record
+//    while a gather is one L2 request at any width: window graphs of k = 15 in
+//    local order, 2 components 6 MB 240 / 256, 8 MB 413 / 323; 3 components
+//    6 MB 173 / 199, 8 MB 302 / 262; 5 components 6 MB 129 / 163, 8 MB 202 /
+//    200; 8 components 12 MB 214 / 252, 20 MB 402 / 408 (shuffled 459 / 433);
+//    10 components 12 MB 211 / 242, 20 MB 394 / 400 (454 / 424); 13 components
+//    20 MB 330 / 376 (382 / 383); 16 components 20 MB 213 / 364, 64 MB 748 /
+//    1048;
+//  * by work, because the saved launches do not shrink with it: transforms of
+//    100K points with 15 edges (9M terms) on 1M x 2 47 / 73, 5M x 2 80 / 117,
+//    1M x 3 65 / 72; an eighth of the rows of the 1M window graph (20M terms)
+//    in 2-D 54 / 76, 3-D 71 / 80; 300K points (27M terms) 129 / 132, 231 / 198
+//    and 180 / 146.
+constexpr int64_t kOneLaunchTerms = 24000000;
+inline bool one_launch_epoch(int64_t n_table, int32_t dim, int64_t edges, int32_t neg_rate)
+{
+    const int64_t mb = dim <= 3 ? 6 : dim <= 5 ? 7 : dim <= 10 ? 16 : dim <= 13 ? 20 : 64;
+    return n_table * dim * (int64_t)sizeof(float) <= mb << 20 || edges * (1 + (int64_t)neg_rate) <= kOneLaunchTerms;
+}
 
 hipError_t launch_epoch(int kernel, int32_t dim, const EpochArgs &A, const WaveGraph &G, hipStream_t s);
 // One asynchronous epoch, in place on A.E_next (A.E must be the same buffer).

@@ -7,10 +7,10 @@
 // scatter to global memory, no atomics on the embedding in global memory).
 // In a transform the tails and negative samples are rows of a frozen layout T
 // (the trained embedding) and only the new points, the rows of E, move.
-//  * edge-parallel (default): one k_epoch_draw launch and, when the vertex
-//    table is split into P > 1 ranges, P k_epoch_repulse launches per epoch,
-//    each wavefront owning a range of whole rows (see the section comment
-//    below).
+//  * edge-parallel (default): one k_epoch_draw launch and, unless that applies
+//    the negative samples too, one k_epoch_repulse launch per range of the
+//    vertex table and epoch, each wavefront owning a range of whole rows (see
+//    the section comment below).
 //  * k_epoch_rowwise: one thread per vertex walking its row (a plain second
 //    implementation used to cross-check the first).
 // Because the sums are exact integers, both paths give the same bits.
@@ -145,9 +145,10 @@ __global__ __launch_bounds__(256) void k_epoch_rowwise(EpochArgs A, const int64_
 //    of them or, at 1-2 components, within 64 rows of them),
 //    draws the edge's negative samples and files each one as a 4-byte record
 //    under the range of the vertex table it falls in.  The accumulator goes
-//    to delta.  With a table of one range (P = 1) the draw kernel's FUSED
-//    instance gathers each negative's row itself, adds its repulsion to the
-//    accumulator and commits E_{n+1}: no records and no range launch.
+//    to delta.  Where an epoch is one launch (one_launch_epoch: a small table,
+//    wide rows or little work) the draw kernel's FUSED instance gathers each
+//    negative's row itself, adds its repulsion and commits E_{n+1}: no records
+//    and no range launch.
 //  * k_epoch_repulse (range p) reads the wave's records of range p and adds
 //    their repulsions.  All gathers of one launch hit one 1/P slice of the
 //    vertex table, which is sized to stay resident in an XCD's L2.  The last
@@ -183,6 +184,13 @@ constexpr int draw_halo() { return DIM <= 2 ? kHalo : 0; }
 // element makes the stride odd and spreads the rows over all banks.
 template <int DIM>
 constexpr int lds_stride() { return DIM >= 4 && DIM % 2 == 0 ? DIM + 1 : DIM; }
+// Table rows that the one-launch path keeps in flight per lane (of an edge's
+// negative samples): more cost waves per SIMD.  1 / 2 / 4 rows, 20 epochs of
+// 100K points, us: 2 components 597 / 591 / 600, 3 components 636 / 616 / 646,
+// 5 components 784 / 748 / 795, 8 components 855 / 852 / 934, 16 components
+// 1427 / 1445 / 1668 (30K points 655 / 699 / 820).
+template <int DIM>
+constexpr int one_launch_group() { return DIM <= 12 ? 2 : 1; }
 // LDS index of element t of a wave's rows stored back to back (t >= 0)
 template <int DIM, int S>
 __device__ __forceinline__ int lds_at(int t) { if constexpr (S == DIM) return t; else return (t / DIM) * S + t % DIM; }
@@ -197,46 +205,52 @@ __device__ __forceinline__ uint32_t range_base(uint32_t p, int32_t lg, uint32_t 
 // tails from LDS, self draws skipped, both shares of the attraction); else they
 // index a frozen table (a transform).  C16: the tails are read as 16-bit
 // offsets from their rows (G.col16), 2 bytes per edge instead of 4.  FUSED:
-// the table is one range (G.n_phases == 1) and each negative's repulsion is
+// the epoch is one launch (G.one_launch) and each negative's repulsion is
 // applied here; a separate instance, so that the record-filing kernel of
 // several ranges carries none of its registers (at 8 components the draw
-// launch took 222 instead of 186 us with both paths in one kernel).
+// launch took 222 instead of 186 us with both paths in one kernel).  A lane
+// adds its edge's attraction and repulsions in registers and the wave's LDS
+// sums take one add per component and edge; one per component and term made
+// an epoch of 50K points in 10 components 65 us (28 now), of 100K points in 3
+// components 40 us (29 now), while at 2 components the gathers bound it.
 template <int DIM, int NQ, bool FIT, bool C16, bool FUSED>
 __global__ __launch_bounds__(256) void k_epoch_draw(EpochArgs A, WaveGraph G)
 {
     constexpr int CAP = rows_cap(DIM);
     constexpr int S = lds_stride<DIM>();
     __shared__ long long s_acc[kWavesPerBlock][CAP * S];
-    // a transform's tails index the frozen table: no halo
-    constexpr int kHaloW = FIT ? draw_halo<DIM>() : 0;
+    // a halo only where most tails lie close to their rows (the C16 graphs); a
+    // transform's tails index the frozen table
+    constexpr int kHaloW = FIT && C16 ? draw_halo<DIM>() : 0;
     __shared__ float s_y[kWavesPerBlock][(CAP + 2 * kHaloW) * S];   // the wave's rows of E_n and halos
-    __shared__ uint32_t s_rec[kWavesPerBlock][kMaxPhases];
+    __shared__ uint32_t s_rec[FUSED ? 1 : kWavesPerBlock][FUSED ? 1 : kMaxPhases];
     __shared__ uint2 s_q[kWavesPerBlock][kQueue];
 
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const unsigned lane = threadIdx.x % kWave;
     const int64_t w = logical_wave();
     if (w >= G.n_waves) return;
-    const int64_t r0 = __builtin_amdgcn_readfirstlane(G.part[w]);
-    const int nrows = __builtin_amdgcn_readfirstlane(G.part[w + 1]) - (int)r0;
+    const WaveDesc ds = load_desc(G.desc, w);
+    const int64_t r0 = ds.r0;
+    const int nrows = ds.nrows;
     if (nrows <= 0) {
         if (lane == 0) A.counts[w] = 0;
-        if ((int)lane < G.n_phases) G.rec_count[(int64_t)lane * G.n_waves + w] = 0;
+        if (!FUSED && (int)lane < G.n_phases) G.rec_count[(int64_t)lane * G.n_waves + w] = 0;
         return;
     }
-    const int64_t e0 = uniform64(G.row_ptr[r0]);
-    const int64_t e1 = uniform64(G.row_ptr[r0 + nrows]);
+    const int64_t e0 = ds.e0;
+    const int64_t e1 = e0 + ds.ne;
 
     long long *acc = s_acc[wv];
     float *yrows = s_y[wv] + kHaloW * S;   // row h of the wave at yrows[h * S], h in [-kHaloW, nrows + kHaloW)
-    uint32_t *rec_n = s_rec[wv];
+    uint32_t *rec_n = s_rec[FUSED ? 0 : wv];
     const size_t g0 = (size_t)r0 * DIM;
     // staged rows [lo, hi): the wave's own rows and up to kHaloW on each side
     constexpr int64_t halo = kHaloW;
     const int64_t lo = r0 >= halo ? r0 - halo : 0;
     const int64_t hi = r0 + nrows + halo <= (int64_t)A.n ? r0 + nrows + halo : (int64_t)A.n;
     for (int t = lane; t < nrows * S; t += kWave) acc[t] = 0;
-    if ((int)lane < kMaxPhases) rec_n[lane] = 0;
+    if (!FUSED && (int)lane < kMaxPhases) rec_n[lane] = 0;
     {
         // all of a lane's row loads are issued before the first LDS store
         constexpr int kStageD = ((CAP + 2 * kHaloW) * DIM + kWave - 1) / kWave;
@@ -281,15 +295,12 @@ __global__ __launch_bounds__(256) void k_epoch_draw(EpochArgs A, WaveGraph G)
     };
     const int32_t R = A.neg_rate;
     const int32_t lg = G.lg_phases;
-    const int64_t roff = record_offset(w, e0, R, G.n_phases);
-    int64_t cap64 = (record_offset(w + 1, e1, R, G.n_phases) - roff) / G.n_phases;   // slots per range
+    const int64_t roff = FUSED ? 0 : record_offset(w, e0, R, G.n_phases);
+    int64_t cap64 = FUSED ? 0 : (record_offset(w + 1, e1, R, G.n_phases) - roff) / G.n_phases;   // slots per range
     if (G.cap_limit >= 0 && cap64 > G.cap_limit) cap64 = G.cap_limit;
     // a wave's record slots span less than 2^32 bytes (checked by the host)
     const uint32_t cap = (uint32_t)cap64;
     uint32_t *const rec_wave = G.rec + roff;   // this wave's slots, range p from p * cap
-    // One table range: the whole table stays in L2 beside the edge stream, so
-    // each negative's repulsion is applied here (no records, no range launch)
-    constexpr bool fused = FUSED;
     uint2 *q = s_q[wv];
     uint32_t qhead = 0, qtail = 0;
     bool overflow = false;   // a record found its range's slots full
@@ -301,27 +312,26 @@ __global__ __launch_bounds__(256) void k_epoch_draw(EpochArgs A, WaveGraph G)
         if (slot < cap) at32(rec_wave, p * cap + slot) = ((uint32_t)h << 24) | (k - range_base(p, lg, A.n_table));
         else overflow = true;
     };
-    // repulsions of four drawn words of a lane's edge, applied at once: all
-    // four table rows are loaded before the first term is computed
-    auto repel4 = [&](const uint32_t *u, int cnt, uint32_t i, int h, const float (&yi)[DIM], bool live)
-                      __attribute__((always_inline)) {
-        uint32_t k[4];
-        float yk[4][DIM];
+    // repulsions of kGroup drawn words of a lane's edge added to the lane's
+    // sums: all rows of a group are loaded before the first term is computed
+    constexpr int kGroup = one_launch_group<DIM>();
+    auto repel = [&](const uint32_t *u, int cnt, uint32_t i, const float (&yi)[DIM], long long (&sum)[DIM])
+                     __attribute__((always_inline)) {
+        uint32_t k[kGroup];
+        float yk[kGroup][DIM];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < kGroup; ++r) {
             k[r] = word_to_vertex(u[r], A.n_table);
             if (r < cnt) load_row<DIM>(A.T, k[r], yk[r]);
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < kGroup; ++r) {
             if (r < cnt) {
                 long long fx[DIM];
                 repulsion_fixed<DIM>(yi, yk[r], A.a, A.b, fx);
-                if (live && !(FIT && k[r] == i)) {
+                const bool skip = FIT && k[r] == i;   // a draw equal to the source adds nothing
 #pragma unroll
-                    for (int d = 0; d < DIM; ++d)
-                        atomicAdd(reinterpret_cast<unsigned long long *>(&acc[h * S + d]), (unsigned long long)fx[d]);
-                }
+                for (int d = 0; d < DIM; ++d) sum[d] += skip ? 0ll : fx[d];
             }
         }
     };
@@ -330,46 +340,68 @@ __global__ __launch_bounds__(256) void k_epoch_draw(EpochArgs A, WaveGraph G)
         const bool valid = (int)lane < count;
         const uint2 ent = q[(qhead + lane) & (kQueue - 1)];
         const int h = valid ? (int)(ent.y >> 24) : 0;
-        const int64_t e = valid ? e0 + (ent.y & 0xFFFFFFu) : e0;
-        const uint32_t tail = valid ? ent.x : (uint32_t)r0;
+        const int64_t e = (int64_t)((uint32_t)e0 + (valid ? ent.y & 0xFFFFFFu : 0u));   // < 2^31 edges
+        const uint32_t tail = valid ? ent.x : (FIT ? (uint32_t)r0 : 0u);
         const uint32_t i = (uint32_t)(r0 + h);
         float yi[DIM], yj[DIM];
 #pragma unroll
         for (int d = 0; d < DIM; ++d) yi[d] = yrows[h * S + d];
-        // y_j from the staged rows when j is one of them, else from the table;
-        // the LDS read is unconditional (a valid row otherwise) so that the
-        // two reads never merge into one generic-address load
-        const bool near = FIT && (int64_t)tail >= lo && (int64_t)tail < hi;
-        const int64_t jt = near ? (int64_t)tail - r0 : 0;
+        if constexpr (kHaloW > 0) {
+            // y_j from the staged rows when j is one of them, else from the table;
+            // the LDS read is unconditional (a valid row otherwise) so that the
+            // two reads never merge into one generic-address load
+            const bool near = (int64_t)tail >= lo && (int64_t)tail < hi;
+            const int64_t jt = near ? (int64_t)tail - r0 : 0;
 #pragma unroll
-        for (int d = 0; d < DIM; ++d) yj[d] = yrows[jt * S + d];
-        if (!near) load_row<DIM>(A.T, tail, yj);
-        long long fx[DIM];
-        attraction_fixed<DIM>(yi, yj, A.a, A.b, FIT ? 2.0f : 1.0f, fx);
-        if (valid) {
-#pragma unroll
-            for (int d = 0; d < DIM; ++d)
-                atomicAdd(reinterpret_cast<unsigned long long *>(&acc[h * S + d]), (unsigned long long)fx[d]);
+            for (int d = 0; d < DIM; ++d) yj[d] = yrows[jt * S + d];
+            if (!near) load_row<DIM>(A.T, tail, yj);
+        } else {
+            load_row<DIM>(A.T, tail, yj);
         }
-        if (fused) {
-            // every lane draws (the words of a lane without an edge add nothing)
-            for (int32_t qq = 0; 4 * qq < R; ++qq) {
-                const Ctr wd = negative_words(e, A.epoch, qq, A.key_lo, A.key_hi);
-                repel4(wd.w, R - 4 * qq, i, h, yi, valid);
-            }
-        } else if (valid) {
-            if constexpr (NQ >= 0) {
-                uint32_t u[4 * NQ > 0 ? 4 * NQ : 1];
-                if constexpr (NQ > 0) negative_words_all<NQ>(e, A.epoch, A.key_lo, A.key_hi, u);
+        if constexpr (FUSED) {
+            // every lane draws (the sums of a lane without an edge are not added)
+            long long sum[DIM];
+            if constexpr (NQ > 0 && 4 * NQ % kGroup == 0) {
+                uint32_t u[4 * NQ];
+                negative_words_all<NQ>(e, A.epoch, A.key_lo, A.key_hi, u);
+                attraction_fixed<DIM>(yi, yj, A.a, A.b, FIT ? 2.0f : 1.0f, sum);
 #pragma unroll
-                for (int r = 0; r < 4 * NQ; ++r)
-                    if (r < R) file(u[r], i, h);
+                for (int g = 0; g < 4 * NQ; g += kGroup)
+                    if (g < R) repel(&u[g], R - g, i, yi, sum);
             } else {
+                attraction_fixed<DIM>(yi, yj, A.a, A.b, FIT ? 2.0f : 1.0f, sum);
                 for (int32_t qq = 0; 4 * qq < R; ++qq) {
-                    Ctr wd = negative_words(e, A.epoch, qq, A.key_lo, A.key_hi);
+                    const Ctr wd = negative_words(e, A.epoch, qq, A.key_lo, A.key_hi);
 #pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        if (4 * qq + t < R) file(wd.w[t], i, h);
+                    for (int g = 0; g < 4; g += kGroup)
+                        if (4 * qq + g < R) repel(&wd.w[g], R - 4 * qq - g, i, yi, sum);
+                }
+            }
+            if (valid) {
+#pragma unroll
+                for (int d = 0; d < DIM; ++d)
+                    atomicAdd(reinterpret_cast<unsigned long long *>(&acc[h * S + d]), (unsigned long long)sum[d]);
+            }
+        } else {
+            long long fx[DIM];
+            attraction_fixed<DIM>(yi, yj, A.a, A.b, FIT ? 2.0f : 1.0f, fx);
+            if (valid) {
+#pragma unroll
+                for (int d = 0; d < DIM; ++d)
+                    atomicAdd(reinterpret_cast<unsigned long long *>(&acc[h * S + d]), (unsigned long long)fx[d]);
+                if constexpr (NQ >= 0) {
+                    uint32_t u[4 * NQ > 0 ? 4 * NQ : 1];
+                    if constexpr (NQ > 0) negative_words_all<NQ>(e, A.epoch, A.key_lo, A.key_hi, u);
+#pragma unroll
+                    for (int r = 0; r < 4 * NQ; ++r)
+                        if (r < R) file(u[r], i, h);
+                } else {
+                    for (int32_t qq = 0; 4 * qq < R; ++qq) {
+                        Ctr wd = negative_words(e, A.epoch, qq, A.key_lo, A.key_hi);
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            if (4 * qq + t < R) file(wd.w[t], i, h);
+                    }
                 }
             }
         }
@@ -422,17 +454,17 @@ __global__ __launch_bounds__(256) void k_epoch_draw(EpochArgs A, WaveGraph G)
     }
     wave_sync();
 
-    if (A.in_place || fused) {
+    if (A.in_place || FUSED) {
         for (int t = lane; t < nrows * DIM; t += kWave)
             A.E_next[g0 + t] = commit(yrows[lds_at<DIM, S>(t)], acc[lds_at<DIM, S>(t)], A.alpha);
     } else {
         for (int t = lane; t < nrows * DIM; t += kWave) G.delta[g0 + t] = acc[lds_at<DIM, S>(t)];
     }
-    if ((int)lane < G.n_phases) G.rec_count[(int64_t)lane * G.n_waves + w] = (int32_t)rec_n[lane];
+    if (!FUSED && (int)lane < G.n_phases) G.rec_count[(int64_t)lane * G.n_waves + w] = (int32_t)rec_n[lane];
     // per-wave count, summed by a separate pass (a global atomic per wave on
     // one address would serialise thousands of waves)
     if (lane == 0) A.counts[w] = (int32_t)qn;
-    if (__ballot(overflow) != 0 && lane == 0) atomicOr(G.overflow, 1u);
+    if (!FUSED && __ballot(overflow) != 0 && lane == 0) atomicOr(G.overflow, 1u);
 }
 
 // Waves per SIMD the repulsion kernel's registers are held to: at 1-2
@@ -457,11 +489,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(rep_waves<D
     const unsigned lane = threadIdx.x % kWave;
     const int64_t w = logical_wave();
     if (w >= G.n_waves) return;
-    const int64_t r0 = __builtin_amdgcn_readfirstlane(G.part[w]);
-    const int nrows = __builtin_amdgcn_readfirstlane(G.part[w + 1]) - (int)r0;
+    const WaveDesc ds = load_desc(G.desc, w);
+    const int64_t r0 = ds.r0;
+    const int nrows = ds.nrows;
     if (nrows <= 0) return;
-    const int64_t e0 = uniform64(G.row_ptr[r0]);
-    const int64_t e1 = uniform64(G.row_ptr[r0 + nrows]);
+    const int64_t e0 = ds.e0;
+    const int64_t e1 = e0 + ds.ne;
     const int64_t roff = record_offset(w, e0, A.neg_rate, G.n_phases);
     int64_t cap = (record_offset(w + 1, e1, A.neg_rate, G.n_phases) - roff) / G.n_phases;
     if (G.cap_limit >= 0 && cap > G.cap_limit) cap = G.cap_limit;
@@ -565,7 +598,7 @@ int32_t phase_log2(int64_t n, int32_t dim)
 template <int DIM, int NQ, bool FIT, bool C16>
 static void launch_draw(int64_t grid, const EpochArgs &A, const WaveGraph &G, hipStream_t s)
 {
-    if (G.n_phases == 1)
+    if (G.one_launch)
         hipLaunchKernelGGL((k_epoch_draw<DIM, NQ, FIT, C16, true>), dim3((unsigned)grid), dim3(256), 0, s, A, G);
     else
         hipLaunchKernelGGL((k_epoch_draw<DIM, NQ, FIT, C16, false>), dim3((unsigned)grid), dim3(256), 0, s, A, G);
@@ -586,7 +619,7 @@ static hipError_t launch_epoch_dq(int kernel, const EpochArgs &A, const WaveGrap
     if constexpr (DIM <= 4) {
         if (A.same_table && G.col16) {
             launch_draw<DIM, NQ, true, true>(grid, A, G, s);
-            for (int32_t p = 0; G.n_phases > 1 && p < G.n_phases; ++p)
+            for (int32_t p = 0; !G.one_launch && p < G.n_phases; ++p)
                 hipLaunchKernelGGL((k_epoch_repulse<DIM>), dim3((unsigned)grid), dim3(256), 0, s, A, G, p);
             return hipGetLastError();
         }
@@ -595,7 +628,7 @@ static hipError_t launch_epoch_dq(int kernel, const EpochArgs &A, const WaveGrap
         launch_draw<DIM, NQ, true, false>(grid, A, G, s);
     else
         launch_draw<DIM, NQ, false, false>(grid, A, G, s);
-    for (int32_t p = 0; G.n_phases > 1 && p < G.n_phases; ++p)
+    for (int32_t p = 0; !G.one_launch && p < G.n_phases; ++p)
         hipLaunchKernelGGL((k_epoch_repulse<DIM>), dim3((unsigned)grid), dim3(256), 0, s, A, G, p);
     return hipGetLastError();
 }

@@ -477,8 +477,15 @@ __global__ void k_partition(const int64_t *__restrict__ row_ptr, int64_t r0, int
 // head[e] = row of edge e minus the first row of its wave (< rows_cap <= 256).
 // One thread per row of [r0, r1): its wave is the last w with part[w] <= row.
 __global__ void k_head_local(const int64_t *__restrict__ row_ptr, int64_t r0, int64_t r1,
-                             const int32_t *__restrict__ part, int64_t n_waves, uint8_t *__restrict__ head)
+                             const int32_t *__restrict__ part, int64_t n_waves, WaveDesc *__restrict__ desc,
+                             uint8_t *__restrict__ head)
 {
+    const int64_t w0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (w0 < n_waves) {
+        const int32_t a = part[w0], b = part[w0 + 1];
+        const int64_t ea = row_ptr[a], eb = row_ptr[b];
+        desc[w0] = WaveDesc{a, b - a, (int32_t)ea, (int32_t)(eb - ea)};
+    }
     const int64_t r = r0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= r1) return;
     int64_t lo = 0, hi = n_waves - 1;
@@ -491,34 +498,40 @@ __global__ void k_head_local(const int64_t *__restrict__ row_ptr, int64_t r0, in
 }
 
 hipError_t launch_partition(const int64_t *row_ptr, int64_t r0, int64_t r1, int32_t dim, int64_t cost,
-                            int32_t *part, int64_t n_waves, uint8_t *head, hipStream_t s)
+                            int32_t *part, WaveDesc *desc, int64_t n_waves, uint8_t *head, hipStream_t s)
 {
     if (cost < 1 || cost > kWaveCost || r0 < 0 || r1 <= r0 || n_waves < 1) return hipErrorInvalidValue;
     static_assert(rows_cap(1) <= 256 && rows_cap(16) <= 256, "head offsets must fit in a byte");
     int64_t blocks = (n_waves + 1 + 255) / 256;
     hipLaunchKernelGGL(k_partition, dim3((unsigned)blocks), dim3(256), 0, s, row_ptr, r0, r1, row_weight(dim), cost,
                        part, n_waves);
-    hipLaunchKernelGGL(k_head_local, dim3((unsigned)((r1 - r0 + 255) / 256)), dim3(256), 0, s, row_ptr, r0, r1, part,
-                       n_waves, head);
+    const int64_t threads = r1 - r0 > n_waves ? r1 - r0 : n_waves;
+    hipLaunchKernelGGL(k_head_local, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, row_ptr, r0, r1, part,
+                       n_waves, desc, head);
     return hipGetLastError();
 }
 
 // delta[e] = col[e] - (row of e) in 16 bits; *wide gets 1 when some delta
-// does not fit (then the wave kernels read the 32-bit columns and delta is not
-// used).  One block per 256 rows reads and writes the rows' edges with
+// does not fit and *near the number of deltas of at most kHalo (the wave
+// kernels read the 32-bit columns, and stage no halo, unless all fit and most
+// are near).  One block per 256 rows reads and writes the rows' edges with
 // consecutive threads on consecutive edges and finds each edge's row by a
 // binary search over the rows' starts staged in LDS (one thread walking a
 // whole row waits on one load per edge: 454 us at 1M vertices, k = 15).
 __global__ __launch_bounds__(256) void k_col_delta(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                                                   int64_t n, int16_t *__restrict__ delta, unsigned *__restrict__ wide)
+                                                   int64_t n, int16_t *__restrict__ delta, unsigned *__restrict__ wide,
+                                                   unsigned long long *__restrict__ near)
 {
     __shared__ int64_t s_rp[257];
+    __shared__ unsigned s_near;
+    if (threadIdx.x == 0) s_near = 0;
     const int64_t r0 = (int64_t)blockIdx.x * 256;
     const int nr = (int)(n - r0 < 256 ? n - r0 : 256);
     for (int t = threadIdx.x; t <= nr; t += 256) s_rp[t] = row_ptr[r0 + t];
     __syncthreads();
     const int64_t e1 = s_rp[nr];
     bool w = false;
+    unsigned close = 0;
     for (int64_t e = s_rp[0] + threadIdx.x; e < e1; e += 256) {
         // the row of e: the last of the block's rows that starts at or before
         // e (an empty row shares its start with the next row)
@@ -529,15 +542,20 @@ __global__ __launch_bounds__(256) void k_col_delta(const int64_t *__restrict__ r
         }
         const int64_t d = (int64_t)col[e] - (r0 + lo);
         w |= d < INT16_MIN || d > INT16_MAX;
+        close += d >= -kHalo && d <= kHalo;
         delta[e] = (int16_t)d;
     }
+    if (close) atomicAdd(&s_near, close);
     if (__ballot(w) != 0 && (threadIdx.x & 63) == 0) atomicOr(wide, 1u);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_near) atomicAdd(near, (unsigned long long)s_near);
 }
 
 hipError_t launch_col_delta(const int64_t *row_ptr, const int32_t *col, int64_t n, int16_t *delta, unsigned *wide,
-                            hipStream_t s)
+                            unsigned long long *near, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_col_delta, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, row_ptr, col, n, delta, wide);
+    hipLaunchKernelGGL(k_col_delta, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, row_ptr, col, n, delta, wide,
+                       near);
     return hipGetLastError();
 }
 

@@ -302,6 +302,25 @@ __device__ __forceinline__ int64_t logical_wave()
     return lb * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
 }
 
+// What one wave of the edge-parallel kernels works on: rows [r0, r0 + nrows)
+// and edges [e0, e0 + ne) (fewer than 2^31 rows and edges).  One 16-byte load
+// at a wave's start, where the partition and the row pointers it is made from
+// are two dependent loads.
+struct __align__(16) WaveDesc {
+    int32_t r0, nrows, e0, ne;
+};
+
+__device__ __forceinline__ WaveDesc load_desc(const WaveDesc *desc, int64_t w)
+{
+    const int4 v = *reinterpret_cast<const int4 *>(desc + w);
+    WaveDesc d;
+    d.r0 = __builtin_amdgcn_readfirstlane(v.x);
+    d.nrows = __builtin_amdgcn_readfirstlane(v.y);
+    d.e0 = __builtin_amdgcn_readfirstlane(v.z);
+    d.ne = __builtin_amdgcn_readfirstlane(v.w);
+    return d;
+}
+
 __device__ __forceinline__ unsigned lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 
 // Number of set bits of `mask` below the calling lane.
