@@ -352,10 +352,9 @@ int umap_fuzzy_graph_device(int64_t n, int32_t k, const int32_t *knn_ids, const 
  * umap_fuzzy_graph_device_noalloc -- umap_fuzzy_graph_device for callers that
  * cannot allocate device memory (code being captured into a HIP graph, tight
  * serving loops, harnesses that forbid hipMalloc): the same kernels and the
- * same result bit for bit, with its scratch (rho, sigma, the partial sums of
- * the mean distance, the error flags: about 16 n bytes + 2 MB) taken from a
- * static array that the library keeps on each GPU it runs on until the process
- * ends (about 18 MB per GPU).  It calls no hipMalloc, hipFree or allocating
+ * same result bit for bit, with its scratch (rho, sigma and the error flags:
+ * about 16 n bytes) taken from a static array that the library keeps on each
+ * GPU it runs on until the process ends (16 MB per GPU).  It calls no hipMalloc, hipFree or allocating
  * library routine.  Arguments, layout and errors as umap_fuzzy_graph_device,
  * and n <= 1,048,576 (UMAP_E_INVAL beyond).  Every call on one GPU uses that
  * GPU's one array: calls that overlap on a GPU (other host threads, other

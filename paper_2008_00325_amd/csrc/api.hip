@@ -897,16 +897,13 @@ int umap_fuzzy_graph_device(int64_t n, int32_t k, const int32_t *knn_ids, const 
     try {
         int ndev = 0;
         if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return fail(UMAP_E_DEVICE, "no HIP device available");
-        const int64_t np = ul::graph_partials(n, k);
-        size_t bytes = 2 * need<double>(n) + need<double>(np + 1) + need<unsigned>(1);
+        size_t bytes = need<double2>(n) + need<unsigned>(1);
         UL_HIP(hipMallocAsync(&scratch, bytes, s));
         Carver cv{static_cast<char *>(scratch)};
-        double *rho = cv.take<double>(n);
-        double *sigma = cv.take<double>(n);
-        double *partial = cv.take<double>(np + 1);
+        double2 *rho_sigma = cv.take<double2>(n);
         unsigned *flags = cv.take<unsigned>(1);
         UL_HIP(hipMemsetAsync(flags, 0, sizeof(unsigned), s));
-        UL_HIP(ul::launch_fuzzy_graph(n, k, knn_ids, knn_dists, rows, cols, vals, rho, sigma, partial, np, flags, s));
+        UL_HIP(ul::launch_fuzzy_graph(n, k, knn_ids, knn_dists, rows, cols, vals, rho_sigma, flags, s));
         unsigned hflags = 0;
         UL_HIP(hipMemcpyAsync(&hflags, flags, sizeof hflags, hipMemcpyDeviceToHost, s));
         UL_HIP(hipFreeAsync(scratch, s));
@@ -926,11 +923,10 @@ int umap_fuzzy_graph_device(int64_t n, int32_t k, const int32_t *knn_ids, const 
 namespace {
 
 // Scratch of umap_fuzzy_graph_device_noalloc, one copy per GPU for the life of
-// the process: rho and sigma (fp64 per row), the partial sums of the mean
-// distance (fp64, one per 4096 distances, plus the total) and the error flags,
-// for up to kNoAllocMaxRows rows (2 n k < 2^31 bounds the partial sums).
+// the process: rho and sigma (fp64 per row) and the error flags, for up to
+// kNoAllocMaxRows rows.
 constexpr int64_t kNoAllocMaxRows = (int64_t)1 << 20;
-constexpr size_t kNoAllocBytes = 2 * (((size_t)8 << 20)) + ((((size_t)1 << 18) + 1) * 8 + 255) / 256 * 256 + 256;
+constexpr size_t kNoAllocBytes = ((size_t)16 << 20) + 256;
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 // Device address of this GPU's copy of `scratch`, looked up once per device
@@ -971,17 +967,14 @@ int umap_fuzzy_graph_device_noalloc(int64_t n, int32_t k, const int32_t *knn_ids
     try {
         int ndev = 0;
         if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return fail(UMAP_E_DEVICE, "no HIP device available");
-        const int64_t np = ul::graph_partials(n, k);
         Carver cv{noalloc_scratch()};
-        double *rho = cv.take<double>(n);
-        double *sigma = cv.take<double>(n);
-        double *partial = cv.take<double>(np + 1);
+        double2 *rho_sigma = cv.take<double2>(n);
         unsigned long long *flags = cv.take<unsigned long long>(1);
         if (cv.off > kNoAllocBytes) return fail(UMAP_E_INVAL, "scratch of %zu bytes exceeds the static %zu", cv.off,
                                                 kNoAllocBytes);
         // flags start at zero (a fill kernel: no memset node if the caller captures)
         UL_HIP(ul::launch_zero_u64(flags, 1, s));
-        UL_HIP(ul::launch_fuzzy_graph(n, k, knn_ids, knn_dists, rows, cols, vals, rho, sigma, partial, np,
+        UL_HIP(ul::launch_fuzzy_graph(n, k, knn_ids, knn_dists, rows, cols, vals, rho_sigma,
                                       reinterpret_cast<unsigned *>(flags), s));
         unsigned long long hflags = 0;
         UL_HIP(hipMemcpyAsync(&hflags, flags, sizeof hflags, hipMemcpyDeviceToHost, s));

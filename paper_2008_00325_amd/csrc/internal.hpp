@@ -203,9 +203,8 @@ hipError_t launch_trustworthiness(const float *X, int64_t n, int32_t d, const fl
                                   unsigned long long *sum, unsigned *flags, hipStream_t s);
 
 // ---- fuzzy graph (kernels_graph.hip) ----
+// Scratch: rho_sigma[n] (rho_i, sigma_i) and flags[1] (zeroed by the caller).
 hipError_t launch_fuzzy_graph(int64_t n, int32_t k, const int32_t *ids, const float *dists, int32_t *rows,
-                              int32_t *cols, float *vals, double *rho, double *sigma, double *partial,
-                              int64_t npartial, unsigned *flags, hipStream_t s);
-int64_t graph_partials(int64_t n, int32_t k);
+                              int32_t *cols, float *vals, double2 *rho_sigma, unsigned *flags, hipStream_t s);
 
 }  // namespace ul

@@ -240,3 +240,39 @@ def test_random_trustworthiness_case(case):
     got = U.umap_trustworthiness(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), k)
     ref = O.trustworthiness(X, Y, k)
     assert abs(got - ref) <= 2e-6, (got, ref)
+
+
+@pytest.mark.parametrize("n,k", [(65, 2), (200, 8), (1000, 9), (127, 16), (640, 17), (1003, 32), (700, 33), (300, 64),
+                                 (300, 65), (400, 130)])
+def test_fuzzy_graph_row_lengths(n, k):
+    """The device fuzzy graph at the row lengths where its kernels change (rows
+    in registers up to 8, 16, 32 and 64, looked up by as many lanes, then in
+    pieces), with rows of every scale of distance, ties, repeated neighbours
+    and unsorted entries: the same slots and, within one fp32 ulp, the same
+    values as an fp64 evaluation."""
+    import torch
+
+    print(f"[gpu case] fuzzy graph n {n} k {k}", flush=True)
+    rng = np.random.default_rng(n * 131 + k)
+    ids = np.stack([rng.permutation(n)[:k] for _ in range(n)]).astype(np.int32)
+    dist = np.cumsum(rng.exponential(1.0, size=(n, k)), axis=1) * 10.0 ** rng.integers(-12, 13, size=(n, 1))
+    dist[rng.random(n) < 0.1] = 0.0
+    dist[rng.random((n, k)) < 0.05] = 0.0
+    dist[::7] = np.round(dist[::7])
+    dist = np.take_along_axis(dist, rng.permuted(np.tile(np.arange(k), (n, 1)), axis=1), axis=1).astype(np.float32)
+    ids[3, 1] = ids[3, 0]   # a neighbour listed twice: its last entry counts
+    rows, cols, vals = (torch.empty(2 * n * k, dtype=t, device="cuda") for t in (torch.int32, torch.int32, torch.float32))
+    U.umap_fuzzy_graph_device(n, k, torch.from_numpy(ids).cuda(), torch.from_numpy(dist).cuda(), rows, cols, vals)
+    rows, cols, vals = (t.cpu().numpy() for t in (rows, cols, vals))
+    A = O.membership(dist, *O.smooth_knn(dist)).reshape(-1)
+    at = {}
+    for t in range(n * k):
+        at[(t // k, int(ids.flat[t]))] = t
+    for t in range(n * k):
+        i, j = t // k, int(ids.flat[t])
+        back = at.get((j, i)) if i != j else None
+        b = 0.0 if i == j else A[t] + (A[back] if back is not None else 0.0) * (1.0 - A[t])
+        assert (rows[t], cols[t]) == (i, j)
+        assert abs(float(vals[t]) - b) <= 2.0 ** -23 * b + 1e-30
+        s = n * k + t
+        assert (rows[s], cols[s], vals[s]) == ((i, i, 0.0) if back is not None else (j, i, vals[t]))
