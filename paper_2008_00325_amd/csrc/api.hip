@@ -265,19 +265,29 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         B.n_cols = h->n_table;
         B.bipartite = table != nullptr;
         B.n_epochs = n_epochs;
-        B.nblocks_scan = ul::scan_blocks(n);
-        size_t sbytes = 2 * need<int32_t>(n) + 2 * need<int32_t>(nnz) + 2 * need<float>(nnz) +
-                        need<int64_t>(B.nblocks_scan) + need<ul::PrepScalars>(1);
+        const int64_t nb = ul::bucket_count(n), nc = ul::bucket_counters(n), nrb = ul::row_blocks(n),
+                      n_long = ul::long_row_slots(nnz);
+        size_t sbytes = 2 * need<uint32_t>(nc) + need<int32_t>(ul::kSubs * nb + 1) + need<int32_t>(nb + 1) +
+                        need<uint32_t>(nb) + 3 * need<int32_t>(nrb) +
+                        2 * need<int2>(nnz) + need<uint16_t>(nnz) + need<int32_t>(n) + need<int32_t>(n + 1) +
+                        need<int32_t>(n_long) + need<ul::PrepScalars>(1);
         if (host_inputs) sbytes += 2 * need<int32_t>(nnz) + need<float>(nnz);
         UL_HIP(hipMallocAsync(&scratch, sbytes, stream));
         Carver sc{static_cast<char *>(scratch)};
-        B.deg = sc.take<int32_t>(n);
-        B.cursor = sc.take<int32_t>(n);
-        B.trow = sc.take<int32_t>(nnz);
-        B.tcol = sc.take<int32_t>(nnz);
-        B.tval = sc.take<float>(nnz);
-        B.sval = sc.take<float>(nnz);
-        B.bsum = sc.take<int64_t>(B.nblocks_scan);
+        B.bucket_n = sc.take<uint32_t>(nc);
+        B.cursor = sc.take<uint32_t>(nc);
+        B.first = sc.take<int32_t>(ul::kSubs * nb + 1);
+        B.kfirst = sc.take<int32_t>(nb + 1);
+        B.kept_n = sc.take<uint32_t>(nb);
+        B.pair = sc.take<int2>(nnz);
+        B.pair_rows = sc.take<int2>(nnz);
+        B.lrow = sc.take<uint16_t>(nnz);
+        B.lstart = sc.take<int32_t>(n);
+        B.rp32 = sc.take<int32_t>(n + 1);
+        B.long_rows = sc.take<int32_t>(n_long);
+        B.block_max = sc.take<int32_t>(nrb);
+        B.block_near = sc.take<int32_t>(nrb);
+        B.block_diff = sc.take<int32_t>(nrb);
         B.scalars = sc.take<ul::PrepScalars>(1);
         if (host_inputs) {
             int32_t *dr = sc.take<int32_t>(nnz);
@@ -299,10 +309,9 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         B.row_ptr = h->row_ptr;
         B.col = h->col;
         B.eps = h->eps;
+        B.col16 = table ? nullptr : h->col16;
 
         UL_HIP(hipEventRecord(h->ev[0], stream));
-        UL_HIP(hipMemsetAsync(B.deg, 0, 2 * need<int32_t>(n), stream));   // deg and cursor are adjacent
-        UL_HIP(hipMemsetAsync(B.scalars, 0, sizeof(ul::PrepScalars), stream));
         UL_HIP(ul::launch_prep(B, stream));
         UL_HIP(hipEventRecord(h->ev[1], stream));
 
@@ -320,7 +329,7 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
                        : fail(UMAP_E_INVAL, "a row or column index is outside [0, n)");
         else if (S.flags & ul::kBadValue) rc = fail(UMAP_E_INVAL, "a value is not finite");
         else if (S.flags & ul::kDuplicate) rc = fail(UMAP_E_INVAL, "an edge (i, j) is listed more than once");
-        else if (S.flags & ul::kAsymmetric)
+        else if ((S.flags & ul::kAsymmetric) || (!table && S.up_minus_low != 0))
             rc = fail(UMAP_E_ASYMMETRIC, "the graph is not symmetric: a kept (i, j, v) has no (j, i) with equal v");
         else if ((int64_t)S.max_degree * (8 + 4 * (int64_t)neg_rate) >= ((int64_t)1 << 31))
             rc = fail(UMAP_E_INVAL, "a row of %d edges is too long for the fixed-point accumulator", S.max_degree);
@@ -339,21 +348,11 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         if (h->n_waves < 1) h->n_waves = 1;
         if (h->n_waves > max_waves) throw HipFailure{hipErrorInvalidValue, "wave count exceeds the arena"};
         UL_HIP(ul::launch_partition(h->row_ptr, 0, n, dim, cost, h->part, h->desc, h->n_waves, h->head, stream));
-        if (!table && kept > 0) {
-            // a fit's tails as 16-bit offsets from their rows, where they all
-            // fit and at least half lie within the halo that the kernels of
-            // 1-2 components stage with them (a shuffled graph gets nothing
-            // from the halo's LDS)
-            unsigned wide = 1;
-            unsigned long long near = 0;
-            UL_HIP(hipMemsetAsync(h->overflow, 0, sizeof(unsigned), stream));
-            UL_HIP(hipMemsetAsync(h->active_sum, 0, sizeof near, stream));
-            UL_HIP(ul::launch_col_delta(h->row_ptr, h->col, n, h->col16, h->overflow, h->active_sum, stream));
-            UL_HIP(hipMemcpyAsync(&wide, h->overflow, sizeof wide, hipMemcpyDeviceToHost, stream));
-            UL_HIP(hipMemcpyAsync(&near, h->active_sum, sizeof near, hipMemcpyDeviceToHost, stream));
-            UL_HIP(hipStreamSynchronize(stream));
-            h->col16_ok = wide == 0 && 2 * (int64_t)near >= kept;
-        }
+        // a fit's tails are read as 16-bit offsets from their rows where they all
+        // fit and at least half lie within the halo that the kernels of 1-2
+        // components stage with them (a shuffled graph gets nothing from the
+        // halo's LDS)
+        h->col16_ok = !table && kept > 0 && !(S.flags & ul::kWide) && 2 * (int64_t)S.near >= kept;
         float ms = 0;
         UL_HIP(hipEventElapsedTime(&ms, h->ev[0], h->ev[1]));
         h->st.prep_ms = ms;

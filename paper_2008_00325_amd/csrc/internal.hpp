@@ -17,6 +17,7 @@ enum PrepFlag : unsigned {
     kBadValue = 2u,
     kDuplicate = 4u,
     kAsymmetric = 8u,
+    kWide = 16u,   // a tail's offset from its row needs more than 16 bits (no error)
 };
 
 // Device-resident scalars of the ingest.
@@ -24,7 +25,9 @@ struct PrepScalars {
     unsigned flags;
     unsigned wmax_bits;   // bits of the largest kept candidate weight (> 0)
     int max_degree;
-    int pad;
+    int n_long;           // rows of the long-row list
+    unsigned long long near;   // tails within kHalo of their row
+    long long up_minus_low;    // entries above minus entries below the diagonal
 };
 
 // Work split of the wavefront epoch kernels: wave w owns the whole rows
@@ -64,35 +67,43 @@ struct PrepBuffers {
     int64_t n_cols;     // columns are in [0, n_cols); n unless bipartite
     bool bipartite;     // rows and columns are different vertex sets (no self loops, no symmetry)
     int32_t n_epochs;
-    // scratch (device, capacity nnz or n)
-    int32_t *deg;       // n
-    int32_t *cursor;    // n
-    int32_t *trow;      // nnz
-    int32_t *tcol;      // nnz
-    float *tval;        // nnz
-    float *sval;        // nnz, values in sorted order
-    int64_t *bsum;      // scan partials
-    int64_t nblocks_scan;
+    // scratch (device); nb = bucket_count(n)
+    uint32_t *bucket_n;   // bucket_counters(n): candidates per bucket, a cache line apart
+    uint32_t *cursor;     // bucket_counters(n)
+    int32_t *first;       // kSubs nb + 1
+    uint32_t *kept_n;     // nb
+    int32_t *kfirst;      // nb + 1
+    int2 *pair;           // nnz entries (col, value bits) by bucket, later in (row, col) order
+    uint16_t *lrow;       // nnz, their rows in the bucket
+    int2 *pair_rows;      // nnz, by row
+    int32_t *lstart;      // n
+    int32_t *rp32;        // n + 1, row_ptr in 32 bits
+    int32_t *long_rows;   // long_row_slots(nnz)
+    int32_t *block_max;   // row_blocks(n), per-block parts of the scalars
+    int32_t *block_near;  // row_blocks(n)
+    int32_t *block_diff;  // row_blocks(n)
     PrepScalars *scalars;
     // outputs (device)
     int64_t *row_ptr;   // n + 1
     int32_t *col;       // nnz (capacity)
     float *eps;         // nnz (capacity)
+    int16_t *col16;     // nnz (capacity), col - row; null when bipartite
 };
 
-int64_t scan_blocks(int64_t n);
+// An entry's bucket is counted and filled in one of kSubs parts, by its tile, so
+// that the workgroups of one XCD (tiles are dealt round-robin) share counters
+// with each other only.
+constexpr int kSubs = 8;
+int64_t bucket_count(int64_t n);
+int64_t bucket_counters(int64_t n);
+int64_t row_blocks(int64_t n);
+int64_t long_row_slots(int64_t nnz);
 hipError_t launch_prep(const PrepBuffers &B, hipStream_t s);
 // Waves over rows [r0, r1) (0 <= r0 < r1); n_waves = ceil(units / cost) for
 // the units (edges + row_weight x rows) of the range.
 hipError_t launch_partition(const int64_t *row_ptr, int64_t r0, int64_t r1, int32_t dim, int64_t cost,
                             int32_t *part, WaveDesc *desc, int64_t n_waves, uint8_t *head, hipStream_t s);
 hipError_t launch_zero_u64(unsigned long long *p, int64_t count, hipStream_t s);
-// delta[e] = col[e] - row(e) as int16 for the n rows; *wide = 1 when some delta
-// needs more than 16 bits, *near += the deltas of at most kHalo (both must
-// start at 0).
-hipError_t launch_col_delta(const int64_t *row_ptr, const int32_t *col, int64_t n, int16_t *delta, unsigned *wide,
-                            unsigned long long *near, hipStream_t s);
-
 // ---- layout (kernels_layout.hip) ----
 hipError_t launch_init(float *E, int64_t n, int32_t dim, uint64_t seed, hipStream_t s);
 hipError_t launch_init_transform(const int64_t *row_ptr, const int32_t *col, const float *eps, const float *T,

@@ -2,28 +2,30 @@
 // section: the COO list is sorted by row and indexed by a CSR row pointer).
 //
 // Steps (all on the handle's stream, one host synchronisation at the end):
-//   1. check indices and values; w_max = largest weight of a candidate edge
-//      (val > 0, row != col; a bipartite graph -- new points to a frozen
-//      table -- keeps row == col, which are different vertices there)
-//   2. count kept edges per row (candidates with val >= w_max / n_epochs)
-//   3. exclusive scan of the counts -> row_ptr (int64), largest row
-//   4. scatter kept edges into their row's segment (order inside a row is
-//      arbitrary at this point)
-//   5. sort each row by column, and compute eps = w_max / val: rows of up to
-//      kLongRow entries by a rank sort (the rank of an entry is the number of
-//      smaller columns in its row; equal columns flag a duplicate), longer
-//      rows by a stable radix sort of their columns, one workgroup per row
-//      (equal neighbours after it flag a duplicate)
-//   6. symmetry (not for a bipartite graph): each kept (i, j, v) must find
-//      (j, i) with bit-equal v by binary search in row j
-//   7. wave partition for the epoch kernel
+//   1. k_check: indices and values checked, w_max = the largest weight of a
+//      candidate edge (val > 0, row != col; a bipartite graph -- new points to a
+//      frozen table -- keeps row == col, which are different vertices there),
+//      candidates counted per bucket of 2^lg consecutive rows
+//   2. k_bucket_scatter: the candidates filed by bucket, a tile of 8K entries at
+//      a time, so that a bucket gets runs of a tile's entries
+//   3. k_bucket_rows: one workgroup per bucket drops what lies below
+//      w_max / n_epochs, counts its rows in LDS and files the rest by row
+//   4. k_row_sort: 16 rows at a time sorted by column in LDS (rank sort; equal
+//      columns flag a duplicate); row_ptr, col, eps = w_max / val and the tails
+//      as 16-bit offsets written.  Rows of more than kLongRow entries by
+//      k_long_row_sort, a stable radix sort, one workgroup per row
+//   5. k_symmetry (not for a bipartite graph): each kept (i, j, v) must have
+//      a (j, i) with bit-equal v
+//   6. wave partition for the epoch kernel
+//
+// Each entry is read twice and written three times, in runs; the former count
+// and scatter with one global atomic and three 4-byte stores per entry at
+// random rows took 1640 us on 30M shuffled entries (1M rows), where steps 2-3
+// take 300, and its rank sort from memory 396 us (step 4 now 150).
 #include "internal.hpp"
 
 namespace ul {
 
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 8;
-constexpr int kScanTile = kScanThreads * kScanItems;
 
 // rows in [0, n), columns in [0, n_cols); bipartite: row and column index
 // different vertex sets
@@ -56,37 +58,6 @@ __device__ __forceinline__ unsigned wave_max(unsigned v)
     return v;
 }
 
-__global__ __launch_bounds__(256) void k_check_max(const int32_t *__restrict__ rows, const int32_t *__restrict__ cols,
-                                                   const float *__restrict__ vals, int64_t nnz, IngestShape sh,
-                                                   PrepScalars *S)
-{
-    unsigned flags = 0, mx = 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < nnz; t += stride) {
-        int32_t r = rows[t], c = cols[t];
-        float v = vals[t];
-        if ((uint32_t)r >= sh.n || (uint32_t)c >= sh.n_cols) flags |= kBadIndex;
-        if (!isfinite(v)) flags |= kBadValue;
-        if (candidate(r, c, v, sh)) mx = max(mx, __float_as_uint(v));  // positive floats order as integers
-    }
-    // one atomic per block: every block has a candidate weight, and atomics
-    // from thousands of waves on one address would serialise
-    flags = wave_or(flags);
-    mx = wave_max(mx);
-    __shared__ unsigned s_flags[4], s_max[4];
-    if ((threadIdx.x & 63) == 0) {
-        s_flags[threadIdx.x >> 6] = flags;
-        s_max[threadIdx.x >> 6] = mx;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned f = s_flags[0] | s_flags[1] | s_flags[2] | s_flags[3];
-        const unsigned m = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
-        if (f) atomicOr(&S->flags, f);
-        if (m) atomicMax(&S->wmax_bits, m);
-    }
-}
-
 // Slot of the calling lane in the counter ctr[key], with one atomic add per
 // run of consecutive lanes that hold the same key (inactive lanes end a run):
 // the counter's old value plus the lane's rank in its run.  Kernel-built
@@ -112,294 +83,644 @@ __device__ __forceinline__ int32_t run_atomic_add(int32_t *ctr, int32_t key, boo
     return __shfl(base, h) + lane - h;
 }
 
-__global__ __launch_bounds__(256) void k_count(const int32_t *__restrict__ rows, const int32_t *__restrict__ cols,
-                                               const float *__restrict__ vals, int64_t nnz, IngestShape sh,
-                                               int32_t n_epochs, const PrepScalars *S, int32_t *__restrict__ deg)
-{
-    const float thresh = keep_threshold(S, n_epochs);
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    // wave-uniform trip count: run_atomic_add needs the whole wave
-    for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63u); t0 < nnz; t0 += stride) {
-        const int64_t t = t0 + (threadIdx.x & 63u);
-        const bool in = t < nnz;
-        const int32_t r = in ? rows[t] : 0, c = in ? cols[t] : 0;
-        const float v = in ? vals[t] : 0.0f;
-        const bool keep = in && candidate(r, c, v, sh) && v >= thresh;
-        run_atomic_add(deg, r, keep);
-    }
-}
+// Buckets of consecutive rows: 2^lg rows each, at least kSortRows (the rows of a
+// k_row_sort block lie in one bucket) and at most 2^16 (an entry's row in its
+// bucket is a 16-bit number), about kBuckets of them where that allows.
+constexpr int kSortRows = 32;
+constexpr int kBuckets = 1024;
+constexpr int kMinBucketLg = 8, kMaxBucketLg = 16;
+// counters of buckets lie a cache line apart: workgroups add to all of them
+constexpr int kPad = 32;
+constexpr int kTileThreads = 1024;
+constexpr int kTileItems = 8;
+constexpr int kTile = kTileThreads * kTileItems;
+// rows of a bucket counted in LDS at a time
+constexpr int kBucketRows = 8192;
 
-// Inclusive scan of one value per thread across a 256-thread block.
-__device__ __forceinline__ int64_t block_inclusive_scan(int64_t x, int64_t *s_wave)
+int32_t bucket_lg(int64_t n)
 {
-    const unsigned lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        int64_t y = __shfl_up(x, off);
-        if (lane >= (unsigned)off) x += y;
-    }
-    if (lane == 63) s_wave[wv] = x;
-    __syncthreads();
-    int64_t add = 0;
-    for (unsigned k = 0; k < wv; ++k) add += s_wave[k];
-    __syncthreads();
-    return x + add;
+    int32_t lg = kMinBucketLg;
+    while (lg < kMaxBucketLg && (n >> lg) >= kBuckets) ++lg;
+    return lg;
 }
+int64_t bucket_count(int64_t n) { return (n + ((int64_t)1 << bucket_lg(n)) - 1) >> bucket_lg(n); }
+int64_t bucket_counters(int64_t n) { return kPad * kSubs * bucket_count(n); }
+int64_t row_blocks(int64_t n) { return (n + kSortRows - 1) / kSortRows; }
+// counter of part `sub` of bucket b
+__device__ __forceinline__ int64_t counter_at(int32_t sub, int32_t b, int32_t nb) { return ((int64_t)sub * nb + b) * kPad; }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const int32_t *__restrict__ deg, int64_t n,
-                                                              int64_t *__restrict__ bsum, PrepScalars *S)
+__global__ __launch_bounds__(kTileThreads) void k_check(const int32_t *__restrict__ rows,
+                                                        const int32_t *__restrict__ cols,
+                                                        const float *__restrict__ vals, int64_t nnz, IngestShape sh,
+                                                        int32_t lg, int32_t nb, uint32_t *__restrict__ bucket_n,
+                                                        PrepScalars *S)
 {
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    int64_t s = 0;
-    int mx = 0;
+    extern __shared__ int32_t s_n[];   // nb counters
+    __shared__ unsigned s_flags, s_max;
+    for (int32_t b = threadIdx.x; b < nb; b += kTileThreads) s_n[b] = 0;
+    if (threadIdx.x == 0) s_flags = s_max = 0;
+    __syncthreads();
+    unsigned flags = 0, mx = 0;
+    // the grid is a multiple of kSubs: a block's tiles are of one part
+    for (int64_t t0 = (int64_t)blockIdx.x * kTile; t0 < nnz; t0 += (int64_t)gridDim.x * kTile) {
+        int32_t r[kTileItems], c[kTileItems];
+        float v[kTileItems];
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k)
-        if (base + k < n) {
-            int v = deg[base + k];
-            s += v;
-            mx = max(mx, v);
+        for (int q = 0; q < kTileItems; ++q) {
+            const int64_t t = t0 + q * kTileThreads + threadIdx.x;
+            const bool in = t < nnz;
+            r[q] = in ? rows[t] : 0;
+            c[q] = in ? cols[t] : 0;
+            v[q] = in ? vals[t] : 0.0f;   // 0: not a candidate
         }
-    __shared__ int64_t s_wave[4];
-    int64_t inc = block_inclusive_scan(s, s_wave);
-    if (threadIdx.x == kScanThreads - 1) bsum[blockIdx.x] = inc;
-    mx = (int)wave_max((unsigned)mx);
-    if ((threadIdx.x & 63) == 0 && mx) atomicMax(&S->max_degree, mx);
+#pragma unroll
+        for (int q = 0; q < kTileItems; ++q) {
+            if ((uint32_t)r[q] >= sh.n || (uint32_t)c[q] >= sh.n_cols) flags |= kBadIndex;   // (0, 0) past the end is none
+            if (!isfinite(v[q])) flags |= kBadValue;
+            const bool cand = candidate(r[q], c[q], v[q], sh);
+            if (cand) mx = max(mx, __float_as_uint(v[q]));  // positive floats order as integers
+            run_atomic_add(s_n, cand ? r[q] >> lg : 0, cand);
+        }
+    }
+    flags = wave_or(flags);
+    mx = wave_max(mx);
+    if ((threadIdx.x & 63) == 0) {
+        if (flags) atomicOr(&s_flags, flags);
+        if (mx) atomicMax(&s_max, mx);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (s_flags) atomicOr(&S->flags, s_flags);
+        if (s_max) atomicMax(&S->wmax_bits, s_max);
+    }
+    for (int32_t b = threadIdx.x; b < nb; b += kTileThreads)
+        if (s_n[b]) atomicAdd(&bucket_n[counter_at(blockIdx.x % kSubs, b, nb)], (uint32_t)s_n[b]);
 }
 
-// Exclusive scan of the block sums in place (one block, loops over chunks).
-__global__ __launch_bounds__(kScanThreads) void k_scan_top(int64_t *__restrict__ bsum, int64_t nb)
+// first[t] = n[0] + ... + n[t - 1] for t <= count (one block, loops over chunks).
+// COUNTERS: n[b kSubs + sub] is the counter of part sub of bucket b, and its
+// cursor starts at first[t]; else n[t] = in[t].
+template <bool COUNTERS>
+__global__ __launch_bounds__(kTileThreads) void k_bucket_scan(const uint32_t *__restrict__ in, int32_t count,
+                                                              int32_t *__restrict__ first, uint32_t *__restrict__ cursor)
 {
-    __shared__ int64_t s_wave[4];
-    __shared__ int64_t s_carry;
-    if (threadIdx.x == 0) s_carry = 0;
-    __syncthreads();
-    for (int64_t base = 0; base < nb; base += kScanThreads) {
-        int64_t t = base + threadIdx.x;
-        int64_t v = t < nb ? bsum[t] : 0;
-        int64_t inc = block_inclusive_scan(v, s_wave);
-        int64_t carry = s_carry;
-        if (t < nb) bsum[t] = carry + inc - v;
+    __shared__ int32_t s_wave[kTileThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    int32_t carry = 0;
+    for (int32_t base = 0; base < count; base += kTileThreads) {
+        const int32_t t = base + tid;
+        const int64_t at = COUNTERS ? counter_at(t % kSubs, t / kSubs, count / kSubs) : t;
+        const int32_t v = t < count ? (int32_t)in[at] : 0;
+        int32_t x = v;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t y = __shfl_up(x, off);
+            if (lane >= off) x += y;
+        }
+        if (lane == 63) s_wave[wv] = x;
         __syncthreads();
-        if (threadIdx.x == kScanThreads - 1) s_carry = carry + inc;
+        int32_t before = 0, total = 0;
+#pragma unroll
+        for (int k = 0; k < kTileThreads / 64; ++k) {
+            before += k < wv ? s_wave[k] : 0;
+            total += s_wave[k];
+        }
+        if (t < count) {
+            first[t] = carry + before + x - v;
+            if (COUNTERS) cursor[at] = (uint32_t)(carry + before + x - v);
+        }
+        carry += total;
         __syncthreads();
     }
+    if (tid == 0) first[count] = carry;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t *__restrict__ deg, int64_t n,
-                                                            const int64_t *__restrict__ boff,
-                                                            int64_t *__restrict__ row_ptr, int64_t nb)
+// A tile of entries filed by bucket: ranks in LDS counters, one reservation per
+// tile and bucket.  Bound by its streams: 360 MB read and 300 MB written.
+__global__ __launch_bounds__(kTileThreads) void k_bucket_scatter(const int32_t *__restrict__ rows,
+                                                                 const int32_t *__restrict__ cols,
+                                                                 const float *__restrict__ vals, int64_t nnz,
+                                                                 IngestShape sh, int32_t lg, int32_t nb,
+                                                                 uint32_t *__restrict__ cursor,
+                                                                 int2 *__restrict__ pair, uint16_t *__restrict__ lrow)
 {
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    int v[kScanItems];
-    int64_t s = 0;
+    extern __shared__ int32_t s_n[];   // nb counters, then the tile's first slots
+    for (int32_t b = threadIdx.x; b < nb; b += kTileThreads) s_n[b] = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * kTile;
+    int32_t r[kTileItems], c[kTileItems], rank[kTileItems];
+    float v[kTileItems];
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        v[k] = base + k < n ? deg[base + k] : 0;
-        s += v[k];
-    }
-    __shared__ int64_t s_wave[4];
-    int64_t run = block_inclusive_scan(s, s_wave) - s + boff[blockIdx.x];
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k)
-        if (base + k < n) {
-            row_ptr[base + k] = run;
-            run += v[k];
-        }
-    // the last block also writes the total
-    if (blockIdx.x == nb - 1 && threadIdx.x == kScanThreads - 1) row_ptr[n] = run;
-}
-
-__global__ __launch_bounds__(256) void k_scatter(const int32_t *__restrict__ rows, const int32_t *__restrict__ cols,
-                                                 const float *__restrict__ vals, int64_t nnz, IngestShape sh,
-                                                 int32_t n_epochs, const PrepScalars *S,
-                                                 const int64_t *__restrict__ row_ptr, int32_t *__restrict__ cursor,
-                                                 int32_t *__restrict__ trow, int32_t *__restrict__ tcol,
-                                                 float *__restrict__ tval)
-{
-    const float thresh = keep_threshold(S, n_epochs);
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t t0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63u); t0 < nnz; t0 += stride) {
-        const int64_t t = t0 + (threadIdx.x & 63u);
+    for (int q = 0; q < kTileItems; ++q) {
+        const int64_t t = base + q * kTileThreads + threadIdx.x;
         const bool in = t < nnz;
-        const int32_t r = in ? rows[t] : 0, c = in ? cols[t] : 0;
-        const float v = in ? vals[t] : 0.0f;
-        const bool keep = in && candidate(r, c, v, sh) && v >= thresh;
-        const int32_t slot = run_atomic_add(cursor, r, keep);
-        if (keep) {
-            const int64_t p = row_ptr[r] + slot;
-            trow[p] = r;
-            tcol[p] = c;
-            tval[p] = v;
-        }
+        r[q] = in ? rows[t] : 0;
+        c[q] = in ? cols[t] : 0;
+        v[q] = in ? vals[t] : 0.0f;   // 0: not a candidate
     }
+#pragma unroll
+    for (int q = 0; q < kTileItems; ++q) {
+        const bool cand = candidate(r[q], c[q], v[q], sh);
+        const int32_t slot = run_atomic_add(s_n, cand ? r[q] >> lg : 0, cand);
+        rank[q] = cand ? slot : -1;
+    }
+    __syncthreads();
+    for (int32_t b = threadIdx.x; b < nb; b += kTileThreads) {
+        const int32_t m = s_n[b];
+        if (m) s_n[b] = (int32_t)atomicAdd(&cursor[counter_at(blockIdx.x % kSubs, b, nb)], (uint32_t)m);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kTileItems; ++q) {
+        if (rank[q] < 0) continue;
+        const uint32_t p = (uint32_t)(s_n[r[q] >> lg] + rank[q]);
+        pair[p] = make_int2(c[q], __float_as_int(v[q]));
+        lrow[p] = (uint16_t)(r[q] & ((1 << lg) - 1));
+    }
+}
+
+// One workgroup per bucket: its kept entries counted per row in LDS and filed by
+// row into `out`, from the bucket's first slot on.  lstart[row] = the row's
+// first entry counted from there, kept_n[bucket] = its kept entries.  Buckets of
+// more rows than the counters hold take them kBucketRows at a time.
+__global__ __launch_bounds__(kTileThreads) void k_bucket_rows(const int2 *__restrict__ pair,
+                                                              const uint16_t *__restrict__ lrow,
+                                                              const int32_t *__restrict__ first, int64_t n, int32_t lg,
+                                                              int32_t n_epochs, const PrepScalars *S,
+                                                              int2 *__restrict__ out, int32_t *__restrict__ lstart,
+                                                              uint32_t *__restrict__ kept_n)
+{
+    constexpr int kAhead = 8;   // loads of a thread in flight
+    __shared__ int32_t s_n[kBucketRows];
+    __shared__ int32_t s_wave[kTileThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const float thresh = keep_threshold(S, n_epochs);
+    const int32_t e0 = first[blockIdx.x * kSubs], e1 = first[(blockIdx.x + 1) * kSubs];
+    const int64_t row0 = (int64_t)blockIdx.x << lg;
+    const int32_t rows = (int32_t)(n - row0 < ((int64_t)1 << lg) ? n - row0 : (int64_t)1 << lg);
+    int32_t done = 0;   // kept entries of the rows before
+    for (int32_t a = 0; a < rows; a += kBucketRows) {
+        const int32_t m = rows - a < kBucketRows ? rows - a : kBucketRows;
+        for (int32_t t = tid; t < m; t += kTileThreads) s_n[t] = 0;
+        __syncthreads();
+        for (int32_t c0 = e0; c0 < e1; c0 += kAhead * kTileThreads) {
+            uint32_t q[kAhead];
+            float v[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int32_t e = c0 + u * kTileThreads + tid;
+                q[u] = 0xFFFFFFFFu;
+                if (e < e1) {
+                    q[u] = (uint32_t)lrow[e] - (uint32_t)a;
+                    v[u] = __int_as_float(pair[e].y);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                if (q[u] < (uint32_t)m && v[u] >= thresh) atomicAdd(&s_n[q[u]], 1);
+        }
+        __syncthreads();
+        // exclusive scan of the m counters, kTileThreads at a time
+        for (int32_t b = 0; b < m; b += kTileThreads) {
+            const int32_t t = b + tid;
+            const int32_t v = t < m ? s_n[t] : 0;
+            int32_t x = v;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int32_t y = __shfl_up(x, off);
+                if (lane >= off) x += y;
+            }
+            if (lane == 63) s_wave[wv] = x;
+            __syncthreads();
+            int32_t before = 0, total = 0;
+#pragma unroll
+            for (int k = 0; k < kTileThreads / 64; ++k) {
+                before += k < wv ? s_wave[k] : 0;
+                total += s_wave[k];
+            }
+            if (t < m) {
+                const int32_t start = done + before + x - v;
+                s_n[t] = start;
+                lstart[row0 + a + t] = start;
+            }
+            done += total;
+            __syncthreads();
+        }
+        for (int32_t c0 = e0; c0 < e1; c0 += kAhead * kTileThreads) {
+            uint32_t q[kAhead];
+            int2 p[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int32_t e = c0 + u * kTileThreads + tid;
+                q[u] = 0xFFFFFFFFu;
+                if (e < e1) {
+                    q[u] = (uint32_t)lrow[e] - (uint32_t)a;
+                    p[u] = pair[e];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                if (q[u] < (uint32_t)m && __int_as_float(p[u].y) >= thresh) out[e0 + atomicAdd(&s_n[q[u]], 1)] = p[u];
+        }
+        __syncthreads();
+    }
+    if (tid == 0) kept_n[blockIdx.x] = (uint32_t)done;
 }
 
 // Rows longer than this are sorted by k_long_row_sort: the rank sort reads a
-// row once per entry, deg^2 loads in all.
-constexpr int64_t kLongRow = 2048;
+// row once per entry, deg^2 LDS reads in all.
+constexpr int32_t kLongRow = 512;
 constexpr int kSortThreads = 1024;
 constexpr int kSortWaves = kSortThreads / 64;
+constexpr int kRowTile = 1024;   // entries of consecutive rows in LDS at a time (8 blocks per CU)
 
-__global__ __launch_bounds__(256) void k_row_sort(const int32_t *__restrict__ trow, const int32_t *__restrict__ tcol,
-                                                  const float *__restrict__ tval, const int64_t *__restrict__ row_ptr,
-                                                  int64_t n, PrepScalars *S, int32_t *__restrict__ col,
-                                                  float *__restrict__ sval, float *__restrict__ eps)
+// What k_row_sort and k_long_row_sort write, beside the row pointers.
+struct SortedRows {
+    int32_t *col;
+    float *eps;
+    int2 *pair;        // (col, value bits): the symmetry check's copy
+    int16_t *col16;    // col - row (null: bipartite)
+};
+
+// kSortRows rows per block.  src: the rows' entries in any order, from
+// first[bucket kSubs] + lstart[row] on; out: in (row, col) order.  Rank sort: an
+// entry's slot is the number of smaller columns in its row, read from LDS four
+// at a time (the rows are padded to multiples of four there); the entries are
+// put in order in LDS and written in runs.  A slot left empty is a duplicate.
+// (26.7M entries, 1M rows: 475 us reading the row entry by entry and writing
+// each entry at its slot.)
+__global__ __launch_bounds__(256) void k_row_sort(const int2 *__restrict__ src, const int32_t *__restrict__ first,
+                                                  const int32_t *__restrict__ kfirst,
+                                                  const int32_t *__restrict__ lstart, int64_t n, int32_t lg,
+                                                  PrepScalars *S, int64_t *__restrict__ row_ptr,
+                                                  int32_t *__restrict__ rp32, int32_t *__restrict__ long_rows,
+                                                  int32_t *__restrict__ block_near, int32_t *__restrict__ block_max,
+                                                  SortedRows out)
 {
-    const int64_t kept = row_ptr[n];
+    __shared__ __align__(16) int32_t s_col[kRowTile + 4 * kSortRows];   // columns by padded row
+    __shared__ int2 s_out[kRowTile];
+    __shared__ uint8_t s_row[kRowTile];
+    __shared__ int32_t s_start[kSortRows + 1], s_pad[kSortRows + 1];
+    __shared__ unsigned s_flags, s_near;
+    const int tid = threadIdx.x;
+    const int64_t r0 = (int64_t)blockIdx.x * kSortRows;
+    const int nr = (int)(n - r0 < kSortRows ? n - r0 : kSortRows);
+    const int64_t b = r0 >> lg;
+    const int32_t dst = kfirst[b];
+    const int2 *const in = src + first[b * kSubs];
     const float w_max = __uint_as_float(S->wmax_bits);
-    unsigned flags = 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < kept; p += stride) {
-        const int32_t r = trow[p];
-        const int32_t c = tcol[p];
-        const int64_t rs = row_ptr[r], re = row_ptr[r + 1];
-        if (re - rs > kLongRow) continue;   // k_long_row_sort
-        // rank of c in its row; eight loads of the row in flight at a time
-        int64_t rank = 0;
-        for (int64_t q0 = rs; q0 < re; q0 += 8) {
-            int32_t cq[8];
+    // the rows' first entries, as uniform values (scalar loads) and in LDS
+    int32_t ustart[kSortRows];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) cq[u] = q0 + u < re ? tcol[q0 + u] : INT32_MAX;
+    for (int k = 0; k < kSortRows; ++k) ustart[k] = k < nr ? lstart[r0 + k] : INT32_MAX;
+    if (tid <= nr) {
+        const int64_t r = r0 + tid;
+        // past the last row of a bucket: the bucket's kept entries
+        const int32_t st = r < n && (tid < nr || (r >> lg) == b) ? lstart[r] : kfirst[b + 1] - dst;
+        s_start[tid] = st;
+        if (tid < nr || r == n) {
+            row_ptr[r] = (int64_t)dst + st;
+            rp32[r] = dst + st;
+        }
+    }
+    if (tid == 0) s_flags = s_near = 0;
+    __syncthreads();
+    if (tid < 64) {   // kSortRows < 64
+        const int32_t len = tid < nr ? s_start[tid + 1] - s_start[tid] : 0;
+        // the rows' places in s_col
+        int32_t x = (len + 3) & ~3;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                rank += cq[u] < c;
-                if (cq[u] == c && q0 + u != p) flags |= kDuplicate;
+        for (int off = 1; off < 2 * kSortRows; off <<= 1) {
+            const int32_t y = __shfl_up(x, off);
+            if (tid >= off) x += y;
+        }
+        if (tid <= nr) s_pad[tid] = x - ((len + 3) & ~3);
+        const unsigned mx = wave_max((unsigned)len);
+        if (tid == 0) block_max[blockIdx.x] = (int32_t)mx;
+        if (len > kLongRow) long_rows[atomicAdd(&S->n_long, 1)] = (int32_t)(r0 + tid);
+    }
+    unsigned flags = 0, near = 0;
+    for (int a = 0; a < nr;) {
+        const int32_t t0 = s_start[a];
+        if (s_start[a + 1] - t0 > kLongRow) {   // k_long_row_sort
+            ++a;
+            continue;
+        }
+        int z = a + 1;   // rows [a, z) together
+        while (z < nr && s_start[z + 1] - t0 <= kRowTile && s_start[z + 1] - s_start[z] <= kLongRow) ++z;
+        const int32_t m = s_start[z] - t0;
+        // a thread's entries are tid, tid + 256, ..
+        constexpr int kItems = kRowTile / 256;
+        int2 p[kItems];
+        int row[kItems];
+#pragma unroll
+        for (int u = 0; u < kItems; ++u) {
+            const int32_t t = u * 256 + tid;
+            if (t < m) p[u] = in[t0 + t];
+        }
+        __syncthreads();   // s_pad
+        const int32_t pad0 = s_pad[a];
+        for (int32_t t = tid; t < s_pad[z] - pad0; t += 256) s_col[t] = INT32_MAX;
+        for (int32_t t = tid; t < m; t += 256) s_out[t] = make_int2(-1, 0);
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kItems; ++u) {
+            if (u * 256 >= m) break;
+            const int32_t t = u * 256 + tid;
+            // the last row that starts at or before t (it is not empty)
+            int r = -1;
+#pragma unroll
+            for (int k = 0; k < kSortRows; ++k) r += ustart[k] - t0 <= t;
+            row[u] = r;
+            if (t < m) s_col[s_pad[r] - pad0 + t - (s_start[r] - t0)] = p[u].x;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kItems; ++u) {
+            const int32_t t = u * 256 + tid;
+            if (t < m) {
+                const int32_t rs = s_start[row[u]] - t0;
+                const int quads = (s_start[row[u] + 1] - s_start[row[u]] + 3) >> 2;
+                const int4 *const rc = reinterpret_cast<const int4 *>(&s_col[s_pad[row[u]] - pad0]);
+                int32_t rank = 0;
+#pragma unroll 4
+                for (int q = 0; q < quads; ++q) {
+                    const int4 c = rc[q];
+                    rank += (c.x < p[u].x) + (c.y < p[u].x) + (c.z < p[u].x) + (c.w < p[u].x);
+                }
+                s_out[rs + rank] = p[u];
+                s_row[t] = (uint8_t)row[u];   // the same entries of the row in any order
             }
         }
-        const int64_t dst = rs + rank;
-        const float v = tval[p];
-        col[dst] = c;
-        sval[dst] = v;
-        eps[dst] = w_max / v;
+        __syncthreads();
+        for (int32_t t = tid; t < m; t += 256) {
+            const int2 q = s_out[t];
+            if (q.x < 0) flags |= kDuplicate;
+            const int32_t o = dst + t0 + t;
+            const float v = __int_as_float(q.y);
+            out.col[o] = q.x;
+            out.eps[o] = w_max / v;
+            if (out.col16) {
+                const int64_t d = (int64_t)q.x - (r0 + s_row[t]);
+                out.pair[o] = q;
+                out.col16[o] = (int16_t)d;
+                if (d < INT16_MIN || d > INT16_MAX) flags |= kWide;
+                near += d >= -kHalo && d <= kHalo;
+            }
+        }
+        __syncthreads();
+        a = z;
     }
     flags = wave_or(flags);
-    if ((threadIdx.x & 63) == 0 && flags) atomicOr(&S->flags, flags);
+    if ((tid & 63) == 0 && flags) atomicOr(&s_flags, flags);
+    if (near) atomicAdd(&s_near, near);
+    __syncthreads();
+    if (tid == 0) {
+        // (most blocks of a shuffled graph raise kWide: look before adding)
+        if (s_flags && (s_flags & ~*(volatile unsigned *)&S->flags)) atomicOr(&S->flags, s_flags);
+        block_near[blockIdx.x] = (int32_t)s_near;
+    }
 }
 
-// list[] = the rows longer than kLongRow, count[0] = how many (zeroed before).
-__global__ __launch_bounds__(256) void k_long_rows(const int64_t *__restrict__ row_ptr, int64_t n,
-                                                   int32_t *__restrict__ list, int32_t *count)
+// One workgroup per long row (the grid takes the list in strides): a
+// least-significant-digit radix sort of the row's (column, slot) pairs by
+// column, 4-bit digits, each pass stable (the digit's global offset from a
+// counting sweep, then chunks of 1024 entries in order, each entry placed
+// after the earlier entries of its digit: rank in its wavefront by ballot,
+// wavefront offsets in LDS).  The pairs move between two buffers inside the
+// row's own segment: (col, eps), eps holding the slot as an int, and the two
+// halves of the row's `pair` segment.  An even number of passes leaves the
+// result in (col, eps); then eps, pair and the offsets are written in sorted
+// order and equal neighbours flag a duplicate.
+__global__ __launch_bounds__(kSortThreads) void k_long_row_sort(const int2 *__restrict__ src,
+                                                                const int32_t *__restrict__ first,
+                                                                const int32_t *__restrict__ kfirst,
+                                                                const int32_t *__restrict__ lstart, int64_t n,
+                                                                int32_t lg, int32_t passes,
+                                                                const int32_t *__restrict__ long_rows, PrepScalars *S,
+                                                                SortedRows out)
 {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < n && row_ptr[r + 1] - row_ptr[r] > kLongRow) list[atomicAdd(count, 1)] = (int32_t)r;
-}
-
-// One workgroup per long row: a least-significant-digit radix sort of the
-// row's (column, slot) pairs by column, 4-bit digits, each pass stable (the
-// digit's global offset from a counting sweep, then chunks of 1024 entries in
-// order, each entry placed after the earlier entries of its digit: rank in
-// its wavefront by ballot, wavefront offsets in LDS).  The pairs move between
-// two buffers inside the row's own segment: (tcol, sval) and (col, eps) --
-// sval and eps hold the slot as an int until the last step writes them.  An
-// even number of passes leaves the result in (tcol, sval); then col, sval and
-// eps are written in sorted order and equal neighbours flag a duplicate.
-__global__ __launch_bounds__(kSortThreads) void k_long_row_sort(int32_t *__restrict__ tcol,
-                                                                const float *__restrict__ tval,
-                                                                const int64_t *__restrict__ row_ptr,
-                                                                const int32_t *__restrict__ list,
-                                                                const int32_t *__restrict__ count, int32_t passes,
-                                                                PrepScalars *S, int32_t *__restrict__ col,
-                                                                float *__restrict__ sval, float *__restrict__ eps)
-{
-    if ((int32_t)blockIdx.x >= *count) return;
     __shared__ int32_t s_hist[16];
     __shared__ int32_t s_wcnt[kSortWaves][16];
     __shared__ int32_t s_woff[kSortWaves][16];
-    const int32_t r = list[blockIdx.x];
-    const int64_t rs = row_ptr[r], L = row_ptr[r + 1] - rs;
     const int tid = threadIdx.x, wv = tid / 64, lane = tid % 64;
-    int32_t *const key[2] = {tcol + rs, col + rs};
-    int32_t *const idx[2] = {reinterpret_cast<int32_t *>(sval) + rs, reinterpret_cast<int32_t *>(eps) + rs};
-    for (int64_t t = tid; t < L; t += kSortThreads) idx[0][t] = (int32_t)t;
-    __syncthreads();
-    for (int32_t pass = 0; pass < passes; ++pass) {
-        const int src = pass & 1, dst = src ^ 1;
-        const int shift = 4 * pass;
-        if (tid < 16) s_hist[tid] = 0;
-        __syncthreads();
-        for (int64_t t = tid; t < L; t += kSortThreads) atomicAdd(&s_hist[((uint32_t)key[src][t] >> shift) & 15u], 1);
-        __syncthreads();
-        if (tid == 0) {
-            int32_t run = 0;
-            for (int d = 0; d < 16; ++d) {
-                const int32_t c = s_hist[d];
-                s_hist[d] = run;   // first slot of digit d
-                run += c;
-            }
-        }
-        __syncthreads();
-        for (int64_t c0 = 0; c0 < L; c0 += kSortThreads) {
-            const int64_t t = c0 + tid;
-            const bool valid = t < L;
-            const int32_t k = valid ? key[src][t] : 0;
-            const int32_t ix = valid ? idx[src][t] : 0;
-            const int d = valid ? (int)(((uint32_t)k >> shift) & 15u) : 16;
-            int rank = 0;
-            for (int v = 0; v < 16; ++v) {
-                const unsigned long long m = __ballot(d == v);
-                if (d == v) rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                if (lane == 0) s_wcnt[wv][v] = __popcll(m);
-            }
-            __syncthreads();
-            if (tid < 16) {
-                int32_t run = s_hist[tid];
-                for (int w = 0; w < kSortWaves; ++w) {
-                    s_woff[w][tid] = run;
-                    run += s_wcnt[w][tid];
-                }
-                s_hist[tid] = run;
-            }
-            __syncthreads();
-            if (valid) {
-                const int32_t pos = s_woff[wv][d] + rank;
-                key[dst][pos] = k;
-                idx[dst][pos] = ix;
-            }
-            __syncthreads();
-        }
-    }
     const float w_max = __uint_as_float(S->wmax_bits);
-    unsigned flags = 0;
-    for (int64_t t = tid; t < L; t += kSortThreads) {
-        const int32_t c = key[0][t];
-        const int32_t ix = idx[0][t];
-        if (t > 0 && key[0][t - 1] == c) flags |= kDuplicate;
-        const float v = tval[rs + ix];
-        col[rs + t] = c;
-        sval[rs + t] = v;
-        eps[rs + t] = w_max / v;
+    const int32_t n_long = S->n_long;
+    for (int32_t item = blockIdx.x; item < n_long; item += gridDim.x) {
+        const int64_t r = long_rows[item];
+        const int64_t b = r >> lg;
+        const int32_t ls = lstart[r];
+        const int32_t le = r + 1 < n && ((r + 1) >> lg) == b ? lstart[r + 1] : kfirst[b + 1] - kfirst[b];
+        const int64_t L = le - ls;
+        const int2 *const in = src + first[b * kSubs] + ls;
+        const int64_t rs = (int64_t)kfirst[b] + ls;
+        int32_t *const spare = reinterpret_cast<int32_t *>(out.pair + rs);
+        int32_t *const key[2] = {out.col + rs, spare};
+        int32_t *const idx[2] = {reinterpret_cast<int32_t *>(out.eps) + rs, spare + L};
+        for (int64_t t = tid; t < L; t += kSortThreads) {
+            key[0][t] = in[t].x;
+            idx[0][t] = (int32_t)t;
+        }
+        __syncthreads();
+        for (int32_t pass = 0; pass < passes; ++pass) {
+            const int from = pass & 1, to = from ^ 1;
+            const int shift = 4 * pass;
+            if (tid < 16) s_hist[tid] = 0;
+            __syncthreads();
+            for (int64_t t = tid; t < L; t += kSortThreads) atomicAdd(&s_hist[((uint32_t)key[from][t] >> shift) & 15u], 1);
+            __syncthreads();
+            if (tid == 0) {
+                int32_t run = 0;
+                for (int d = 0; d < 16; ++d) {
+                    const int32_t c = s_hist[d];
+                    s_hist[d] = run;   // first slot of digit d
+                    run += c;
+                }
+            }
+            __syncthreads();
+            for (int64_t c0 = 0; c0 < L; c0 += kSortThreads) {
+                const int64_t t = c0 + tid;
+                const bool valid = t < L;
+                const int32_t k = valid ? key[from][t] : 0;
+                const int32_t ix = valid ? idx[from][t] : 0;
+                const int d = valid ? (int)(((uint32_t)k >> shift) & 15u) : 16;
+                int rank = 0;
+                for (int v = 0; v < 16; ++v) {
+                    const unsigned long long m = __ballot(d == v);
+                    if (d == v) rank = (int)lanes_below(m);
+                    if (lane == 0) s_wcnt[wv][v] = __popcll(m);
+                }
+                __syncthreads();
+                if (tid < 16) {
+                    int32_t run = s_hist[tid];
+                    for (int w = 0; w < kSortWaves; ++w) {
+                        s_woff[w][tid] = run;
+                        run += s_wcnt[w][tid];
+                    }
+                    s_hist[tid] = run;
+                }
+                __syncthreads();
+                if (valid) {
+                    const int32_t pos = s_woff[wv][d] + rank;
+                    key[to][pos] = k;
+                    idx[to][pos] = ix;
+                }
+                __syncthreads();
+            }
+        }
+        unsigned flags = 0, near = 0;
+        for (int64_t t = tid; t < L; t += kSortThreads) {
+            const int32_t c = key[0][t];
+            const float v = __int_as_float(in[idx[0][t]].y);
+            if (t > 0 && key[0][t - 1] == c) flags |= kDuplicate;
+            out.eps[rs + t] = w_max / v;
+            if (out.col16) {
+                const int64_t d = (int64_t)c - r;
+                out.pair[rs + t] = make_int2(c, __float_as_int(v));
+                out.col16[rs + t] = (int16_t)d;
+                if (d < INT16_MIN || d > INT16_MAX) flags |= kWide;
+                near += d >= -kHalo && d <= kHalo;
+            }
+        }
+        flags = wave_or(flags);
+        if (lane == 0 && flags) atomicOr(&S->flags, flags);
+        if (near) atomicAdd(&S->near, (unsigned long long)near);
+        __syncthreads();
     }
-    flags = wave_or(flags);
-    if (lane == 0 && flags) atomicOr(&S->flags, flags);
 }
 
-__global__ __launch_bounds__(256) void k_symmetry(const int32_t *__restrict__ trow, const int32_t *__restrict__ col,
-                                                  const float *__restrict__ sval, const int64_t *__restrict__ row_ptr,
-                                                  int64_t n, PrepScalars *S)
+// The kept graph is symmetric if every (i, j, v) with i < j has its (j, i, v) and
+// there are as many entries above the diagonal as below it (no entry is listed
+// twice): half the lookups.  A wave takes 64 consecutive entries at a time;
+// those above the diagonal are looked up by 16 lanes together, four per load,
+// in the first entries of row j, which is sorted, so that its entries below
+// the diagonal come first: 16 entries a round, three rounds, and what is not
+// decided then by a binary search.  The random lines of the rows bound it on a
+// shuffled graph: 3235 us on 26.7M edges with one binary search per lane and
+// entry, now 560 (local order 690 -> 200).
+__global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair, const int32_t *__restrict__ rp32,
+                                                  int64_t n, PrepScalars *S, int32_t *__restrict__ block_diff)
 {
     // After a duplicate the in-row sort leaves some slots unwritten; the
     // graph is rejected anyway, so skip the check rather than read them.
     if (S->flags & (kDuplicate | kBadIndex | kBadValue)) return;
-    const int64_t kept = row_ptr[n];
-    unsigned flags = 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < kept; p += stride) {
-        const int32_t i = trow[p];   // row slots keep their row through the in-row sort
-        const int32_t j = col[p];
-        if ((uint32_t)j >= (uint32_t)n) {
-            flags |= kAsymmetric;
-            continue;
+    constexpr int kG = 16;        // lanes per lookup
+    constexpr int kRounds = 3;
+    constexpr int kAhead = 8;     // loads in flight
+    __shared__ int32_t s_start[kSortRows + 1];
+    __shared__ int4 s_list[4][64];   // (first entry, end of row, i, value bits)
+    __shared__ int s_diff;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int64_t r0 = (int64_t)blockIdx.x * kSortRows;
+    const int nr = (int)(n - r0 < kSortRows ? n - r0 : kSortRows);
+    if (tid <= nr) s_start[tid] = rp32[r0 + tid];
+    if (tid == 0) s_diff = 0;
+    __syncthreads();
+    const int32_t e1 = s_start[nr];
+    bool bad = false;
+    int diff = 0;   // entries above the diagonal minus entries below
+    const int group = lane / kG, part = lane % kG;
+    for (int32_t c0 = s_start[0] + wv * 64; c0 < e1; c0 += 256) {
+        const int32_t e = c0 + lane;
+        const bool in = e < e1;
+        int2 p = make_int2(0, 0);
+        int32_t i = 0;
+        if (in) {
+            p = pair[e];
+            int lo = 0, hi = nr - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (s_start[mid] <= e) lo = mid; else hi = mid - 1;
+            }
+            i = (int32_t)(r0 + lo);
         }
-        int64_t lo = row_ptr[j], hi = row_ptr[j + 1];
-        const int64_t end = hi;
-        while (lo < hi) {
-            int64_t mid = (lo + hi) >> 1;
-            if (col[mid] < i) lo = mid + 1; else hi = mid;
+        bool open = in && p.x > i;   // still to be found
+        diff += in ? (open ? 1 : -1) : 0;
+        int32_t at = 0, re = 0;
+        if (open) {
+            at = rp32[p.x];
+            re = rp32[p.x + 1];
         }
-        if (lo >= end || col[lo] != i || __float_as_uint(sval[lo]) != __float_as_uint(sval[p])) flags |= kAsymmetric;
+        for (int round = 0; round < kRounds; ++round) {
+            const unsigned long long m = __ballot(open);
+            if (m == 0) break;
+            const int cnt = __popcll(m);
+            const int mine = (int)lanes_below(m);   // place in the list
+            if (open) s_list[wv][mine] = make_int4(at, re, i, p.y);
+            wave_sync();
+            unsigned long long hit = 0;
+            for (int s0 = 0; s0 < cnt; s0 += 4 * kAhead) {
+                int4 w[kAhead];
+                int2 q[kAhead];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    if (s0 + 4 * u >= cnt) break;
+                    const int s = s0 + 4 * u + group;
+                    w[u] = s_list[wv][s < cnt ? s : 0];
+                    q[u] = make_int2(-1, 0);
+                    if (s < cnt && w[u].x + part < w[u].y) q[u] = pair[w[u].x + part];
+                }
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    if (s0 + 4 * u >= cnt) break;
+                    const unsigned long long h = __ballot(q[u].x == w[u].z && q[u].y == w[u].w);   // column -1 is none
+                    if ((mine >> 2) == (s0 >> 2) + u) hit = h;
+                }
+            }
+            if (open) {
+                at += kG;
+                if ((hit >> (kG * (mine & 3))) & ((1ull << kG) - 1ull)) open = false;
+                else if (at >= re) {
+                    open = false;
+                    bad = true;
+                }
+            }
+            wave_sync();   // the list is written again
+        }
+        if (open) {
+            int32_t lo = at, hi = re;
+            while (lo < hi) {
+                const int32_t mid = (lo + hi) >> 1;
+                if (pair[mid].x < i) lo = mid + 1; else hi = mid;
+            }
+            if (lo >= re) bad = true;
+            else {
+                const int2 q = pair[lo];
+                bad |= q.x != i || q.y != p.y;
+            }
+        }
     }
-    flags = wave_or(flags);
-    if ((threadIdx.x & 63) == 0 && flags) atomicOr(&S->flags, flags);
+    if (diff) atomicAdd(&s_diff, diff);
+    if (__ballot(bad) != 0 && lane == 0) atomicOr(&S->flags, (unsigned)kAsymmetric);
+    __syncthreads();
+    if (tid == 0) block_diff[blockIdx.x] = s_diff;
+}
+
+// The blocks' largest rows and partial sums into the scalars (diff null:
+// bipartite).  Thousands of workgroups adding to one line would wait for each
+// other: 62,500 of them took 200 us of the sort and the symmetry check each.
+__global__ __launch_bounds__(256) void k_prep_sums(const int32_t *__restrict__ mx, const int32_t *__restrict__ near,
+                                                   const int32_t *__restrict__ diff, int64_t count, PrepScalars *S)
+{
+    if (S->flags & (kDuplicate | kBadIndex | kBadValue)) diff = nullptr;   // the check did not run
+    int64_t a = 0, d = 0;
+    unsigned m = 0;
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < count; t += (int64_t)gridDim.x * 256) {
+        m = max(m, (unsigned)mx[t]);
+        a += near[t];
+        if (diff) d += diff[t];
+    }
+    m = wave_max(m);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        a += __shfl_xor(a, off);
+        d += __shfl_xor(d, off);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        if (m) atomicMax(&S->max_degree, (int)m);
+        if (a) atomicAdd(&S->near, (unsigned long long)a);
+        if (d) atomicAdd(reinterpret_cast<unsigned long long *>(&S->up_minus_low), (unsigned long long)d);
+    }
 }
 
 static int64_t grid_for(int64_t items)
@@ -409,44 +730,51 @@ static int64_t grid_for(int64_t items)
     return b < 1 ? 1 : b;
 }
 
-int64_t scan_blocks(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
+int64_t long_row_slots(int64_t nnz) { return nnz / (kLongRow + 1); }
 
 hipError_t launch_prep(const PrepBuffers &B, hipStream_t s)
 {
     const IngestShape sh{(uint32_t)B.n, (uint32_t)B.n_cols, B.bipartite ? 1 : 0};
-    const int64_t g = grid_for(B.nnz);
-    // a grid-stride pass with a block-wide reduction: 2048 blocks fill the chip
-    const int64_t g_check = g < 2048 ? g : 2048;
-    hipLaunchKernelGGL(k_check_max, dim3((unsigned)g_check), dim3(256), 0, s, B.rows, B.cols, B.vals, B.nnz, sh,
-                       B.scalars);
-    hipLaunchKernelGGL(k_count, dim3((unsigned)g), dim3(256), 0, s, B.rows, B.cols, B.vals, B.nnz, sh, B.n_epochs,
-                       B.scalars, B.deg);
-    const int64_t nb = B.nblocks_scan;
-    hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, s, B.deg, B.n, B.bsum, B.scalars);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanThreads), 0, s, B.bsum, nb);
-    hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(kScanThreads), 0, s, B.deg, B.n, B.bsum, B.row_ptr, nb);
-    hipLaunchKernelGGL(k_scatter, dim3((unsigned)g), dim3(256), 0, s, B.rows, B.cols, B.vals, B.nnz, sh, B.n_epochs,
-                       B.scalars, B.row_ptr, B.cursor, B.trow, B.tcol, B.tval);
-    hipLaunchKernelGGL(k_row_sort, dim3((unsigned)g), dim3(256), 0, s, B.trow, B.tcol, B.tval, B.row_ptr, B.n,
-                       B.scalars, B.col, B.sval, B.eps);
-    // rows longer than kLongRow: their list in deg (free after the scan), its
-    // length in cursor[0] (free after the scatter)
-    const int64_t max_long = B.nnz / (kLongRow + 1);
+    const int32_t lg = bucket_lg(B.n);
+    const int32_t nb = (int32_t)bucket_count(B.n);
+    const size_t lds = sizeof(int32_t) * (size_t)nb;
+    const int64_t tiles = (B.nnz + kTile - 1) / kTile;
+    // the bucket counters and the scalars start at zero (the cursors at the scan)
+    hipError_t e = launch_zero_u64(reinterpret_cast<unsigned long long *>(B.bucket_n), bucket_counters(B.n) / 2, s);
+    if (e != hipSuccess) return e;
+    e = launch_zero_u64(reinterpret_cast<unsigned long long *>(B.scalars), sizeof(PrepScalars) / 8, s);
+    if (e != hipSuccess) return e;
+    if (tiles > 0) {
+        // every block adds its counters to all buckets' once: two rounds of blocks
+        const int64_t g = tiles < 1024 ? (tiles + kSubs - 1) / kSubs * kSubs : 1024;
+        hipLaunchKernelGGL(k_check, dim3((unsigned)g), dim3(kTileThreads), lds, s, B.rows, B.cols, B.vals, B.nnz, sh, lg,
+                           nb, B.bucket_n, B.scalars);
+    }
+    hipLaunchKernelGGL((k_bucket_scan<true>), dim3(1), dim3(kTileThreads), 0, s, B.bucket_n, kSubs * nb, B.first,
+                       B.cursor);
+    if (tiles > 0)
+        hipLaunchKernelGGL(k_bucket_scatter, dim3((unsigned)tiles), dim3(kTileThreads), lds, s, B.rows, B.cols, B.vals,
+                           B.nnz, sh, lg, nb, B.cursor, B.pair, B.lrow);
+    hipLaunchKernelGGL(k_bucket_rows, dim3((unsigned)nb), dim3(kTileThreads), 0, s, B.pair, B.lrow, B.first, B.n, lg,
+                       B.n_epochs, B.scalars, B.pair_rows, B.lstart, B.kept_n);
+    hipLaunchKernelGGL((k_bucket_scan<false>), dim3(1), dim3(kTileThreads), 0, s, B.kept_n, nb, B.kfirst, nullptr);
+    const SortedRows out{B.col, B.eps, B.pair, B.col16};
+    const dim3 rb((unsigned)row_blocks(B.n));
+    hipLaunchKernelGGL(k_row_sort, rb, dim3(256), 0, s, B.pair_rows, B.first, B.kfirst, B.lstart, B.n, lg,
+                       B.scalars, B.row_ptr, B.rp32, B.long_rows, B.block_near, B.block_max, out);
+    const int64_t max_long = long_row_slots(B.nnz);
     if (max_long > 0) {
         int32_t passes = 0;   // 4-bit digits of the largest column, rounded up to an even count
         for (int64_t top = B.n_cols - 1; top > 0; top >>= 4) ++passes;
         passes += passes & 1;
-        hipError_t e = hipMemsetAsync(B.cursor, 0, sizeof(int32_t), s);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_long_rows, dim3((unsigned)((B.n + 255) / 256)), dim3(256), 0, s, B.row_ptr, B.n, B.deg,
-                           B.cursor);
-        const int64_t rows = max_long < B.n ? max_long : B.n;
-        hipLaunchKernelGGL(k_long_row_sort, dim3((unsigned)rows), dim3(kSortThreads), 0, s, B.tcol, B.tval, B.row_ptr,
-                           B.deg, B.cursor, passes, B.scalars, B.col, B.sval, B.eps);
+        hipLaunchKernelGGL(k_long_row_sort, dim3((unsigned)(max_long < 512 ? max_long : 512)), dim3(kSortThreads), 0, s,
+                           B.pair_rows, B.first, B.kfirst, B.lstart, B.n, lg, passes, B.long_rows, B.scalars, out);
     }
     if (!B.bipartite)
-        hipLaunchKernelGGL(k_symmetry, dim3((unsigned)g), dim3(256), 0, s, B.trow, B.col, B.sval, B.row_ptr, B.n,
-                           B.scalars);
+        hipLaunchKernelGGL(k_symmetry, rb, dim3(256), 0, s, B.pair, B.rp32, B.n, B.scalars, B.block_diff);
+    const int64_t g = (row_blocks(B.n) + 1023) / 1024;
+    hipLaunchKernelGGL(k_prep_sums, dim3((unsigned)(g < 64 ? g : 64)), dim3(256), 0, s, B.block_max, B.block_near,
+                       B.bipartite ? nullptr : B.block_diff, row_blocks(B.n), B.scalars);
     return hipGetLastError();
 }
 
@@ -508,54 +836,6 @@ hipError_t launch_partition(const int64_t *row_ptr, int64_t r0, int64_t r1, int3
     const int64_t threads = r1 - r0 > n_waves ? r1 - r0 : n_waves;
     hipLaunchKernelGGL(k_head_local, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, row_ptr, r0, r1, part,
                        n_waves, desc, head);
-    return hipGetLastError();
-}
-
-// delta[e] = col[e] - (row of e) in 16 bits; *wide gets 1 when some delta
-// does not fit and *near the number of deltas of at most kHalo (the wave
-// kernels read the 32-bit columns, and stage no halo, unless all fit and most
-// are near).  One block per 256 rows reads and writes the rows' edges with
-// consecutive threads on consecutive edges and finds each edge's row by a
-// binary search over the rows' starts staged in LDS (one thread walking a
-// whole row waits on one load per edge: 454 us at 1M vertices, k = 15).
-__global__ __launch_bounds__(256) void k_col_delta(const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                                                   int64_t n, int16_t *__restrict__ delta, unsigned *__restrict__ wide,
-                                                   unsigned long long *__restrict__ near)
-{
-    __shared__ int64_t s_rp[257];
-    __shared__ unsigned s_near;
-    if (threadIdx.x == 0) s_near = 0;
-    const int64_t r0 = (int64_t)blockIdx.x * 256;
-    const int nr = (int)(n - r0 < 256 ? n - r0 : 256);
-    for (int t = threadIdx.x; t <= nr; t += 256) s_rp[t] = row_ptr[r0 + t];
-    __syncthreads();
-    const int64_t e1 = s_rp[nr];
-    bool w = false;
-    unsigned close = 0;
-    for (int64_t e = s_rp[0] + threadIdx.x; e < e1; e += 256) {
-        // the row of e: the last of the block's rows that starts at or before
-        // e (an empty row shares its start with the next row)
-        int lo = 0, hi = nr - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_rp[mid] <= e) lo = mid; else hi = mid - 1;
-        }
-        const int64_t d = (int64_t)col[e] - (r0 + lo);
-        w |= d < INT16_MIN || d > INT16_MAX;
-        close += d >= -kHalo && d <= kHalo;
-        delta[e] = (int16_t)d;
-    }
-    if (close) atomicAdd(&s_near, close);
-    if (__ballot(w) != 0 && (threadIdx.x & 63) == 0) atomicOr(wide, 1u);
-    __syncthreads();
-    if (threadIdx.x == 0 && s_near) atomicAdd(near, (unsigned long long)s_near);
-}
-
-hipError_t launch_col_delta(const int64_t *row_ptr, const int32_t *col, int64_t n, int16_t *delta, unsigned *wide,
-                            unsigned long long *near, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_col_delta, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, row_ptr, col, n, delta, wide,
-                       near);
     return hipGetLastError();
 }
 

@@ -1,0 +1,149 @@
+"""The device ingest against a sort on the host, bit for bit, at the sizes where
+it changes: buckets of 2^8 to 2^14 rows (16,384-row buckets are counted in two
+parts), rows longer than a workgroup sorts together (512 entries), many entries
+in one bucket, empty rows and buckets, pruned entries, and a bipartite graph.
+And what it refuses: an entry without its reverse, or with another value there,
+wherever it stands; duplicates in short and long rows."""
+
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2008_00325_amd import synth
+from paper_2008_00325_amd import umap_layout as U
+
+pytestmark = pytest.mark.gpu
+
+A_DEF, B_DEF = 1.577, 0.895
+
+
+def case(msg):
+    print(f"[gpu case] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module", autouse=True)
+def torch_device_first():
+    import torch
+
+    torch.cuda.init()
+    torch.cuda.set_device(0)
+
+
+def _expected(n, r, c, v, N, bipartite=False):
+    keep = v > 0 if bipartite else (v > 0) & (r != c)
+    w_max = v[keep].max()
+    keep &= v >= w_max / np.float32(N)
+    r, c, v = r[keep], c[keep], v[keep]
+    o = np.lexsort((c, r))
+    row_ptr = np.concatenate([[0], np.cumsum(np.bincount(r, minlength=n))]).astype(np.int64)
+    return row_ptr, c[o], w_max / v[o]
+
+
+def _check(h, n, r, c, v, N, bipartite=False):
+    want = _expected(n, r, c, v, N, bipartite)
+    got = U.umap_layout_get_graph(h)
+    for a, b in zip(got, want):
+        assert np.array_equal(a, b)
+    st = U.umap_layout_stats(h)
+    assert st["max_degree"] == np.diff(want[0]).max() and st["nnz_kept"] == want[1].size
+
+
+def _hubs(n, hubs, degree, seed):
+    """`hubs` vertices joined to `degree` others each, and a sparse rest."""
+    rng = np.random.default_rng(seed)
+    lo, hi = [], []
+    for q in range(hubs):
+        h = int(rng.integers(0, n))
+        t = rng.choice(n, size=degree, replace=False)
+        t = t[t != h]
+        lo.append(np.minimum(h, t))
+        hi.append(np.maximum(h, t))
+    e = rng.integers(0, n, size=(2, 2 * n))
+    e = e[:, e[0] != e[1]]
+    lo.append(e.min(0))
+    hi.append(e.max(0))
+    key = np.unique(np.concatenate(lo).astype(np.int64) * n + np.concatenate(hi))
+    lo, hi = (key // n).astype(np.int32), (key % n).astype(np.int32)
+    v = (rng.random(lo.size) * 0.98 + 0.004).astype(np.float32)   # some below w_max / N
+    p = rng.permutation(2 * lo.size)
+    return np.r_[lo, hi][p], np.r_[hi, lo][p], np.r_[v, v][p]
+
+
+# (vertices, mean degree)
+@pytest.mark.parametrize("n,deg", [(1, 0), (2, 1), (31, 30), (32, 20), (33, 5), (256, 12), (257, 12), (8191, 6),
+                                   (262_143, 5), (262_145, 5), (1_048_577, 3), (9_000_001, 1)])
+def test_random_graphs(n, deg):
+    r, c, v = synth.random_symmetric_coo(n, deg, seed=n % 997) if deg else (np.zeros(0, np.int32),) * 2 + (
+        np.zeros(0, np.float32),)
+    # entries that are dropped: zeros, negative values, self loops
+    extra = np.arange(min(n, 50), dtype=np.int32)
+    r, c = np.r_[r, extra, extra], np.r_[c, extra, (extra + 1) % n]
+    v = np.r_[v, np.full(extra.size, 5.0, np.float32), np.where(extra % 2, 0.0, -1.0).astype(np.float32)]
+    case(f"random graph n {n} degree {deg}")
+    with U.umap_layout_create(n, 2, r, c, v, A_DEF, B_DEF, 50, 5) as h:
+        if deg:
+            _check(h, n, r, c, v, 50)
+        else:
+            assert U.umap_layout_stats(h)["nnz_kept"] == 0
+
+
+@pytest.mark.parametrize("n,hubs,degree", [(700, 3, 511), (700, 3, 512), (700, 40, 513), (5_000, 2, 4_999),
+                                           (300_000, 12, 20_000)])
+def test_hub_graphs(n, hubs, degree):
+    r, c, v = _hubs(n, hubs, degree, seed=degree)
+    case(f"n {n}, {hubs} hubs of degree {degree}")
+    with U.umap_layout_create(n, 2, r, c, v, A_DEF, B_DEF, 200, 5) as h:
+        _check(h, n, r, c, v, 200)
+
+
+@pytest.mark.parametrize("n_new,n_table,k", [(3, 40_000, 9_000), (400, 90_000, 700), (300_001, 130, 3)])
+def test_bipartite(n_new, n_table, k):
+    rng = np.random.default_rng(k)
+    if k > n_table // 16:
+        cols = np.stack([rng.permutation(n_table)[:k] for _ in range(n_new)])
+    else:
+        start, step = rng.integers(0, n_table, (n_new, 1)), rng.integers(1, n_table // k, (n_new, 1))
+        cols = (start + step * np.arange(k)) % n_table
+    rows = np.repeat(np.arange(n_new, dtype=np.int32), k)
+    p = rng.permutation(rows.size)
+    r, c = rows[p], cols.ravel().astype(np.int32)[p]
+    v = rng.uniform(0.001, 1.0, rows.size).astype(np.float32)
+    case(f"bipartite {n_new} x {n_table}, {k} entries per row")
+    with U.umap_transform_create(n_new, synth.embedding_state(n_table, 2, 1), r, c, v, A_DEF, B_DEF, 100, 5) as h:
+        _check(h, n_new, r, c, v, 100, bipartite=True)
+
+
+def test_asymmetric_and_duplicate_entries():
+    n = 3_000
+    r, c, v = _hubs(n, 4, 900, seed=9)
+    v = np.maximum(v, np.float32(0.1))
+    with U.umap_layout_create(n, 2, r, c, v, A_DEF, B_DEF, 200, 5):
+        pass
+    deg = np.bincount(r, minlength=n)
+    long_rows, short_rows = np.flatnonzero(deg > 512), np.flatnonzero(deg < 20)
+    picks = [np.flatnonzero(np.isin(r, long_rows) & np.isin(c, short_rows) & (r < c))[0],
+             np.flatnonzero(np.isin(r, long_rows) & np.isin(c, short_rows) & (r > c))[-1],
+             np.flatnonzero(np.isin(c, long_rows) & np.isin(r, short_rows) & (r < c))[3],
+             np.flatnonzero(np.isin(c, long_rows) & np.isin(r, short_rows) & (r > c))[-4],
+             np.flatnonzero(np.isin(r, short_rows) & np.isin(c, short_rows) & (r < c))[5],
+             np.flatnonzero(np.isin(r, short_rows) & np.isin(c, short_rows) & (r > c))[6]]
+    for e in picks:
+        case(f"entry {e} ({r[e]}, {c[e]}): missing, another value, listed twice")
+        gone = np.delete(np.arange(r.size), e)
+        other = v.copy()
+        other[e] = np.nextafter(v[e], np.float32(1))
+        for rr, cc, vv, code in ((r[gone], c[gone], v[gone], U.UMAP_E_ASYMMETRIC), (r, c, other, U.UMAP_E_ASYMMETRIC),
+                                 (np.r_[r, r[e]], np.r_[c, c[e]], np.r_[v, v[e]], U.UMAP_E_INVAL)):
+            with pytest.raises(U.UmapLayoutError) as ei:
+                U.umap_layout_create(n, 2, rr, cc, vv, A_DEF, B_DEF, 200, 5)
+            assert ei.value.code == code
+    # as many entries above the diagonal as below, none with its reverse
+    a = picks[4]
+    far = np.flatnonzero(np.isin(r, short_rows) & np.isin(c, short_rows) & (r < c) & (r != r[a]))[9]
+    back = np.flatnonzero((r == c[far]) & (c == r[far]))[0]
+    gone = np.delete(np.arange(r.size), [a, back])
+    with pytest.raises(U.UmapLayoutError) as ei:
+        U.umap_layout_create(n, 2, r[gone], c[gone], v[gone], A_DEF, B_DEF, 200, 5)
+    assert ei.value.code == U.UMAP_E_ASYMMETRIC
