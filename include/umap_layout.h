@@ -196,8 +196,11 @@ int umap_layout_epoch_ms(const umap_layout *h, float *out_ms, int32_t capacity);
  * while the handle uses it. */
 int umap_layout_set_stream(umap_layout *h, void *stream);
 
-/* umap_layout_destroy -- free all device memory of the handle (waits for its
- * stream).  NULL is a no-op. */
+/* umap_layout_destroy -- give back all device memory of the handle (waits for
+ * its stream).  NULL is a no-op.  The library keeps freed blocks of handles and
+ * of its blocking calls' scratch for later ones: at most 4 GiB per process, the
+ * ones not needed during the last 64 allocations freed, all of them when an
+ * allocation fails. */
 void umap_layout_destroy(umap_layout *h);
 
 /* umap_layout_last_error -- message of the last failing call on this thread
@@ -323,8 +326,8 @@ int umap_layout_set_rows(umap_layout *h, int64_t row_first, int64_t row_last);
  * the dot products on the matrix cores): a pair closer to a tie than fp32
  * resolves can rank differently from an exact evaluation, each such pair
  * moving T by about 1 / (n^2 k).  Errors: UMAP_E_INVAL (arguments, a non-finite
- * embedding), UMAP_E_NOMEM, UMAP_E_DEVICE.  Scratch of about 8 n k bytes is
- * allocated on `stream` (NULL: null stream) and freed.  Blocking.
+ * embedding), UMAP_E_NOMEM, UMAP_E_DEVICE.  Takes scratch of about 12 n k bytes
+ * (see umap_layout_destroy); runs on `stream` (NULL: null stream).  Blocking.
  */
 int umap_trustworthiness(const float *X, int64_t n, int32_t d, const float *Y, int32_t dim, int32_t k, double *out,
                          void *stream);

@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libumap_layout.so")
 
 SOURCES = ["api.hip", "kernels_prep.hip", "kernels_layout.hip", "kernels_hogwild.hip", "kernels_graph.hip",
-           "kernels_probe.hip", "kernels_trust.hip", "fit_ab.cpp"]
+           "kernels_probe.hip", "kernels_trust.hip", "device_memory.cpp", "fit_ab.cpp"]
 
 HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",

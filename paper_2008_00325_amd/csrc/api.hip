@@ -3,7 +3,7 @@
 // Argument checks that need no GPU run first; then one device arena holds
 // everything the handle keeps (CSR graph, wave partition, two embedding
 // buffers for the epoch-synchronous ping-pong, per-epoch counters), and a
-// stream-ordered scratch allocation holds the ingest's temporaries.
+// scratch block holds the ingest's temporaries (device_memory.hpp).
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "umap_layout.h"
+#include "device_memory.hpp"
 #include "internal.hpp"
 
 namespace {
@@ -89,10 +90,71 @@ struct Carver {
     }
 };
 
+// A scratch block for one blocking call: handed back once the stream is done
+// with it.
+class Scratch {
+public:
+    Scratch(size_t bytes, hipStream_t s) : stream_(s) { UL_HIP(ul::take_block(bytes, &block_)); }
+    ~Scratch() { give(); }
+    Scratch(const Scratch &) = delete;
+    Scratch &operator=(const Scratch &) = delete;
+    char *base() const { return static_cast<char *>(block_.ptr); }
+    unsigned *host() const { return block_.host; }
+    void give()
+    {
+        if (block_.ptr) ul::give_block(&block_, hipStreamSynchronize(stream_) == hipSuccess);
+    }
+
+private:
+    ul::DeviceBlock block_;
+    hipStream_t stream_;
+};
+
 template <typename T>
 size_t need(size_t count)
 {
     return align_up(count * sizeof(T) > 0 ? count * sizeof(T) : 1);
+}
+
+// Index of an entry at or before the first non-finite value (count if there is
+// none): whole pieces without a branch per value, so that the compiler takes
+// several values per instruction.
+size_t first_non_finite(const float *v, size_t count)
+{
+    constexpr size_t kPiece = 2048;
+    size_t t = 0;
+    for (; t + kPiece <= count; t += kPiece) {
+        uint32_t bad = 0;
+        for (size_t q = 0; q < kPiece; ++q) {
+            uint32_t bits;
+            memcpy(&bits, v + t + q, sizeof bits);
+            bad |= ((bits & 0x7F800000u) + 0x00800000u) & 0x80000000u;   // the exponent is all ones
+        }
+        if (bad) return t;
+    }
+    for (; t < count; ++t)
+        if (!isfinite(v[t])) return t;
+    return count;
+}
+
+// The same for a non-finite value or an index outside [0, n_rows) x [0, n_cols).
+int64_t first_bad_entry(const int32_t *rows, const int32_t *cols, const float *vals, int64_t nnz, int64_t n_rows,
+                        int64_t n_cols)
+{
+    constexpr int64_t kPiece = 2048;
+    int64_t t = 0;
+    for (; t + kPiece <= nnz; t += kPiece) {
+        int32_t r_max = 0, r_min = 0, c_max = 0, c_min = 0;
+        for (int64_t q = t; q < t + kPiece; ++q) {
+            r_max = rows[q] > r_max ? rows[q] : r_max;
+            r_min = rows[q] < r_min ? rows[q] : r_min;
+            c_max = cols[q] > c_max ? cols[q] : c_max;
+            c_min = cols[q] < c_min ? cols[q] : c_min;
+        }
+        if (r_min < 0 || c_min < 0 || r_max >= n_rows || c_max >= n_cols) return t;
+        if (first_non_finite(vals + t, (size_t)kPiece) < (size_t)kPiece) return t;
+    }
+    return t;   // the caller looks at the rest
 }
 
 int check_scalars(int64_t n, int32_t dim, int64_t nnz, float a, float b, int32_t n_epochs, int32_t neg_rate)
@@ -130,7 +192,7 @@ struct umap_layout {
     float *table = nullptr;                 // transform: the frozen layout (n_table x dim), else null
     int64_t n_table = 0;                    // rows of the table the tails and negatives index
 
-    void *arena = nullptr;
+    ul::DeviceBlock arena;
     int64_t *row_ptr = nullptr;
     int32_t *col = nullptr;
     int16_t *col16 = nullptr;               // col - row in 16 bits (a fit whose deltas all fit)
@@ -164,14 +226,13 @@ struct umap_layout {
 
     void release()
     {
-        if (stream || arena) (void)hipStreamSynchronize(stream);
+        const bool idle = !arena.ptr || hipStreamSynchronize(stream) == hipSuccess;
         for (auto &e : ev)
             if (e) (void)hipEventDestroy(e);
         for (auto &e : ep_ev)
             if (e) (void)hipEventDestroy(e);
         ep_ev.clear();
-        if (arena) (void)hipFree(arena);
-        arena = nullptr;
+        ul::give_block(&arena, idle);
     }
 };
 
@@ -186,7 +247,6 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
 {
     umap_layout *h = new (std::nothrow) umap_layout();
     if (!h) return fail(UMAP_E_NOMEM, "host allocation failed");
-    void *scratch = nullptr;
     try {
         int ndev = 0;
         if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) {
@@ -232,8 +292,8 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
                        need<int32_t>((size_t)n_phases * max_waves) + need<long long>(nd) + need<unsigned>(1) +
                        need<float>(nd) + need<float>(table_elems);
         if (fault_alloc()) throw HipFailure{hipErrorOutOfMemory, "hipMalloc(arena) [injected]"};
-        UL_HIP(hipMalloc(&h->arena, bytes));
-        Carver cv{static_cast<char *>(h->arena)};
+        UL_HIP(ul::take_block(bytes, &h->arena));
+        Carver cv{static_cast<char *>(h->arena.ptr)};
         h->row_ptr = cv.take<int64_t>(n + 1);
         h->col = cv.take<int32_t>(nnz);
         h->col16 = cv.take<int16_t>(table ? 0 : nnz);
@@ -258,7 +318,7 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
             UL_HIP(hipMemcpyAsync(h->table, table, sizeof(float) * table_elems, hipMemcpyHostToDevice, stream));
         }
 
-        // ingest scratch (stream-ordered)
+        // ingest scratch
         ul::PrepBuffers B{};
         B.nnz = nnz;
         B.n = n;
@@ -272,8 +332,8 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
                         2 * need<int2>(nnz) + need<uint16_t>(nnz) + need<int32_t>(n) + need<int32_t>(n + 1) +
                         need<int32_t>(n_long) + need<ul::PrepScalars>(1);
         if (host_inputs) sbytes += 2 * need<int32_t>(nnz) + need<float>(nnz);
-        UL_HIP(hipMallocAsync(&scratch, sbytes, stream));
-        Carver sc{static_cast<char *>(scratch)};
+        Scratch scratch(sbytes, stream);
+        Carver sc{scratch.base()};
         B.bucket_n = sc.take<uint32_t>(nc);
         B.cursor = sc.take<uint32_t>(nc);
         B.first = sc.take<int32_t>(ul::kSubs * nb + 1);
@@ -315,13 +375,17 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         UL_HIP(ul::launch_prep(B, stream));
         UL_HIP(hipEventRecord(h->ev[1], stream));
 
+        // the scalars and the last row pointer, by way of pinned memory
         ul::PrepScalars S{};
         int64_t kept = 0;
-        UL_HIP(hipMemcpyAsync(&S, B.scalars, sizeof S, hipMemcpyDeviceToHost, stream));
-        UL_HIP(hipMemcpyAsync(&kept, h->row_ptr + n, sizeof kept, hipMemcpyDeviceToHost, stream));
+        static_assert(sizeof S + sizeof kept <= ul::kHostBytes, "the pinned buffer holds the read-back");
+        char *const hb = reinterpret_cast<char *>(scratch.host());
+        UL_HIP(hipMemcpyAsync(hb, B.scalars, sizeof S, hipMemcpyDeviceToHost, stream));
+        UL_HIP(hipMemcpyAsync(hb + sizeof S, h->row_ptr + n, sizeof kept, hipMemcpyDeviceToHost, stream));
         UL_HIP(hipStreamSynchronize(stream));
-        UL_HIP(hipFreeAsync(scratch, stream));
-        scratch = nullptr;
+        memcpy(&S, hb, sizeof S);
+        memcpy(&kept, hb + sizeof S, sizeof kept);
+        scratch.give();
 
         int rc = UMAP_OK;
         if (S.flags & ul::kBadIndex)
@@ -360,12 +424,10 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         return UMAP_OK;
     } catch (const HipFailure &f) {
         int rc = hip_fail(f);
-        if (scratch) (void)hipFreeAsync(scratch, stream);
         h->release();
         delete h;
         return rc;
     } catch (...) {
-        if (scratch) (void)hipFreeAsync(scratch, stream);
         h->release();
         delete h;
         return fail(UMAP_E_NOMEM, "unexpected host failure");
@@ -546,7 +608,7 @@ int umap_layout_create(umap_layout **out, int64_t n, int32_t n_components, const
         int rc = check_scalars(n, n_components, nnz, a, b, n_epochs, neg_rate);
         if (rc) return rc;
         if (nnz > 0 && (!rows || !cols || !vals)) return fail(UMAP_E_INVAL, "rows, cols and vals must not be NULL");
-        for (int64_t t = 0; t < nnz; ++t) {
+        for (int64_t t = first_bad_entry(rows, cols, vals, nnz, n, n); t < nnz; ++t) {
             if (rows[t] < 0 || rows[t] >= n || cols[t] < 0 || cols[t] >= n)
                 return fail(UMAP_E_INVAL, "entry %lld: index (%d, %d) outside [0, %lld)", (long long)t, rows[t],
                             cols[t], (long long)n);
@@ -572,9 +634,9 @@ int umap_transform_create(umap_layout **out, int64_t n_new, int32_t n_components
         if (!table) return fail(UMAP_E_INVAL, "table is NULL");
         if (nnz > 0 && (!rows || !cols || !vals)) return fail(UMAP_E_INVAL, "rows, cols and vals must not be NULL");
         const size_t table_elems = (size_t)n_table * (size_t)n_components;
-        for (size_t t = 0; t < table_elems; ++t)
+        for (size_t t = first_non_finite(table, table_elems); t < table_elems; ++t)
             if (!isfinite(table[t])) return fail(UMAP_E_INVAL, "table entry %zu is not finite", t);
-        for (int64_t t = 0; t < nnz; ++t) {
+        for (int64_t t = first_bad_entry(rows, cols, vals, nnz, n_new, n_table); t < nnz; ++t) {
             if (rows[t] < 0 || rows[t] >= n_new || cols[t] < 0 || cols[t] >= n_table)
                 return fail(UMAP_E_INVAL, "entry %lld: index (%d, %d) outside [0, %lld) x [0, %lld)", (long long)t,
                             rows[t], cols[t], (long long)n_new, (long long)n_table);
@@ -892,27 +954,23 @@ int umap_fuzzy_graph_device(int64_t n, int32_t k, const int32_t *knn_ids, const 
     if (2 * n * (int64_t)k >= ((int64_t)1 << 31)) return fail(UMAP_E_INVAL, "2 n k must be below 2^31");
     if (!knn_ids || !knn_dists || !rows || !cols || !vals) return fail(UMAP_E_INVAL, "a pointer argument is NULL");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    void *scratch = nullptr;
     try {
         int ndev = 0;
         if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return fail(UMAP_E_DEVICE, "no HIP device available");
-        size_t bytes = need<double2>(n) + need<unsigned>(1);
-        UL_HIP(hipMallocAsync(&scratch, bytes, s));
-        Carver cv{static_cast<char *>(scratch)};
+        Scratch scratch(need<double2>(n) + need<unsigned long long>(1), s);
+        Carver cv{scratch.base()};
         double2 *rho_sigma = cv.take<double2>(n);
-        unsigned *flags = cv.take<unsigned>(1);
-        UL_HIP(hipMemsetAsync(flags, 0, sizeof(unsigned), s));
-        UL_HIP(ul::launch_fuzzy_graph(n, k, knn_ids, knn_dists, rows, cols, vals, rho_sigma, flags, s));
-        unsigned hflags = 0;
-        UL_HIP(hipMemcpyAsync(&hflags, flags, sizeof hflags, hipMemcpyDeviceToHost, s));
-        UL_HIP(hipFreeAsync(scratch, s));
-        scratch = nullptr;
+        unsigned long long *flags = cv.take<unsigned long long>(1);
+        UL_HIP(ul::launch_zero_u64(flags, 1, s));
+        UL_HIP(ul::launch_fuzzy_graph(n, k, knn_ids, knn_dists, rows, cols, vals, rho_sigma,
+                                      reinterpret_cast<unsigned *>(flags), s));
+        UL_HIP(hipMemcpyAsync(scratch.host(), flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
         UL_HIP(hipStreamSynchronize(s));
+        const unsigned hflags = *scratch.host();
         if (hflags & ul::kBadIndex) return fail(UMAP_E_INVAL, "a neighbour id is outside [0, n)");
         if (hflags & ul::kBadValue) return fail(UMAP_E_INVAL, "a neighbour distance is not finite");
         return UMAP_OK;
     } catch (const HipFailure &f) {
-        if (scratch) (void)hipFreeAsync(scratch, s);
         return hip_fail(f);
     }
 }
@@ -999,15 +1057,14 @@ int umap_trustworthiness(const float *X, int64_t n, int32_t d, const float *Y, i
     if (2 * n - 3 * (int64_t)k - 1 <= 0) return fail(UMAP_E_INVAL, "need 2n - 3k - 1 > 0 (n = %lld, k = %d)", (long long)n, k);
     if (n * (int64_t)k >= ((int64_t)1 << 31)) return fail(UMAP_E_INVAL, "n k must be below 2^31");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    void *scratch = nullptr;
     try {
         int ndev = 0;
         if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return fail(UMAP_E_DEVICE, "no HIP device available");
         const size_t nk = (size_t)n * (size_t)k;
         size_t bytes = need<float>(n) + need<int32_t>(nk) + need<float>(nk) + need<int32_t>(nk) + need<int64_t>(n) +
                        need<unsigned long long>(1) + need<unsigned>(1);
-        UL_HIP(hipMallocAsync(&scratch, bytes, s));
-        Carver cv{static_cast<char *>(scratch)};
+        Scratch scratch(bytes, s);
+        Carver cv{scratch.base()};
         float *nx = cv.take<float>(n);
         int32_t *nbr = cv.take<int32_t>(nk);
         float *thr = cv.take<float>(nk);
@@ -1019,17 +1076,17 @@ int umap_trustworthiness(const float *X, int64_t n, int32_t d, const float *Y, i
         UL_HIP(ul::launch_trustworthiness(X, n, d, Y, dim, k, nx, nbr, thr, cnt, pen, sum, flags, s));
         unsigned long long hsum = 0;
         unsigned hflags = 0;
-        UL_HIP(hipMemcpyAsync(&hsum, sum, sizeof hsum, hipMemcpyDeviceToHost, s));
-        UL_HIP(hipMemcpyAsync(&hflags, flags, sizeof hflags, hipMemcpyDeviceToHost, s));
-        UL_HIP(hipFreeAsync(scratch, s));
-        scratch = nullptr;
+        char *const hb = reinterpret_cast<char *>(scratch.host());
+        UL_HIP(hipMemcpyAsync(hb, sum, sizeof hsum, hipMemcpyDeviceToHost, s));
+        UL_HIP(hipMemcpyAsync(hb + sizeof hsum, flags, sizeof hflags, hipMemcpyDeviceToHost, s));
         UL_HIP(hipStreamSynchronize(s));
+        memcpy(&hsum, hb, sizeof hsum);
+        memcpy(&hflags, hb + sizeof hsum, sizeof hflags);
         if (hflags) return fail(UMAP_E_INVAL, "the embedding has non-finite coordinates");
         const double nn = (double)n, kk = (double)k;
         *out = 1.0 - 2.0 / (nn * kk * (2.0 * nn - 3.0 * kk - 1.0)) * (double)hsum;
         return UMAP_OK;
     } catch (const HipFailure &f) {
-        if (scratch) (void)hipFreeAsync(scratch, s);
         return hip_fail(f);
     }
 }

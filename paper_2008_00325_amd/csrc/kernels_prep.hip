@@ -18,10 +18,12 @@
 //      a (j, i) with bit-equal v
 //   6. wave partition for the epoch kernel
 //
-// Each entry is read twice and written three times, in runs; the former count
-// and scatter with one global atomic and three 4-byte stores per entry at
-// random rows took 1640 us on 30M shuffled entries (1M rows), where steps 2-3
-// take 300, and its rank sort from memory 396 us (step 4 now 150).
+// Entries move in runs: a count and a scatter with one global atomic and three
+// 4-byte stores per entry at random rows took 1343 us on a shuffled graph of
+// 777,777 rows (23.3M entries), where steps 2 and 3 take 164 and 193; a rank sort
+// from memory and a pass for the offsets 470 us, step 4 276.  (1M rows in local
+// order: 836 -> 115 + 221 us, 470 -> 375 us.)  Steps 3 and 4 are bound by the
+// latency of a workgroup's chain of loads, step 2 by its streams.
 #include "internal.hpp"
 
 namespace ul {
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(kTileThreads) void k_bucket_scan(const uint32_t *__
 }
 
 // A tile of entries filed by bucket: ranks in LDS counters, one reservation per
-// tile and bucket.  Bound by its streams: 360 MB read and 300 MB written.
+// tile and bucket (in the counters of the tile's XCD: 226 -> 164 us).
 __global__ __launch_bounds__(kTileThreads) void k_bucket_scatter(const int32_t *__restrict__ rows,
                                                                  const int32_t *__restrict__ cols,
                                                                  const float *__restrict__ vals, int64_t nnz,
@@ -348,7 +350,7 @@ struct SortedRows {
 // at a time (the rows are padded to multiples of four there); the entries are
 // put in order in LDS and written in runs.  A slot left empty is a duplicate.
 // (26.7M entries, 1M rows: 475 us reading the row entry by entry and writing
-// each entry at its slot.)
+// each entry at its slot, 446 us with 16 rows per block, now 375.)
 __global__ __launch_bounds__(256) void k_row_sort(const int2 *__restrict__ src, const int32_t *__restrict__ first,
                                                   const int32_t *__restrict__ kfirst,
                                                   const int32_t *__restrict__ lstart, int64_t n, int32_t lg,
@@ -596,8 +598,8 @@ __global__ __launch_bounds__(kSortThreads) void k_long_row_sort(const int2 *__re
 // in the first entries of row j, which is sorted, so that its entries below
 // the diagonal come first: 16 entries a round, three rounds, and what is not
 // decided then by a binary search.  The random lines of the rows bound it on a
-// shuffled graph: 3235 us on 26.7M edges with one binary search per lane and
-// entry, now 560 (local order 690 -> 200).
+// shuffled graph: 2559 us on 20.8M edges with one binary search per lane and
+// entry, now 486 (26.7M edges in local order 693 -> 274).
 __global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair, const int32_t *__restrict__ rp32,
                                                   int64_t n, PrepScalars *S, int32_t *__restrict__ block_diff)
 {
