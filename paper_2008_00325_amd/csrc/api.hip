@@ -56,7 +56,8 @@ int hip_fail(const HipFailure &f)
 // arena allocation report out-of-memory; UMAP_LAYOUT_FAULT=launch@K makes the
 // launch of epoch K report a device error (nothing is launched in either
 // case); UMAP_LAYOUT_FAULT=records gives the wavefront kernel no record slots,
-// so every negative sample overflows and the epochs are redone.
+// so every negative sample overflows and the epochs are redone;
+// UMAP_LAYOUT_FAULT=split gives the trustworthiness no room for the points' parts.
 bool fault_alloc()
 {
     const char *f = getenv("UMAP_LAYOUT_FAULT");
@@ -67,6 +68,12 @@ bool fault_records()
 {
     const char *f = getenv("UMAP_LAYOUT_FAULT");
     return f && strcmp(f, "records") == 0;
+}
+
+bool fault_split()
+{
+    const char *f = getenv("UMAP_LAYOUT_FAULT");
+    return f && strcmp(f, "split") == 0;
 }
 
 int fault_launch_epoch()
@@ -94,7 +101,9 @@ struct Carver {
 // with it.
 class Scratch {
 public:
-    Scratch(size_t bytes, hipStream_t s) : stream_(s) { UL_HIP(ul::take_block(bytes, &block_)); }
+    explicit Scratch(hipStream_t s) : stream_(s) {}
+    Scratch(size_t bytes, hipStream_t s) : stream_(s) { UL_HIP(take(bytes)); }
+    hipError_t take(size_t bytes) { return ul::take_block(bytes, &block_); }
     ~Scratch() { give(); }
     Scratch(const Scratch &) = delete;
     Scratch &operator=(const Scratch &) = delete;
@@ -1060,20 +1069,28 @@ int umap_trustworthiness(const float *X, int64_t n, int32_t d, const float *Y, i
     try {
         int ndev = 0;
         if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return fail(UMAP_E_DEVICE, "no HIP device available");
-        const size_t nk = (size_t)n * (size_t)k;
-        size_t bytes = need<float>(n) + need<int32_t>(nk) + need<float>(nk) + need<int32_t>(nk) + need<int64_t>(n) +
-                       need<unsigned long long>(1) + need<unsigned>(1);
-        Scratch scratch(bytes, s);
+        const size_t np = (size_t)ul::trust_padded(n), nk = np * (size_t)k;
+        const size_t rest = need<float>(np) + 2 * need<int32_t>(nk) + need<float>(nk) + need<unsigned long long>(2);
+        size_t split_bytes = fault_split() ? 0 : ul::trust_split_bytes(n, d);
+        Scratch scratch(s);
+        hipError_t taken = scratch.take(need<char>(split_bytes) + rest);
+        if (taken != hipSuccess && split_bytes) {   // no room for the parts: the kernels on X itself
+            (void)hipGetLastError();
+            split_bytes = 0;
+            taken = scratch.take(need<char>(split_bytes) + rest);
+        }
+        UL_HIP(taken);
         Carver cv{scratch.base()};
-        float *nx = cv.take<float>(n);
+        char *split = cv.take<char>(split_bytes);
+        float *nx = cv.take<float>(np);
         int32_t *nbr = cv.take<int32_t>(nk);
         float *thr = cv.take<float>(nk);
         int32_t *cnt = cv.take<int32_t>(nk);
-        int64_t *pen = cv.take<int64_t>(n);
-        unsigned long long *sum = cv.take<unsigned long long>(1);
-        unsigned *flags = cv.take<unsigned>(1);
-        UL_HIP(hipMemsetAsync(flags, 0, sizeof(unsigned), s));
-        UL_HIP(ul::launch_trustworthiness(X, n, d, Y, dim, k, nx, nbr, thr, cnt, pen, sum, flags, s));
+        unsigned long long *sum = cv.take<unsigned long long>(2);
+        unsigned *flags = reinterpret_cast<unsigned *>(sum + 1);
+        UL_HIP(ul::launch_zero_u64(sum, 2, s));
+        UL_HIP(ul::launch_trustworthiness(X, n, d, Y, dim, k, split_bytes ? split : nullptr, nx, nbr, thr, cnt, sum,
+                                          flags, s));
         unsigned long long hsum = 0;
         unsigned hflags = 0;
         char *const hb = reinterpret_cast<char *>(scratch.host());

@@ -207,10 +207,16 @@ hipError_t launch_probe_gather(const void *table, int64_t entries, int64_t threa
                                hipStream_t s);
 
 // ---- trustworthiness (kernels_trust.hip) ----
-// Scratch: nx[n], nbr[n k], thr[n k], cnt[n k], pen[n], sum[1], flags[1]
-// (flags zeroed by the caller).
+// The ranks come from the points split into bf16 parts (trust_split_bytes; 0
+// beyond kTrustSplitBytes: from fp32 products of X itself, every pair twice).
+constexpr int64_t kTrustSplitBytes = (int64_t)16 << 30;
+int64_t trust_padded(int64_t n);
+size_t trust_split_bytes(int64_t n, int32_t d);
+// Scratch, with np = trust_padded(n): split (or null), nx[np], nbr[np k],
+// thr[np k], cnt[np k] (slot s of point i at s np + i), sum[1] and flags[1]
+// (both zeroed by the caller).
 hipError_t launch_trustworthiness(const float *X, int64_t n, int32_t d, const float *Y, int32_t dim, int32_t k,
-                                  float *nx, int32_t *nbr, float *thr, int32_t *cnt, int64_t *pen,
+                                  void *split, float *nx, int32_t *nbr, float *thr, int32_t *cnt,
                                   unsigned long long *sum, unsigned *flags, hipStream_t s);
 
 // ---- fuzzy graph (kernels_graph.hip) ----

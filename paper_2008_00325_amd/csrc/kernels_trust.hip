@@ -9,16 +9,17 @@
 // excluded, ties by index); neighbours with r <= k are the input neighbours
 // and add nothing.
 //
-//  1. k_tw_norms: |x_i|^2 of every input row.
+//  1. k_tw_split: every input row as three bf16 parts per feature, and |x_i|^2
+//     (k_tw_norms where the parts would not fit).
 //  2. k_tw_embed_knn: one wavefront per point, a brute-force scan of the
 //     embedding keeping the k best (distance, index) pairs sorted across lanes.
 //  3. k_tw_thresholds: input distance from i to each embedding neighbour.
-//  4. k_tw_rank: the input distances of blocks of 128 points to tiles of
-//     columns as fp32 MFMA tiles (v_mfma_f32_16x16x4f32), turned into
-//     distances in registers and compared with each point's neighbour
-//     thresholds: only the counts r(i, j) - 1 leave the chip, never the n x n
-//     distances.
-//  5. k_tw_penalty: per-point penalty sum; k_tw_sum: one fixed-order reduction.
+//  4. k_tw_rank_pairs: the input distances of every pair of points once, as tiles
+//     of 128 x 128 on the bf16 matrix cores, compared in registers with the
+//     neighbour thresholds of both points: only the counts r(i, j) - 1 leave the
+//     chip, never the n x n distances.  (k_tw_rank: every pair twice, fp32
+//     matrix instructions on X itself; only where the parts would not fit.)
+//  5. k_tw_penalty: the penalties' sum.
 #include "internal.hpp"
 
 namespace ul {
@@ -54,13 +55,30 @@ __device__ __forceinline__ uint64_t pair_key(float a, int32_t ia)
     return ((uint64_t)ord << 32) | (uint32_t)ia;
 }
 
+// the value of a lane given by a uniform number, as a uniform value
+__device__ __forceinline__ float read_lane(float v, int lane)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+// the value of the lane below (lane 0: its own), without the LDS crossbar
+__device__ __forceinline__ int from_lane_below(int v)
+{
+    return __builtin_amdgcn_update_dpp(v, v, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
+}
+
 // One wavefront per point i: lanes 0..k-1 hold the k best (distance, index)
-// pairs seen so far, ascending; each chunk of 64 candidates is merged by
-// inserting the qualifying lanes one at a time.
+// pairs seen so far, ascending; the points come in chunks of 64, and the lanes of
+// a chunk that qualify are inserted one at a time.  Later candidates have larger
+// indices, so once the list is full a candidate must be strictly closer than its
+// last entry, whose distance is kept as a uniform value; kAhead chunks are
+// loaded and compared together, and most groups hold no candidate.  (Fetching the
+// last pair from its lane for every chunk, one chunk at a time: 443 us at 20,000
+// points, 3620 at 70,000; now 360 and 2340.)
 template <int DIM>
-__global__ __launch_bounds__(256) void k_tw_embed_knn(const float *__restrict__ Y, int64_t n, int32_t k,
+__global__ __launch_bounds__(256) void k_tw_embed_knn(const float *__restrict__ Y, int64_t n, int32_t k, int64_t np,
                                                       int32_t *__restrict__ nbr)
 {
+    constexpr int kAhead = DIM <= 2 ? 8 : DIM <= 4 ? 4 : DIM <= 8 ? 2 : 1;
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kWave;
     if (i >= n) return;
     const int lane = (int)(threadIdx.x % kWave);
@@ -69,45 +87,62 @@ __global__ __launch_bounds__(256) void k_tw_embed_knn(const float *__restrict__ 
     for (int q = 0; q < DIM; ++q) yi[q] = Y[i * DIM + q];
     float bd = INFINITY;
     int32_t bi = 0x7FFFFFFF;
-    for (int64_t base = 0; base < n; base += kWave) {
-        const int64_t c = base + lane;
-        float dc = INFINITY;
-        if (c < n && c != i) {
-            dc = 0.0f;
+    float last = INFINITY;   // distance of entry k - 1
+    bool full = false;
+    for (int64_t base = 0; base < n; base += kAhead * kWave) {
+        float y[kAhead][DIM], dc[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t c = base + u * kWave + lane;
+            const int64_t cc = c < n ? c : n - 1;
+#pragma unroll
+            for (int q = 0; q < DIM; ++q) y[u][q] = Y[cc * DIM + q];
+        }
+        float least = NAN;   // fminf ignores it
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t c = base + u * kWave + lane;
+            float s = 0.0f;
 #pragma unroll
             for (int q = 0; q < DIM; ++q) {
-                const float t = Y[c * DIM + q] - yi[q];
-                dc = fmaf(t, t, dc);
+                const float t = y[u][q] - yi[q];
+                s = fmaf(t, t, s);
             }
+            dc[u] = c < n && c != i ? s : NAN;   // NaN: never a candidate
+            least = fminf(least, dc[u]);
         }
-        const int32_t ci = (int32_t)c;
-        bool pending = c < n && c != i;
-        while (true) {
-            const float td = __shfl(bd, k - 1);
-            const int32_t ti = __shfl(bi, k - 1);
-            pending = pending && pair_less(dc, ci, td, ti);
-            const unsigned long long m = __ballot(pending);
-            if (m == 0) break;
-            const int src = __ffsll((long long)m) - 1;
-            const float nd = __shfl(dc, src);
-            const int32_t ni = __shfl(ci, src);
-            if (lane == src) pending = false;
-            // insertion position: slots holding a smaller pair
-            const int pos = __popcll(__ballot(lane < k && pair_less(bd, bi, nd, ni)));
-            const float up_d = __shfl_up(bd, 1);
-            const int32_t up_i = __shfl_up(bi, 1);
-            if (lane < k) {
-                if (lane == pos) {
-                    bd = nd;
-                    bi = ni;
-                } else if (lane > pos) {
-                    bd = up_d;
-                    bi = up_i;
+        if (full && __ballot(least < last) == 0) continue;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int32_t ci = (int32_t)(base + u * kWave + lane);
+            bool pending = true;
+            while (true) {
+                pending = pending && (full ? dc[u] < last : dc[u] <= last);
+                const unsigned long long m = __ballot(pending);
+                if (m == 0) break;
+                const int src = __ffsll((long long)m) - 1;
+                const float nd = read_lane(dc[u], src);
+                const int32_t ni = __builtin_amdgcn_readlane(ci, src);
+                if (lane == src) pending = false;
+                // insertion position: slots holding a smaller pair
+                const int pos = __popcll(__ballot(lane < k && pair_less(bd, bi, nd, ni)));
+                const float up_d = __int_as_float(from_lane_below(__float_as_int(bd)));
+                const int32_t up_i = from_lane_below(bi);
+                if (lane < k) {
+                    if (lane == pos) {
+                        bd = nd;
+                        bi = ni;
+                    } else if (lane > pos) {
+                        bd = up_d;
+                        bi = up_i;
+                    }
                 }
+                last = read_lane(bd, k - 1);
+                full = __builtin_amdgcn_readlane(bi, k - 1) != 0x7FFFFFFF;
             }
         }
     }
-    if (lane < k) nbr[i * k + lane] = bi;
+    if (lane < k) nbr[(int64_t)lane * np + i] = bi;
 }
 
 // One wavefront per point i: the input distance to each of its k embedding
@@ -116,18 +151,19 @@ __global__ __launch_bounds__(256) void k_tw_embed_knn(const float *__restrict__ 
 // running threshold) raises `flags` and gets a threshold that nothing counts
 // against.
 __global__ __launch_bounds__(256) void k_tw_thresholds(const float *__restrict__ X, int64_t n, int32_t d, int32_t k,
-                                                       const float *__restrict__ nx, const int32_t *__restrict__ nbr,
-                                                       float *__restrict__ thr, unsigned *__restrict__ flags)
+                                                       int64_t np, const float *__restrict__ nx,
+                                                       const int32_t *__restrict__ nbr, float *__restrict__ thr,
+                                                       unsigned *__restrict__ flags)
 {
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kWave;
     const int lane = threadIdx.x % kWave;
     if (i >= n) return;   // whole waves
     const float *xi = X + i * d;
     for (int32_t s = 0; s < k; ++s) {
-        const int64_t j = nbr[i * k + s];   // the same for every lane
+        const int64_t j = nbr[s * np + i];   // the same for every lane
         if (j < 0 || j >= n) {
             if (lane == 0) {
-                thr[i * k + s] = -INFINITY;
+                thr[s * np + i] = -INFINITY;
                 atomicOr(flags, 1u);
             }
             continue;
@@ -137,7 +173,7 @@ __global__ __launch_bounds__(256) void k_tw_thresholds(const float *__restrict__
         for (int32_t q = lane; q < d; q += kWave) dot = fmaf(xi[q], xj[q], dot);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off);
-        if (lane == 0) thr[i * k + s] = nx[i] + nx[j] - 2.0f * dot;
+        if (lane == 0) thr[s * np + i] = nx[i] + nx[j] - 2.0f * dot;
     }
 }
 
@@ -178,7 +214,7 @@ __device__ __forceinline__ float4 load_features(const float *__restrict__ X, int
 }
 
 template <int KMAX, int CT, int CH>
-__device__ __forceinline__ void rank_body(const float *__restrict__ X, int64_t n, int32_t d, int32_t k,
+__device__ __forceinline__ void rank_body(const float *__restrict__ X, int64_t n, int32_t d, int32_t k, int64_t np,
                                           const float *__restrict__ nx, const int32_t *__restrict__ nbr,
                                           const float *__restrict__ thr, int64_t tiles_per_split,
                                           int32_t *__restrict__ cnt_out)
@@ -211,7 +247,7 @@ __device__ __forceinline__ void rank_body(const float *__restrict__ X, int64_t n
 #pragma unroll
     for (int s = 0; s < KMAX; ++s) {
         const bool use = row_ok && s < k;
-        tkey[s] = use ? pair_key(thr[row * k + s], nbr[row * k + s]) : 0ull;
+        tkey[s] = use ? pair_key(thr[s * np + row], nbr[s * np + row]) : 0ull;
         cnt[s] = 0;
     }
     const float nrow = row_ok ? nx[row] : 0.0f;
@@ -305,23 +341,27 @@ __device__ __forceinline__ void rank_body(const float *__restrict__ X, int64_t n
         int32_t c = cnt[s];
         c += __shfl_xor(c, 16);
         c += __shfl_xor(c, 32);
-        if (row_ok && g == 0 && s < k && c != 0) atomicAdd(&cnt_out[row * k + s], c);
+        if (row_ok && g == 0 && s < k && c != 0) atomicAdd(&cnt_out[s * np + row], c);
     }
 }
 
-// pen[i] = sum_s max(0, r(i, nbr_s) - k), r = 1 + the count of points before
-// the neighbour.
-__global__ __launch_bounds__(256) void k_tw_penalty(const int32_t *__restrict__ cnt, int64_t n, int32_t k,
-                                                    int64_t *__restrict__ pen)
+// *sum += sum_i sum_s max(0, r(i, nbr_s) - k), r = 1 + the count of points before
+// the neighbour: whole numbers, so the order of the adds does not matter.
+__global__ __launch_bounds__(256) void k_tw_penalty(const int32_t *__restrict__ cnt, int64_t n, int32_t k, int64_t np,
+                                                    unsigned long long *__restrict__ sum)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
     int64_t p = 0;
-    for (int32_t s = 0; s < k; ++s) {
-        const int64_t rank = (int64_t)cnt[i * k + s] + 1;
-        if (rank > k) p += rank - k;
-    }
-    pen[i] = p;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        for (int32_t s = 0; s < k; ++s) {
+            const int64_t rank = (int64_t)cnt[s * np + i] + 1;
+            if (rank > k) p += rank - k;
+        }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) p += __shfl_xor(p, off);
+    __shared__ long long s_p[4];
+    if ((threadIdx.x & 63) == 0) s_p[threadIdx.x >> 6] = p;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(sum, (unsigned long long)(s_p[0] + s_p[1] + s_p[2] + s_p[3]));
 }
 
 __global__ __launch_bounds__(256) void k_tw_zero(int32_t *__restrict__ p, int64_t count)
@@ -332,26 +372,27 @@ __global__ __launch_bounds__(256) void k_tw_zero(int32_t *__restrict__ p, int64_
 
 template <int KMAX, int CT, int CH>
 __global__ __launch_bounds__(512) void k_tw_rank(const float *__restrict__ X, int64_t n, int32_t d, int32_t k,
-                                                 const float *__restrict__ nx, const int32_t *__restrict__ nbr,
-                                                 const float *__restrict__ thr, int64_t tiles_per_split,
+                                                 int64_t np, const float *__restrict__ nx,
+                                                 const int32_t *__restrict__ nbr, const float *__restrict__ thr,
+                                                 int64_t tiles_per_split,
                                                  int32_t *__restrict__ cnt_out)
 {
-    rank_body<KMAX, CT, CH>(X, n, d, k, nx, nbr, thr, tiles_per_split, cnt_out);
+    rank_body<KMAX, CT, CH>(X, n, d, k, np, nx, nbr, thr, tiles_per_split, cnt_out);
 }
 
 // The same for k <= 16, held to 128 registers: two blocks per CU, which this
 // instance reaches without spilling (the wider ones would spill).
 template <int KMAX, int CT, int CH>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_tw_rank_occ(
-    const float *__restrict__ X, int64_t n, int32_t d, int32_t k, const float *__restrict__ nx,
+    const float *__restrict__ X, int64_t n, int32_t d, int32_t k, int64_t np, const float *__restrict__ nx,
     const int32_t *__restrict__ nbr, const float *__restrict__ thr, int64_t tiles_per_split,
     int32_t *__restrict__ cnt_out)
 {
-    rank_body<KMAX, CT, CH>(X, n, d, k, nx, nbr, thr, tiles_per_split, cnt_out);
+    rank_body<KMAX, CT, CH>(X, n, d, k, np, nx, nbr, thr, tiles_per_split, cnt_out);
 }
 
 template <int KMAX, int CT, int CH = kRankChunk>
-static void launch_rank(const float *X, int64_t n, int32_t d, int32_t k, const float *nx, const int32_t *nbr,
+static void launch_rank(const float *X, int64_t n, int32_t d, int32_t k, int64_t np, const float *nx, const int32_t *nbr,
                         const float *thr, int32_t *cnt, hipStream_t s)
 {
     const int64_t row_blocks = (n + kRkRows - 1) / kRkRows;
@@ -364,65 +405,430 @@ static void launch_rank(const float *X, int64_t n, int32_t d, int32_t k, const f
     splits = (n_tiles + per_split - 1) / per_split;
     if constexpr (KMAX <= 16)
         hipLaunchKernelGGL((k_tw_rank_occ<KMAX, CT, CH>), dim3((unsigned)row_blocks, (unsigned)splits), dim3(512), 0,
-                           s, X, n, d, k, nx, nbr, thr, per_split, cnt);
+                           s, X, n, d, k, np, nx, nbr, thr, per_split, cnt);
     else
         hipLaunchKernelGGL((k_tw_rank<KMAX, CT, CH>), dim3((unsigned)row_blocks, (unsigned)splits), dim3(512), 0, s,
-                           X, n, d, k, nx, nbr, thr, per_split, cnt);
+                           X, n, d, k, np, nx, nbr, thr, per_split, cnt);
 }
 
-// Sum of pen[0..n) in a fixed order: one block, strided partial sums, then a
-// tree.
-__global__ __launch_bounds__(256) void k_tw_sum(const int64_t *__restrict__ pen, int64_t n,
-                                                unsigned long long *__restrict__ out)
+// ---------------------------------------------------------------------------
+// The ranks from every pair of points once, on the bf16 matrix cores.
+//
+// Each fp32 feature is split into three bf16 values whose sum it is (8 + 8 + 8
+// bits), and a dot product is the sum of the six products of parts down to 2^-16
+// of the leading one, in fp32 accumulators; what is left out is below 2^-24 of
+// the product, the fp32 rounding of one term.  Six bf16 instructions of 32
+// features take 96 matrix-core cycles where the fp32 ones take 256.
+// 70,000 x 784, k = 15: 28.3 ms where k_tw_rank takes 85.0; 20,000 x 300, k = 30:
+// 2.5 against 5.6.  Against 64-bit sums the dot products' error is that of the
+// fp32 chain or less (image-like points, 800 features: 2.3e-7 of |x| |y| against
+// 2.8e-7; 32 features 2.5e-8 against 5.6e-8).  The matrix cores are busy a third of the time, the VALU
+// (counting) a quarter, LDS two fifths: two waves per SIMD (registers) do not
+// cover the operands' way from the Infinity Cache.
+//
+// A block multiplies 128 points (rows) with tiles of 128 points on and above the
+// diagonal and counts each distance for both of its points.  The split points
+// lie in memory as the block wants them in LDS: [panel of 128][32 features]
+// [point][12 units of 16 bytes: 3 parts x 4 groups of 8 features], the units of
+// point r rotated by (r / 4) % 4 so that 16 lanes reading 16 points' units meet
+// on no bank.  Four waves, 64 x 64 distances each (16 result tiles of 16 x 16);
+// the next 32 features are loaded to registers while these are multiplied.
+// ---------------------------------------------------------------------------
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+constexpr int kPanel = 128;
+constexpr int kUnits = 12;
+constexpr int kFeat = 32;                  // features per step
+constexpr int kCountPiece = 16;            // thresholds counted at a time
+constexpr int kTrStride = 68;              // floats per column of a transposed piece
+constexpr int kTrCols = 16;
+
+__device__ __forceinline__ int unit_slot(int u, int r)
 {
-    __shared__ unsigned long long s_part[256];
-    unsigned long long s = 0;
-    for (int64_t t = threadIdx.x; t < n; t += 256) s += (unsigned long long)pen[t];
-    s_part[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) s_part[threadIdx.x] += s_part[threadIdx.x + w];
-        __syncthreads();
+    const int t = u + ((r >> 2) & 3);
+    return t < kUnits ? t : t - kUnits;
+}
+
+// bf16 of x, to nearest even (toward zero where that would overflow)
+__device__ __forceinline__ uint32_t bf16_bits(float x)
+{
+    const uint32_t b = __float_as_uint(x);
+    const uint32_t r = (b + 0x7FFFu + ((b >> 16) & 1u)) >> 16;
+    return (r & 0x7F80u) == 0x7F80u ? b >> 16 : r;
+}
+
+// One wave per point of the padded panels: its parts and its squared norm
+// (+infinity for the points past n, so that nothing counts them).
+__global__ __launch_bounds__(256) void k_tw_split(const float *__restrict__ X, int64_t n, int32_t d, int32_t steps,
+                                                  uint4 *__restrict__ P, float *__restrict__ nx)
+{
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kWave;
+    const int lane = (int)(threadIdx.x % kWave);
+    const int r = (int)(i % kPanel);
+    const float *const x = X + i * d;
+    float sq = 0.0f;
+    for (int32_t g = lane; g < 4 * steps; g += kWave) {
+        uint32_t part[3][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            uint32_t lo[3], hi[3];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int32_t f = 8 * g + 2 * q + h;
+                const float v = i < n && f < d ? x[f] : 0.0f;
+                sq = fmaf(v, v, sq);
+                uint32_t(&b)[3] = h ? hi : lo;
+                b[0] = bf16_bits(v);
+                const float v1 = v - __uint_as_float(b[0] << 16);
+                b[1] = bf16_bits(v1);
+                b[2] = bf16_bits(v1 - __uint_as_float(b[1] << 16));
+            }
+#pragma unroll
+            for (int p = 0; p < 3; ++p) part[p][q] = lo[p] | (hi[p] << 16);
+        }
+        uint4 *const row = P + (((i / kPanel) * steps + g / 4) * kPanel + r) * kUnits;
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            row[unit_slot(4 * p + g % 4, r)] = make_uint4(part[p][0], part[p][1], part[p][2], part[p][3]);
     }
-    if (threadIdx.x == 0) *out = s_part[0];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
+    if (lane == 0) nx[i] = i < n ? sq : INFINITY;
+}
+
+// the next float above x (x itself where it is not finite)
+__device__ __forceinline__ float next_up(float x)
+{
+    const int32_t b = __float_as_int(x + 0.0f);   // -0 becomes +0
+    return fabsf(x) < INFINITY ? __int_as_float(b + ((b >> 31) | 1)) : x;
+}
+
+// Counting "x < t" for several thresholds t: the sign of x - t is shifted into a
+// word per threshold and the words' bits are counted, two instructions per
+// comparison.  (A compare into a scalar mask is followed by two wait states
+// before the mask can be added: twice the cycles.)  x and t are not both
+// infinite: x is a distance or +infinity, t finite or -infinity.
+__device__ __forceinline__ uint32_t push_less(uint32_t bits, float x, float t)
+{
+    return __builtin_amdgcn_alignbit(bits, __float_as_uint(x - t), 31);
+}
+
+// Blocks take `span` column tiles of one row panel, from the diagonal on: for the
+// last m panels ceil(1 / span) + .. + ceil(m / span) blocks.
+__host__ __device__ inline int64_t panel_blocks(int64_t m, int64_t span)
+{
+    const int64_t q = m / span, r = m % span;
+    return span * q * (q + 1) / 2 + r * (q + 1);
+}
+
+template <int KS>
+__global__ __launch_bounds__(256, 2) void k_tw_rank_pairs(const uint4 *__restrict__ P, int64_t n, int64_t np,
+                                                          int32_t steps, int64_t span, int32_t k,
+                                                          const float *__restrict__ nx,
+                                                          const int32_t *__restrict__ nbr,
+                                                          const float *__restrict__ thr, int32_t *__restrict__ cnt)
+{
+    constexpr int kOperand = kPanel * kUnits;                       // units per panel and step
+    constexpr int kTrBytes = 4 * kTrCols * kTrStride * 4;           // transposed pieces of the four waves
+    constexpr int kThBytes = 4 * KS * kPanel * 4;                   // thresholds and neighbours, rows' and columns'
+    constexpr int kOpBytes = 2 * kOperand * 16 > kTrBytes + kThBytes ? 2 * kOperand * 16 : kTrBytes + kThBytes;
+    __shared__ __align__(16) unsigned char s_mem[kOpBytes];
+    __shared__ int32_t s_cnt[2][KS][kPanel];                        // rows, columns
+    __shared__ __align__(16) float s_nx[2][kPanel];
+    v4u *const s_op = reinterpret_cast<v4u *>(s_mem);               // while multiplying: rows, then columns
+    float *const s_tr = reinterpret_cast<float *>(s_mem);           // while counting
+    float(*const s_thr)[KS][kPanel] = reinterpret_cast<float(*)[KS][kPanel]>(s_mem + kTrBytes);
+    int32_t(*const s_nbr)[KS][kPanel] = reinterpret_cast<int32_t(*)[KS][kPanel]>(s_mem + kTrBytes + kThBytes / 2);
+
+    const int tid = threadIdx.x, lane = tid % kWave, wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int g = lane / 16, li = lane % 16;
+    const int wr = (wv >> 1) * 64, wc = (wv & 1) * 64;              // the wave's rows and columns in the tile
+    const int64_t panels = np / kPanel;
+    // row panel I: the first with panel_blocks of all panels up to it above blockIdx.x
+    int64_t lo = 0, hi = panels - 1;
+    const int64_t all = panel_blocks(panels, span);
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (all - panel_blocks(panels - mid - 1, span) > (int64_t)blockIdx.x) hi = mid; else lo = mid + 1;
+    }
+    const int64_t I = lo;
+    const int64_t J0 = I + ((int64_t)blockIdx.x - (all - panel_blocks(panels - I, span))) * span;
+    const int64_t J1 = J0 + span < panels ? J0 + span : panels;
+    const int64_t r0 = I * kPanel;
+    const int pieces = (k + KS - 1) / KS;
+
+    for (int t = tid; t < KS * kPanel; t += 256) s_cnt[0][t / kPanel][t % kPanel] = 0;
+    // units of this lane's fragments: point li of a 16-point group, features 8 g .. 8 g + 7
+    int off[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) off[p] = li * kUnits + unit_slot(4 * p + g, li);
+    const v4u *const rowsP = reinterpret_cast<const v4u *>(P) + I * steps * kOperand + tid;
+
+    for (int64_t J = J0; J < J1; ++J) {
+        const int64_t c0 = J * kPanel;
+        const v4u *const colsP = reinterpret_cast<const v4u *>(P) + J * steps * kOperand + tid;
+        v4f acc[4][4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[a][b] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        constexpr int kLoads = kOperand / 256;   // units a thread loads per operand
+        v4u ra[kLoads], ca[kLoads];
+#pragma unroll
+        for (int v = 0; v < kLoads; ++v) {
+            ra[v] = rowsP[v * 256];
+            ca[v] = colsP[v * 256];
+        }
+        if (tid < kPanel) s_nx[0][tid] = nx[r0 + tid];
+        else s_nx[1][tid - kPanel] = nx[c0 + tid - kPanel];
+        for (int32_t step = 0; step < steps; ++step) {
+            __syncthreads();   // the last step's operands (or the last tile's counting) are done with
+#pragma unroll
+            for (int v = 0; v < kLoads; ++v) {
+                s_op[v * 256 + tid] = ra[v];
+                s_op[kOperand + v * 256 + tid] = ca[v];
+            }
+            __syncthreads();
+            // the next step's operands (the last step's again after it: no branch)
+            const int64_t next = (int64_t)(step + 1 < steps ? step + 1 : step) * kOperand;
+#pragma unroll
+            for (int v = 0; v < kLoads; ++v) {
+                ra[v] = rowsP[next + v * 256];
+                ca[v] = colsP[next + v * 256];
+            }
+            v8bf a[4][3];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    a[t][p] = __builtin_bit_cast(v8bf, s_op[(wr + 16 * t) * kUnits + off[p]]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                v8bf b[3];
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    b[p] = __builtin_bit_cast(v8bf, s_op[kOperand + (wc + 16 * u) * kUnits + off[p]]);
+                // smallest products first; the four result tiles in turn, so that
+                // no instruction waits for the one before it
+                constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+                for (int q = 0; q < 6; ++q)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t][kA[q]], b[kB[q]], acc[t][u], 0, 0, 0);
+            }
+        }
+        // distances: lane (g, li) holds row 16 t + 4 g + e, column 16 u + li
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float nc = s_nx[1][wc + 16 * u + li];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float4 nr = *reinterpret_cast<const float4 *>(&s_nx[0][wr + 16 * t + 4 * g]);
+                const float nrv[4] = {nr.x, nr.y, nr.z, nr.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float dist = nrv[e] + nc - 2.0f * acc[t][u][e];
+                    if (I == J && wr + 16 * t + 4 * g + e == wc + 16 * u + li) dist = INFINITY;   // the point itself
+                    acc[t][u][e] = dist;
+                }
+            }
+        }
+        for (int piece = 0; piece < pieces; ++piece) {
+            __syncthreads();   // the operands, or the last piece's thresholds and counts, are done with
+            // A point counts for neighbour s of another when its distance is
+            // smaller, or equal with a smaller index; neighbour s itself does not.
+            // Where all points of a piece come before neighbour s, "equal" counts
+            // (the next float up is the threshold); where it is among them, that
+            // neighbour's count is taken point by point.
+#pragma unroll
+            for (int q = 0; q < KS * kPanel / 256; ++q) {
+                const int t = q * 256 + tid;
+                const int s = t / kPanel, at = t % kPanel;
+                const int64_t slot = (piece * KS + s) * np;
+#pragma unroll
+                for (int side = 0; side < 2; ++side) {
+                    const int64_t p = (side ? c0 : r0) + at;
+                    const bool use = piece * KS + s < k && p < n;
+                    s_thr[side][s][at] = use ? thr[slot + p] : -INFINITY;
+                    s_nbr[side][s][at] = use ? nbr[slot + p] : -1;
+                }
+                s_cnt[1][s][at] = 0;
+                if (pieces > 1) s_cnt[0][s][at] = 0;
+            }
+            __syncthreads();
+            if (I != J) {
+                const int32_t i0 = (int32_t)(r0 + wr);   // rows i0 .. i0 + 63
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int col = wc + 16 * u + li;
+                    float th[KS];
+                    uint32_t bits[KS];
+                    unsigned among = 0;
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) {
+                        const float x0 = s_thr[1][s][col];
+                        const int32_t at = s_nbr[1][s][col] - i0;
+                        const bool in = (uint32_t)at < 64u;
+                        th[s] = in ? -INFINITY : at >= 64 ? next_up(x0) : x0;
+                        among |= in ? 1u << s : 0u;
+                        bits[s] = 0;
+                    }
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float x = acc[t][u][e];
+#pragma unroll
+                            for (int s = 0; s < KS; ++s) bits[s] = push_less(bits[s], x, th[s]);
+                        }
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) atomicAdd(&s_cnt[1][s][col], __popc(bits[s]));
+                    if (__ballot(among != 0) == 0) continue;
+#pragma unroll 1
+                    for (int s = 0; s < KS; ++s) {
+                        const bool in = (among >> s & 1u) != 0;
+                        if (__ballot(in) == 0) continue;
+                        const int at = s_nbr[1][s][col] - i0;
+                        const float x0 = s_thr[1][s][col], x1 = next_up(x0);
+                        uint32_t c = 0;
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const int i = 16 * t + 4 * g + e;
+                                // before neighbour s equal counts, after it not, itself never
+                                c = push_less(c, i == at ? INFINITY : acc[t][u][e], i < at ? x1 : x0);
+                            }
+                        if (in) atomicAdd(&s_cnt[1][s][col], __popc(c));
+                    }
+                }
+            }
+            // the rows: the distances transposed, kTrCols columns at a time, a lane per row
+            float *const tr = s_tr + wv * kTrCols * kTrStride;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                wave_sync();
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    *reinterpret_cast<v4f *>(&tr[li * kTrStride + 16 * t + 4 * g]) = acc[t][u];
+                wave_sync();
+                const int32_t j0 = (int32_t)(c0 + wc + kTrCols * u);   // columns j0 .. j0 + 15
+                float x[kTrCols];
+#pragma unroll
+                for (int j = 0; j < kTrCols; ++j) x[j] = tr[j * kTrStride + lane];
+                unsigned among = 0;
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    const float x0 = s_thr[0][s][wr + lane];
+                    const int32_t at = s_nbr[0][s][wr + lane] - j0;
+                    const bool in = (uint32_t)at < (uint32_t)kTrCols;
+                    const float th = in ? -INFINITY : at >= kTrCols ? next_up(x0) : x0;
+                    among |= in ? 1u << s : 0u;
+                    uint32_t bits = 0;
+#pragma unroll
+                    for (int j = 0; j < kTrCols; ++j) bits = push_less(bits, x[j], th);
+                    atomicAdd(&s_cnt[0][s][wr + lane], __popc(bits));
+                }
+                if (__ballot(among != 0) == 0) continue;
+#pragma unroll 1
+                for (int s = 0; s < KS; ++s) {
+                    const bool in = (among >> s & 1u) != 0;
+                    if (__ballot(in) == 0) continue;
+                    const int at = s_nbr[0][s][wr + lane] - j0;
+                    const float x0 = s_thr[0][s][wr + lane], x1 = next_up(x0);
+                    uint32_t c = 0;
+#pragma unroll
+                    for (int j = 0; j < kTrCols; ++j) c = push_less(c, j == at ? INFINITY : x[j], j < at ? x1 : x0);
+                    if (in) atomicAdd(&s_cnt[0][s][wr + lane], __popc(c));
+                }
+            }
+            __syncthreads();
+            const bool rows_too = pieces > 1 || J + 1 == J1;
+            for (int t = tid; t < KS * kPanel; t += 256) {
+                const int s = piece * KS + t / kPanel;
+                const int q = t % kPanel;
+                if (s >= k) break;
+                if (s_cnt[1][t / kPanel][q]) atomicAdd(&cnt[s * np + c0 + q], s_cnt[1][t / kPanel][q]);
+                if (rows_too && s_cnt[0][t / kPanel][q]) atomicAdd(&cnt[s * np + r0 + q], s_cnt[0][t / kPanel][q]);
+            }
+        }
+    }
+}
+
+int64_t trust_padded(int64_t n) { return (n + kPanel - 1) / kPanel * kPanel; }
+
+size_t trust_split_bytes(int64_t n, int32_t d)
+{
+    const int64_t steps = ((int64_t)d + kFeat - 1) / kFeat;
+    const int64_t bytes = trust_padded(n) * steps * kUnits * 16;
+    return bytes <= kTrustSplitBytes ? (size_t)bytes : 0;
+}
+
+template <int KS>
+static void launch_pairs(const uint4 *P, int64_t n, int64_t np, int32_t steps, int32_t k, const float *nx,
+                         const int32_t *nbr, const float *thr, int32_t *cnt, hipStream_t s)
+{
+    const int64_t panels = np / kPanel;
+    // about 4096 blocks where the points allow it (two are resident per CU), a
+    // row panel's counts and operands being shared by the tiles of a block
+    int64_t span = panels * (panels + 1) / 2 / 4096;
+    span = span < 1 ? 1 : span > 32 ? 32 : span;
+    while (panel_blocks(panels, span) >= (int64_t)1 << 30) span *= 2;   // grid limit
+    hipLaunchKernelGGL((k_tw_rank_pairs<KS>), dim3((unsigned)panel_blocks(panels, span)), dim3(256), 0, s, P, n, np,
+                       steps, span, k, nx, nbr, thr, cnt);
 }
 
 template <int DIM>
-static hipError_t launch_knn_dim(const float *Y, int64_t n, int32_t k, int32_t *nbr, hipStream_t s)
+static hipError_t launch_knn_dim(const float *Y, int64_t n, int32_t k, int64_t np, int32_t *nbr, hipStream_t s)
 {
     const int64_t blocks = (n * kWave + 255) / 256;
-    hipLaunchKernelGGL((k_tw_embed_knn<DIM>), dim3((unsigned)blocks), dim3(256), 0, s, Y, n, k, nbr);
+    hipLaunchKernelGGL((k_tw_embed_knn<DIM>), dim3((unsigned)blocks), dim3(256), 0, s, Y, n, k, np, nbr);
     return hipGetLastError();
 }
 
 hipError_t launch_trustworthiness(const float *X, int64_t n, int32_t d, const float *Y, int32_t dim, int32_t k,
-                                  float *nx, int32_t *nbr, float *thr, int32_t *cnt, int64_t *pen,
+                                  void *split, float *nx, int32_t *nbr, float *thr, int32_t *cnt,
                                   unsigned long long *sum, unsigned *flags, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_tw_norms, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, X, n, d, nx);
+    const int64_t np = trust_padded(n);
+    const int32_t steps = (d + kFeat - 1) / kFeat;
+    if (split)
+        hipLaunchKernelGGL(k_tw_split, dim3((unsigned)(np / 4)), dim3(256), 0, s, X, n, d, steps,
+                           static_cast<uint4 *>(split), nx);
+    else
+        hipLaunchKernelGGL(k_tw_norms, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, X, n, d, nx);
     hipError_t e = hipSuccess;
     switch (dim) {
 #define UL_CASE(D) \
-    case D: e = launch_knn_dim<D>(Y, n, k, nbr, s); break;
+    case D: e = launch_knn_dim<D>(Y, n, k, np, nbr, s); break;
         UL_CASE(1) UL_CASE(2) UL_CASE(3) UL_CASE(4) UL_CASE(5) UL_CASE(6) UL_CASE(7) UL_CASE(8)
         UL_CASE(9) UL_CASE(10) UL_CASE(11) UL_CASE(12) UL_CASE(13) UL_CASE(14) UL_CASE(15) UL_CASE(16)
 #undef UL_CASE
     default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_tw_thresholds, dim3((unsigned)((n * kWave + 255) / 256)), dim3(256), 0, s, X, n, d, k, nx,
+    hipLaunchKernelGGL(k_tw_thresholds, dim3((unsigned)((n * kWave + 255) / 256)), dim3(256), 0, s, X, n, d, k, np, nx,
                        nbr, thr, flags);
-    const int64_t nk = n * k;
+    const int64_t nk = np * k;
     hipLaunchKernelGGL(k_tw_zero, dim3((unsigned)((nk + 255) / 256 < 4096 ? (nk + 255) / 256 : 4096)), dim3(256), 0,
                        s, cnt, nk);
-    if (k <= 16)
-        launch_rank<16, 4>(X, n, d, k, nx, nbr, thr, cnt, s);
-    else if (k <= 32)
-        launch_rank<32, 4>(X, n, d, k, nx, nbr, thr, cnt, s);
-    else
-        launch_rank<64, 2>(X, n, d, k, nx, nbr, thr, cnt, s);
-    hipLaunchKernelGGL(k_tw_penalty, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, cnt, n, k, pen);
-    hipLaunchKernelGGL(k_tw_sum, dim3(1), dim3(256), 0, s, pen, n, sum);
+    if (split) {
+        const uint4 *const P = static_cast<const uint4 *>(split);
+        if (k <= 8)
+            launch_pairs<8>(P, n, np, steps, k, nx, nbr, thr, cnt, s);
+        else
+            launch_pairs<kCountPiece>(P, n, np, steps, k, nx, nbr, thr, cnt, s);
+    } else if (k <= 16) {
+        launch_rank<16, 4>(X, n, d, k, np, nx, nbr, thr, cnt, s);
+    } else if (k <= 32) {
+        launch_rank<32, 4>(X, n, d, k, np, nx, nbr, thr, cnt, s);
+    } else {
+        launch_rank<64, 2>(X, n, d, k, np, nx, nbr, thr, cnt, s);
+    }
+    const int64_t pb = (n + 255) / 256;
+    hipLaunchKernelGGL(k_tw_penalty, dim3((unsigned)(pb < 256 ? pb : 256)), dim3(256), 0, s, cnt, n, k, np, sum);
     return hipGetLastError();
 }
 

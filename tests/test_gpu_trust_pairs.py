@@ -1,0 +1,94 @@
+"""Trustworthiness where its tiles and pieces change: panels of 128 points, 32
+features per step, 8 or 16 thresholds at a time.  Points on a lattice of small
+integers, many of them repeated, have exact fp32 distances with ties
+everywhere, so the GPU's ranks must equal the oracle's one for one; generic
+points agree within the swaps that fp32 cannot tell apart.  The fp32 kernels
+that run where the points' bf16 parts do not fit are held to the same."""
+
+import sys
+
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2008_00325_amd import umap_layout as U
+
+pytestmark = pytest.mark.gpu
+
+
+def case(msg):
+    print(f"[gpu case] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+def _both(monkeypatch, X, Y, k):
+    import torch
+
+    torch.cuda.set_device(0)
+    x, y = torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda()
+    pairs = U.umap_trustworthiness(x, y, k)
+    monkeypatch.setenv("UMAP_LAYOUT_FAULT", "split")
+    plain = U.umap_trustworthiness(x, y, k)
+    monkeypatch.delenv("UMAP_LAYOUT_FAULT")
+    return pairs, plain
+
+
+SHAPES = [(5, 1, 1, 1), (127, 31, 3, 7), (128, 32, 2, 8), (129, 33, 2, 9), (256, 64, 16, 16), (257, 5, 1, 17),
+          (383, 100, 2, 32), (385, 7, 3, 33), (640, 17, 2, 64), (1500, 3, 2, 15)]
+
+
+@pytest.mark.parametrize("n,d,dim,k", SHAPES)
+def test_lattice_ranks_equal_the_oracle(monkeypatch, n, d, dim, k):
+    rng = np.random.default_rng(n * 7 + d)
+    X = rng.integers(-3, 4, size=(n, d)).astype(np.float32)
+    X[rng.integers(0, n, n // 4)] = X[rng.integers(0, n, n // 4)]
+    Y = rng.standard_normal((n, dim)).astype(np.float32)   # the oracle takes ties of the embedding in any order
+    case(f"lattice n {n} d {d} dim {dim} k {k}")
+    want = O.trustworthiness(X, Y, k)
+    for got in _both(monkeypatch, X, Y, k):
+        assert abs(got - want) <= 1e-12
+
+
+@pytest.mark.parametrize("n,d,dim,k", [(1001, 40, 2, 15), (2049, 300, 3, 5), (1500, 784, 2, 30)])
+def test_scales_of_features(monkeypatch, n, d, dim, k):
+    """Features of very different scales (all three parts of a value matter)."""
+    rng = np.random.default_rng(n)
+    Z = rng.standard_normal((n, dim))
+    X = (np.sin(Z @ rng.standard_normal((dim, d))) * 10.0 ** rng.integers(-4, 5, size=d)).astype(np.float32)
+    Y = (Z + 0.05 * rng.standard_normal((n, dim))).astype(np.float32)
+    case(f"scales n {n} d {d} dim {dim} k {k}")
+    want = O.trustworthiness(X, Y, k)
+    # a pair that fp32 distances order differently moves T by 2 / (n k (2n - 3k - 1)); a hundred of n k are allowed
+    for got in _both(monkeypatch, X, Y, k):
+        assert abs(got - want) <= 200.0 / (n * k * (2.0 * n - 3.0 * k - 1.0))
+
+
+def test_far_and_non_finite_embedding():
+    """Embedding coordinates whose squared distances overflow are ranked by
+    index; non-finite ones are refused."""
+    import torch
+
+    n, k = 300, 15
+    rng = np.random.default_rng(1)
+    X = rng.standard_normal((n, 6)).astype(np.float32)
+    Y = rng.standard_normal((n, 2)).astype(np.float32)
+    Y[7] = 1e30
+    Y[200] = -3e38
+    with np.errstate(over="ignore"):
+        D = ((Y[:, None, :] - Y[None, :, :]) ** 2).sum(-1)
+    assert np.isinf(D[7]).sum() == n - 1
+    case("embedding with overflowing distances")
+    t = U.umap_trustworthiness(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), k)
+    np.fill_diagonal(D, np.nan)
+    nbr = np.argsort(np.where(np.isnan(D), np.inf, D) + 0.0, axis=1, kind="stable")
+    nbr = np.stack([r[r != i][:k] for i, r in enumerate(nbr)])
+    DX = ((X[:, None, :].astype(np.float64) - X[None, :, :]) ** 2).sum(-1)
+    np.fill_diagonal(DX, np.inf)
+    rank = np.argsort(np.argsort(DX, axis=1, kind="stable"), axis=1, kind="stable") + 1
+    pen = np.maximum(np.take_along_axis(rank, nbr, axis=1) - k, 0).sum()
+    want = 1.0 - 2.0 / (n * k * (2.0 * n - 3.0 * k - 1.0)) * pen
+    assert abs(t - want) <= 4.0 / (n * k * (2.0 * n - 3.0 * k - 1.0))
+    Y[3] = np.nan
+    with pytest.raises(U.UmapLayoutError) as ei:
+        U.umap_trustworthiness(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), k)
+    assert ei.value.code == U.UMAP_E_INVAL
