@@ -774,7 +774,11 @@ static void launch_pairs(const uint4 *P, int64_t n, int64_t np, int32_t steps, i
     // about 4096 blocks where the points allow it (two are resident per CU), a
     // row panel's counts and operands being shared by the tiles of a block
     int64_t span = panels * (panels + 1) / 2 / 4096;
-    span = span < 1 ? 1 : span > 32 ? 32 : span;
+    // ... but runs of at most 4 tiles from 256 panels on, so that the last blocks
+    // do not run alone for long (runs of up to 32 / of 4: 50,000 x 100 8.14 / 7.78
+    // ms per call, 70,000 x 784 32.5 / 29.1; taking 8 x 8 panels and runs per XCD
+    // besides: 7.46 and 29.6, 40,000 x 300 10.2 / 10.4)
+    span = span < 1 ? 1 : panels >= 256 ? (span > 4 ? 4 : span) : span;
     while (panel_blocks(panels, span) >= (int64_t)1 << 30) span *= 2;   // grid limit
     hipLaunchKernelGGL((k_tw_rank_pairs<KS>), dim3((unsigned)panel_blocks(panels, span)), dim3(256), 0, s, P, n, np,
                        steps, span, k, nx, nbr, thr, cnt);

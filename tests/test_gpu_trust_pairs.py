@@ -49,6 +49,20 @@ def test_lattice_ranks_equal_the_oracle(monkeypatch, n, d, dim, k):
         assert abs(got - want) <= 1e-12
 
 
+@pytest.mark.parametrize("n,d,k", [(32640, 3, 5), (32641, 7, 17), (33001, 96, 5)])
+def test_long_rows_of_tiles_equal_the_fp32_kernels(monkeypatch, n, d, k):
+    """Both sides of the size where the runs of tiles get shorter (255, 256 and 258
+    panels): both kernels' distances are exact on a lattice, so that the ranks are the
+    same."""
+    rng = np.random.default_rng(n + d)
+    X = rng.integers(-3, 4, size=(n, d)).astype(np.float32)
+    X[rng.integers(0, n, n // 4)] = X[rng.integers(0, n, n // 4)]
+    Y = rng.standard_normal((n, 2)).astype(np.float32)
+    case(f"runs n {n} d {d} k {k}")
+    pairs, plain = _both(monkeypatch, X, Y, k)
+    assert abs(pairs - plain) <= 1e-12
+
+
 @pytest.mark.parametrize("n,d,dim,k", [(1001, 40, 2, 15), (2049, 300, 3, 5), (1500, 784, 2, 30)])
 def test_scales_of_features(monkeypatch, n, d, dim, k):
     """Features of very different scales (all three parts of a value matter)."""
