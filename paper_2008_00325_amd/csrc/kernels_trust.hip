@@ -21,6 +21,7 @@
 //     matrix instructions on X itself; only where the parts would not fit.)
 //  5. k_tw_penalty: the penalties' sum.
 #include "internal.hpp"
+#include "launch_sizes.hpp"
 
 namespace ul {
 
@@ -514,16 +515,8 @@ __device__ __forceinline__ uint32_t push_less(uint32_t bits, float x, float t)
     return __builtin_amdgcn_alignbit(bits, __float_as_uint(x - t), 31);
 }
 
-// Blocks take `span` column tiles of one row panel, from the diagonal on: for the
-// last m panels ceil(1 / span) + .. + ceil(m / span) blocks.
-__host__ __device__ inline int64_t panel_blocks(int64_t m, int64_t span)
-{
-    const int64_t q = m / span, r = m % span;
-    return span * q * (q + 1) / 2 + r * (q + 1);
-}
-
 template <int KS>
-__global__ __launch_bounds__(256, 2) void k_tw_rank_pairs(const uint4 *__restrict__ P, int64_t n, int64_t np,
+__global__ __launch_bounds__(kPairThreads, 2) void k_tw_rank_pairs(const uint4 *__restrict__ P, int64_t n, int64_t np,
                                                           int32_t steps, int64_t span, int32_t k,
                                                           const float *__restrict__ nx,
                                                           const int32_t *__restrict__ nbr,
@@ -771,16 +764,8 @@ static void launch_pairs(const uint4 *P, int64_t n, int64_t np, int32_t steps, i
                          const int32_t *nbr, const float *thr, int32_t *cnt, hipStream_t s)
 {
     const int64_t panels = np / kPanel;
-    // about 4096 blocks where the points allow it (two are resident per CU), a
-    // row panel's counts and operands being shared by the tiles of a block
-    int64_t span = panels * (panels + 1) / 2 / 4096;
-    // ... but runs of at most 4 tiles from 256 panels on, so that the last blocks
-    // do not run alone for long (runs of up to 32 / of 4: 50,000 x 100 8.14 / 7.78
-    // ms per call, 70,000 x 784 32.5 / 29.1; taking 8 x 8 panels and runs per XCD
-    // besides: 7.46 and 29.6, 40,000 x 300 10.2 / 10.4)
-    span = span < 1 ? 1 : panels >= 256 ? (span > 4 ? 4 : span) : span;
-    while (panel_blocks(panels, span) >= (int64_t)1 << 30) span *= 2;   // grid limit
-    hipLaunchKernelGGL((k_tw_rank_pairs<KS>), dim3((unsigned)panel_blocks(panels, span)), dim3(256), 0, s, P, n, np,
+    const int64_t span = panel_span(panels);
+    hipLaunchKernelGGL((k_tw_rank_pairs<KS>), dim3((unsigned)panel_blocks(panels, span)), dim3(kPairThreads), 0, s, P, n, np,
                        steps, span, k, nx, nbr, thr, cnt);
 }
 

@@ -1,0 +1,38 @@
+// launch_sizes.hpp -- how many workgroups a call takes, as plain functions of its
+// sizes (no HIP types: they are also compiled and checked on the host alone).
+#pragma once
+
+#include <stdint.h>
+
+namespace ul {
+
+// A launch's work-items per grid dimension must stay below 2^32.
+constexpr int64_t kGridItems = (int64_t)1 << 32;
+
+// ---- ranks of the trustworthiness: blocks of 256 threads over pairs of panels ----
+constexpr int64_t kPairThreads = 256;
+
+// Blocks take `span` column tiles of one row panel, from the diagonal on: for the
+// last m panels ceil(1 / span) + .. + ceil(m / span) blocks.
+constexpr int64_t panel_blocks(int64_t m, int64_t span)
+{
+    const int64_t q = m / span, r = m % span;
+    return span * q * (q + 1) / 2 + r * (q + 1);
+}
+
+// Column tiles per block: about 4096 blocks where the points allow it (two are
+// resident per CU), a row panel's counts and operands being shared by the tiles of
+// a block; but runs of at most 4 tiles from 256 panels on, so that the last blocks
+// do not run alone for long (runs of up to 32 / of 4: 50,000 x 100 8.14 / 7.78
+// ms per call, 70,000 x 784 32.5 / 29.1; taking 8 x 8 panels and runs per XCD
+// besides: 7.46 and 29.6, 40,000 x 300 10.2 / 10.4).  Longer again where that
+// many blocks would not fit one launch (from 1,482,625 points on).
+constexpr int64_t panel_span(int64_t panels)
+{
+    int64_t span = panels * (panels + 1) / 2 / 4096;
+    span = span < 1 ? 1 : panels >= 256 ? (span > 4 ? 4 : span) : span;
+    while (span < panels && panel_blocks(panels, span) * kPairThreads >= kGridItems) span *= 2;
+    return span;
+}
+
+}  // namespace ul

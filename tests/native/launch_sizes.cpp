@@ -1,0 +1,21 @@
+// Prints launch sizes of csrc/launch_sizes.hpp for the numbers on stdin, one line per line read.
+#include <inttypes.h>
+#include <stdio.h>
+#include <string.h>
+
+#include "launch_sizes.hpp"
+
+int main()
+{
+    char what[16];
+    int64_t x;
+    while (scanf("%15s %" SCNd64, what, &x) == 2) {
+        if (!strcmp(what, "pairs")) {   // panels -> column tiles per block, blocks, threads per block
+            const int64_t span = ul::panel_span(x);
+            printf("%" PRId64 " %" PRId64 " %" PRId64 "\n", span, ul::panel_blocks(x, span), ul::kPairThreads);
+        } else {
+            return 1;
+        }
+    }
+    return 0;
+}

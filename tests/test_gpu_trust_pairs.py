@@ -63,6 +63,18 @@ def test_long_rows_of_tiles_equal_the_fp32_kernels(monkeypatch, n, d, k):
     assert abs(pairs - plain) <= 1e-12
 
 
+def test_more_blocks_than_one_launch_holds(monkeypatch):
+    """11,584 panels: runs of four tiles would take more than 2^24 blocks of 256
+    threads, the most that a launch holds, so the runs are longer."""
+    n = 11_584 * 128 - 5
+    rng = np.random.default_rng(8)
+    X = rng.integers(-40, 41, size=(n, 3)).astype(np.float32)
+    Y = np.concatenate([X[:, :1] + rng.standard_normal((n, 1)), rng.standard_normal((n, 1))], axis=1).astype(np.float32)
+    case(f"grid limit n {n}")
+    pairs, plain = _both(monkeypatch, X, Y, 2)
+    assert 0.0 < pairs < 1.0 and abs(pairs - plain) <= 1e-12
+
+
 @pytest.mark.parametrize("n,d,dim,k", [(1001, 40, 2, 15), (2049, 300, 3, 5), (1500, 784, 2, 30)])
 def test_scales_of_features(monkeypatch, n, d, dim, k):
     """Features of very different scales (all three parts of a value matter)."""

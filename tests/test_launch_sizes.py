@@ -1,0 +1,40 @@
+"""Launch sizes at the limits of what the calls accept, on the host: a launch has
+fewer than 2^32 work-items per grid dimension and its blocks cover the work."""
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+GRID_ITEMS = 2**32
+
+
+@pytest.fixture(scope="module")
+def sizes(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    exe = str(tmp_path_factory.mktemp("sizes") / "launch_sizes")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror",
+                    "-I", os.path.join(ROOT, "paper_2008_00325_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "native", "launch_sizes.cpp"), "-o", exe], check=True, timeout=120)
+
+    def ask(lines):
+        r = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0
+        return [tuple(int(x) for x in line.split()) for line in r.stdout.splitlines()]
+
+    return ask
+
+
+def test_pair_ranks_fit_a_launch(sizes):
+    # 11,583 / 11,584 panels: 2^24 blocks of four tiles; the last: more than the points that the embedding's
+    # neighbours are found of (a wavefront per point)
+    panels = [1, 2, 255, 256, 547, 11_583, 11_584, 20_000, 524_288]
+    got = sizes([f"pairs {m}" for m in panels])
+    for m, (span, blocks, threads) in zip(panels, got):
+        assert span >= 1 and blocks * threads < GRID_ITEMS
+        if m <= 20_000:
+            assert blocks == sum(-(-q // span) for q in range(1, m + 1))
+    assert [s for s, _, _ in got][4:7] == [4, 4, 8]
