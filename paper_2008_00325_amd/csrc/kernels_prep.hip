@@ -257,7 +257,8 @@ __global__ __launch_bounds__(kTileThreads) void k_bucket_rows(const int2 *__rest
     __shared__ int32_t s_wave[kTileThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const float thresh = keep_threshold(S, n_epochs);
-    const int32_t e0 = first[blockIdx.x * kSubs], e1 = first[(blockIdx.x + 1) * kSubs];
+    // unsigned: a step beyond the last entry may pass 2^31
+    const uint32_t e0 = first[blockIdx.x * kSubs], e1 = first[(blockIdx.x + 1) * kSubs];
     const int64_t row0 = (int64_t)blockIdx.x << lg;
     const int32_t rows = (int32_t)(n - row0 < ((int64_t)1 << lg) ? n - row0 : (int64_t)1 << lg);
     int32_t done = 0;   // kept entries of the rows before
@@ -265,12 +266,12 @@ __global__ __launch_bounds__(kTileThreads) void k_bucket_rows(const int2 *__rest
         const int32_t m = rows - a < kBucketRows ? rows - a : kBucketRows;
         for (int32_t t = tid; t < m; t += kTileThreads) s_n[t] = 0;
         __syncthreads();
-        for (int32_t c0 = e0; c0 < e1; c0 += kAhead * kTileThreads) {
+        for (uint32_t c0 = e0; c0 < e1; c0 += kAhead * kTileThreads) {
             uint32_t q[kAhead];
             float v[kAhead];
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
-                const int32_t e = c0 + u * kTileThreads + tid;
+                const uint32_t e = c0 + u * kTileThreads + tid;
                 q[u] = 0xFFFFFFFFu;
                 if (e < e1) {
                     q[u] = (uint32_t)lrow[e] - (uint32_t)a;
@@ -308,12 +309,12 @@ __global__ __launch_bounds__(kTileThreads) void k_bucket_rows(const int2 *__rest
             done += total;
             __syncthreads();
         }
-        for (int32_t c0 = e0; c0 < e1; c0 += kAhead * kTileThreads) {
+        for (uint32_t c0 = e0; c0 < e1; c0 += kAhead * kTileThreads) {
             uint32_t q[kAhead];
             int2 p[kAhead];
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
-                const int32_t e = c0 + u * kTileThreads + tid;
+                const uint32_t e = c0 + u * kTileThreads + tid;
                 q[u] = 0xFFFFFFFFu;
                 if (e < e1) {
                     q[u] = (uint32_t)lrow[e] - (uint32_t)a;
@@ -618,12 +619,13 @@ __global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair,
     if (tid <= nr) s_start[tid] = rp32[r0 + tid];
     if (tid == 0) s_diff = 0;
     __syncthreads();
-    const int32_t e1 = s_start[nr];
+    // entry numbers are unsigned: steps beyond a row's or the last entry may pass 2^31
+    const uint32_t e1 = s_start[nr];
     bool bad = false;
     int diff = 0;   // entries above the diagonal minus entries below
     const int group = lane / kG, part = lane % kG;
-    for (int32_t c0 = s_start[0] + wv * 64; c0 < e1; c0 += 256) {
-        const int32_t e = c0 + lane;
+    for (uint32_t c0 = s_start[0] + wv * 64; c0 < e1; c0 += 256) {
+        const uint32_t e = c0 + lane;
         const bool in = e < e1;
         int2 p = make_int2(0, 0);
         int32_t i = 0;
@@ -632,13 +634,13 @@ __global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair,
             int lo = 0, hi = nr - 1;
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
-                if (s_start[mid] <= e) lo = mid; else hi = mid - 1;
+                if ((uint32_t)s_start[mid] <= e) lo = mid; else hi = mid - 1;
             }
             i = (int32_t)(r0 + lo);
         }
         bool open = in && p.x > i;   // still to be found
         diff += in ? (open ? 1 : -1) : 0;
-        int32_t at = 0, re = 0;
+        uint32_t at = 0, re = 0;
         if (open) {
             at = rp32[p.x];
             re = rp32[p.x + 1];
@@ -648,7 +650,7 @@ __global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair,
             if (m == 0) break;
             const int cnt = __popcll(m);
             const int mine = (int)lanes_below(m);   // place in the list
-            if (open) s_list[wv][mine] = make_int4(at, re, i, p.y);
+            if (open) s_list[wv][mine] = make_int4((int)at, (int)re, i, p.y);
             wave_sync();
             unsigned long long hit = 0;
             for (int s0 = 0; s0 < cnt; s0 += 4 * kAhead) {
@@ -660,7 +662,8 @@ __global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair,
                     const int s = s0 + 4 * u + group;
                     w[u] = s_list[wv][s < cnt ? s : 0];
                     q[u] = make_int2(-1, 0);
-                    if (s < cnt && w[u].x + part < w[u].y) q[u] = pair[w[u].x + part];
+                    const uint32_t x = (uint32_t)w[u].x + part;
+                    if (s < cnt && x < (uint32_t)w[u].y) q[u] = pair[x];
                 }
 #pragma unroll
                 for (int u = 0; u < kAhead; ++u) {
@@ -680,9 +683,9 @@ __global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair,
             wave_sync();   // the list is written again
         }
         if (open) {
-            int32_t lo = at, hi = re;
+            uint32_t lo = at, hi = re;
             while (lo < hi) {
-                const int32_t mid = (lo + hi) >> 1;
+                const uint32_t mid = (lo + hi) >> 1;
                 if (pair[mid].x < i) lo = mid + 1; else hi = mid;
             }
             if (lo >= re) bad = true;

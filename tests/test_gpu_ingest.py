@@ -147,3 +147,46 @@ def test_asymmetric_and_duplicate_entries():
     with pytest.raises(U.UmapLayoutError) as ei:
         U.umap_layout_create(n, 2, r[gone], c[gone], v[gone], A_DEF, B_DEF, 200, 5)
     assert ei.value.code == U.UMAP_E_ASYMMETRIC
+
+
+def test_entries_up_to_the_last_31_bit_number():
+    """2^31 - 2 entries, all kept: the passes over entries end within one step of
+    2^31, where 32-bit signed entry numbers would wrap.  A ring of 11.5M vertices
+    joined to 93 on each side."""
+    import ctypes
+
+    import torch
+
+    m = 93
+    n = (2**31 - 2) // (2 * m)
+    nnz = 2 * m * n
+    assert nnz == 2**31 - 2
+    if torch.cuda.mem_get_info()[0] < 130 * 2**30:
+        pytest.skip("needs 130 GiB of device memory")
+    case(f"ring of {n} vertices, {nnz} entries")
+    off = torch.cat([torch.arange(-m, 0), torch.arange(1, m + 1)]).to("cuda", torch.int32)
+    r, c = (torch.empty(n, 2 * m, dtype=torch.int32, device="cuda") for _ in range(2))
+    v = (1.0 - 0.005 * off.abs().float()).repeat(n)
+    r[:] = torch.arange(n, dtype=torch.int32, device="cuda")[:, None]
+    torch.add(r, off[None, :], out=c)
+    c[c < 0] += n
+    c[c >= n] -= n
+    h = U.umap_layout_create_device(n, 2, r, c, v, nnz, A_DEF, B_DEF, 2, 0)
+    del r, c, v
+    torch.cuda.empty_cache()
+    with h:
+        st = U.umap_layout_stats(h)
+        assert st["nnz_kept"] == nnz and st["max_degree"] == 2 * m
+        row_ptr, col = np.empty(n + 1, np.int64), np.empty(nnz, np.int32)
+        assert U.lib().umap_layout_get_graph(h.ptr, row_ptr.ctypes.data_as(ctypes.c_void_p),
+                                             col.ctypes.data_as(ctypes.c_void_p), None, None) == U.UMAP_OK
+    assert np.array_equal(row_ptr, 2 * m * np.arange(n + 1, dtype=np.int64))
+    col = col.reshape(n, 2 * m)
+    off = np.r_[np.arange(-m, 0), np.arange(1, m + 1)].astype(np.int32)
+    step = 1 << 20
+    for a in range(0, n, step):
+        print(f"[gpu case] rows from {a}", flush=True)
+        want = np.arange(a, min(n, a + step), dtype=np.int32)[:, None] + off[None, :]
+        if a == 0 or a + step >= n:
+            want = np.sort(want % n, axis=1)
+        assert np.array_equal(col[a:a + step], want)
