@@ -25,6 +25,7 @@
 // order: 836 -> 115 + 221 us, 470 -> 375 us.)  Steps 3 and 4 are bound by the
 // latency of a workgroup's chain of loads, step 2 by its streams.
 #include "internal.hpp"
+#include "launch_sizes.hpp"
 
 namespace ul {
 
@@ -366,7 +367,9 @@ __global__ __launch_bounds__(256) void k_row_sort(const int2 *__restrict__ src, 
     __shared__ int32_t s_start[kSortRows + 1], s_pad[kSortRows + 1];
     __shared__ unsigned s_flags, s_near;
     const int tid = threadIdx.x;
-    const int64_t r0 = (int64_t)blockIdx.x * kSortRows;
+    const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const int64_t r0 = block * kSortRows;
+    if (r0 >= n) return;   // the last row of a grid of two dimensions
     const int nr = (int)(n - r0 < kSortRows ? n - r0 : kSortRows);
     const int64_t b = r0 >> lg;
     const int32_t dst = kfirst[b];
@@ -399,7 +402,7 @@ __global__ __launch_bounds__(256) void k_row_sort(const int2 *__restrict__ src, 
         }
         if (tid <= nr) s_pad[tid] = x - ((len + 3) & ~3);
         const unsigned mx = wave_max((unsigned)len);
-        if (tid == 0) block_max[blockIdx.x] = (int32_t)mx;
+        if (tid == 0) block_max[block] = (int32_t)mx;
         if (len > kLongRow) long_rows[atomicAdd(&S->n_long, 1)] = (int32_t)(r0 + tid);
     }
     unsigned flags = 0, near = 0;
@@ -481,7 +484,7 @@ __global__ __launch_bounds__(256) void k_row_sort(const int2 *__restrict__ src, 
     if (tid == 0) {
         // (most blocks of a shuffled graph raise kWide: look before adding)
         if (s_flags && (s_flags & ~*(volatile unsigned *)&S->flags)) atomicOr(&S->flags, s_flags);
-        block_near[blockIdx.x] = (int32_t)s_near;
+        block_near[block] = (int32_t)s_near;
     }
 }
 
@@ -614,7 +617,9 @@ __global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair,
     __shared__ int4 s_list[4][64];   // (first entry, end of row, i, value bits)
     __shared__ int s_diff;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int64_t r0 = (int64_t)blockIdx.x * kSortRows;
+    const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const int64_t r0 = block * kSortRows;
+    if (r0 >= n) return;   // the last row of a grid of two dimensions
     const int nr = (int)(n - r0 < kSortRows ? n - r0 : kSortRows);
     if (tid <= nr) s_start[tid] = rp32[r0 + tid];
     if (tid == 0) s_diff = 0;
@@ -698,7 +703,7 @@ __global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair,
     if (diff) atomicAdd(&s_diff, diff);
     if (__ballot(bad) != 0 && lane == 0) atomicOr(&S->flags, (unsigned)kAsymmetric);
     __syncthreads();
-    if (tid == 0) block_diff[blockIdx.x] = s_diff;
+    if (tid == 0) block_diff[block] = s_diff;
 }
 
 // The blocks' largest rows and partial sums into the scalars (diff null:
@@ -764,7 +769,8 @@ hipError_t launch_prep(const PrepBuffers &B, hipStream_t s)
                        B.n_epochs, B.scalars, B.pair_rows, B.lstart, B.kept_n);
     hipLaunchKernelGGL((k_bucket_scan<false>), dim3(1), dim3(kTileThreads), 0, s, B.kept_n, nb, B.kfirst, nullptr);
     const SortedRows out{B.col, B.eps, B.pair, B.col16};
-    const dim3 rb((unsigned)row_blocks(B.n));
+    const Grid2 rg = grid2(row_blocks(B.n), 256);
+    const dim3 rb(rg.x, rg.y);
     hipLaunchKernelGGL(k_row_sort, rb, dim3(256), 0, s, B.pair_rows, B.first, B.kfirst, B.lstart, B.n, lg,
                        B.scalars, B.row_ptr, B.rp32, B.long_rows, B.block_near, B.block_max, out);
     const int64_t max_long = long_row_slots(B.nnz);

@@ -9,6 +9,18 @@ namespace ul {
 // A launch's work-items per grid dimension must stay below 2^32.
 constexpr int64_t kGridItems = (int64_t)1 << 32;
 
+// A grid of at least `blocks` blocks of `threads` threads: one dimension where that
+// many fit, else two (block blockIdx.y * x + blockIdx.x; those past the last have no work).
+struct Grid2 {
+    uint32_t x, y;
+};
+constexpr Grid2 grid2(int64_t blocks, int64_t threads)
+{
+    const int64_t most = (kGridItems - 1) / threads;
+    const int64_t y = (blocks + most - 1) / most;
+    return Grid2{(uint32_t)((blocks + y - 1) / y), (uint32_t)y};
+}
+
 // ---- ranks of the trustworthiness: blocks of 256 threads over pairs of panels ----
 constexpr int64_t kPairThreads = 256;
 

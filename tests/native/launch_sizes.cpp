@@ -13,6 +13,9 @@ int main()
         if (!strcmp(what, "pairs")) {   // panels -> column tiles per block, blocks, threads per block
             const int64_t span = ul::panel_span(x);
             printf("%" PRId64 " %" PRId64 " %" PRId64 "\n", span, ul::panel_blocks(x, span), ul::kPairThreads);
+        } else if (!strcmp(what, "grid")) {   // blocks of 256 threads -> the grid's dimensions
+            const ul::Grid2 g = ul::grid2(x, 256);
+            printf("%" PRIu32 " %" PRIu32 "\n", g.x, g.y);
         } else {
             return 1;
         }

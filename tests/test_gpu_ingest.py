@@ -190,3 +190,34 @@ def test_entries_up_to_the_last_31_bit_number():
         if a == 0 or a + step >= n:
             want = np.sort(want % n, axis=1)
         assert np.array_equal(col[a:a + step], want)
+
+
+@pytest.mark.parametrize("n", [2**29 + 5, 3 * 2**29 + 77])
+def test_more_rows_than_one_grid_dimension(n):
+    """Blocks of 32 rows that need a second grid dimension (from 2^29 rows on), and
+    bucket counters beyond 64 KB of LDS (from 2^30 rows on)."""
+    import torch
+
+    if torch.cuda.mem_get_info()[0] < 160 * 2**30:
+        pytest.skip("needs 160 GiB of device memory")
+    rng = np.random.default_rng(3)
+    ends = np.r_[np.arange(40), n // 2 + np.arange(40), n - 1 - np.arange(40), rng.integers(0, n, 1000)]
+    key = np.unique(np.sort(rng.permutation(np.r_[ends, ends]).reshape(-1, 2), axis=1).astype(np.int64) @ [n, 1])
+    lo, hi = key // n, key % n
+    lo, hi = lo[lo != hi].astype(np.int32), hi[lo != hi].astype(np.int32)
+    v = rng.uniform(0.6, 1.0, lo.size).astype(np.float32)
+    r, c, v = np.r_[lo, hi], np.r_[hi, lo], np.r_[v, v]
+    case(f"{n} rows")
+    with U.umap_layout_create_device(n, 1, *(torch.from_numpy(x).cuda() for x in (r, c, v)), r.size, A_DEF, B_DEF, 2,
+                                     1) as h:
+        row_ptr, col, eps = U.umap_layout_get_graph(h)
+        st = U.umap_layout_stats(h)
+    o = np.lexsort((c, r))
+    assert np.array_equal(col, c[o]) and np.array_equal(eps, v.max() / v[o])
+    rows, count = np.unique(r, return_counts=True)
+    assert st["max_degree"] == count.max() and st["nnz_kept"] == r.size
+    at, a = 0, 0
+    for b, m in zip(rows.tolist() + [n], count.tolist() + [0]):   # row_ptr is constant from one row's end to the next
+        assert (row_ptr[a:b + 1] == at).all(), (a, b)
+        at, a = at + m, b + 1
+    assert a == n + 1

@@ -38,3 +38,12 @@ def test_pair_ranks_fit_a_launch(sizes):
         if m <= 20_000:
             assert blocks == sum(-(-q // span) for q in range(1, m + 1))
     assert [s for s, _, _ in got][4:7] == [4, 4, 8]
+
+
+def test_row_blocks_fit_a_launch(sizes):
+    # blocks of 32 rows of up to 2^31 - 1 rows: beyond 2^29 rows one dimension does not hold them
+    rows = [1, 32, 33, 2**29 - 32, 2**29 - 31, 2**29, 2**30 + 77, 2**31 - 1]
+    for n, (x, y) in zip(rows, sizes([f"grid {-(-n // 32)}" for n in rows])):
+        assert x * 256 < GRID_ITEMS and y < 2**16
+        assert -(-n // 32) <= x * y < -(-n // 32) + y
+        assert (y == 1) == (n <= 2**29 - 32)
