@@ -335,11 +335,11 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         B.bipartite = table != nullptr;
         B.n_epochs = n_epochs;
         const int64_t nb = ul::bucket_count(n), nc = ul::bucket_counters(n), nrb = ul::row_blocks(n),
-                      n_long = ul::long_row_slots(nnz);
+                      n_long = ul::long_row_slots(nnz), n_sym = table ? 0 : ul::symmetry_slots(nnz);
         size_t sbytes = 2 * need<uint32_t>(nc) + need<int32_t>(ul::kSubs * nb + 1) + need<int32_t>(nb + 1) +
                         need<uint32_t>(nb) + 3 * need<int32_t>(nrb) +
                         2 * need<int2>(nnz) + need<uint16_t>(nnz) + need<int32_t>(n) + need<int32_t>(n + 1) +
-                        need<int32_t>(n_long) + need<ul::PrepScalars>(1);
+                        need<int32_t>(n_long) + need<int2>(n_sym) + need<ul::PrepScalars>(1);
         if (host_inputs) sbytes += 2 * need<int32_t>(nnz) + need<float>(nnz);
         Scratch scratch(sbytes, stream);
         Carver sc{scratch.base()};
@@ -354,6 +354,7 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         B.lstart = sc.take<int32_t>(n);
         B.rp32 = sc.take<int32_t>(n + 1);
         B.long_rows = sc.take<int32_t>(n_long);
+        B.sym_list = sc.take<int2>(n_sym);
         B.block_max = sc.take<int32_t>(nrb);
         B.block_near = sc.take<int32_t>(nrb);
         B.block_diff = sc.take<int32_t>(nrb);

@@ -26,6 +26,7 @@ struct PrepScalars {
     unsigned wmax_bits;   // bits of the largest kept candidate weight (> 0)
     int max_degree;
     int n_long;           // rows of the long-row list
+    int n_sym, unused;    // pieces of sym_list
     unsigned long long near;   // tails within kHalo of their row
     long long up_minus_low;    // entries above minus entries below the diagonal
 };
@@ -79,6 +80,7 @@ struct PrepBuffers {
     int32_t *lstart;      // n
     int32_t *rp32;        // n + 1, row_ptr in 32 bits
     int32_t *long_rows;   // long_row_slots(nnz)
+    int2 *sym_list;       // symmetry_slots(nnz): (block of rows, piece)
     int32_t *block_max;   // row_blocks(n), per-block parts of the scalars
     int32_t *block_near;  // row_blocks(n)
     int32_t *block_diff;  // row_blocks(n)
@@ -98,6 +100,7 @@ int64_t bucket_count(int64_t n);
 int64_t bucket_counters(int64_t n);
 int64_t row_blocks(int64_t n);
 int64_t long_row_slots(int64_t nnz);
+int64_t symmetry_slots(int64_t nnz);
 hipError_t launch_prep(const PrepBuffers &B, hipStream_t s);
 // Waves over rows [r0, r1) (0 <= r0 < r1); n_waves = ceil(units / cost) for
 // the units (edges + row_weight x rows) of the range.

@@ -338,6 +338,13 @@ constexpr int kSortThreads = 1024;
 constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kRowTile = 1024;   // entries of consecutive rows in LDS at a time (8 blocks per CU)
 
+// Entries that a block of k_symmetry takes at a time.
+constexpr int32_t kSymEntries = 4096;
+__host__ __device__ inline int32_t symmetry_pieces(int32_t entries)
+{
+    return entries > kSymEntries ? (int32_t)(((int64_t)entries + kSymEntries - 1) / kSymEntries) : 1;
+}
+
 // What k_row_sort and k_long_row_sort write, beside the row pointers.
 struct SortedRows {
     int32_t *col;
@@ -359,13 +366,14 @@ __global__ __launch_bounds__(256) void k_row_sort(const int2 *__restrict__ src, 
                                                   PrepScalars *S, int64_t *__restrict__ row_ptr,
                                                   int32_t *__restrict__ rp32, int32_t *__restrict__ long_rows,
                                                   int32_t *__restrict__ block_near, int32_t *__restrict__ block_max,
-                                                  SortedRows out)
+                                                  int2 *__restrict__ sym_list, SortedRows out)
 {
     __shared__ __align__(16) int32_t s_col[kRowTile + 4 * kSortRows];   // columns by padded row
     __shared__ int2 s_out[kRowTile];
     __shared__ uint8_t s_row[kRowTile];
     __shared__ int32_t s_start[kSortRows + 1], s_pad[kSortRows + 1];
     __shared__ unsigned s_flags, s_near;
+    __shared__ int32_t s_piece;
     const int tid = threadIdx.x;
     const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
     const int64_t r0 = block * kSortRows;
@@ -404,6 +412,13 @@ __global__ __launch_bounds__(256) void k_row_sort(const int2 *__restrict__ src, 
         const unsigned mx = wave_max((unsigned)len);
         if (tid == 0) block_max[block] = (int32_t)mx;
         if (len > kLongRow) long_rows[atomicAdd(&S->n_long, 1)] = (int32_t)(r0 + tid);
+    }
+    // the symmetry check's pieces of these entries but the first
+    const int32_t more = out.col16 ? symmetry_pieces(s_start[nr] - s_start[0]) - 1 : 0;
+    if (more > 0) {
+        if (tid == 0) s_piece = atomicAdd(&S->n_sym, more);
+        __syncthreads();
+        for (int32_t t = tid; t < more; t += 256) sym_list[s_piece + t] = make_int2((int)block, t + 1);
     }
     unsigned flags = 0, near = 0;
     for (int a = 0; a < nr;) {
@@ -603,9 +618,19 @@ __global__ __launch_bounds__(kSortThreads) void k_long_row_sort(const int2 *__re
 // the diagonal come first: 16 entries a round, three rounds, and what is not
 // decided then by a binary search.  The random lines of the rows bound it on a
 // shuffled graph: 2559 us on 20.8M edges with one binary search per lane and
-// entry, now 486 (26.7M edges in local order 693 -> 274).
-__global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair, const int32_t *__restrict__ rp32,
-                                                  int64_t n, PrepScalars *S, int32_t *__restrict__ block_diff)
+// entry, now 486 (26.7M edges in local order 693 -> 274).  Rows of more than
+// kLookupRow entries go to the binary search at once, which reads the columns
+// alone.
+// A block takes up to kSymEntries entries of its kSortRows rows; the further
+// pieces of long or dense rows are listed by k_row_sort and taken by blocks of
+// their own, so that no block has a long row to itself: 9M edges of a complete
+// graph of 3,000 vertices, where each block had 32 rows, 4444 us, now 500; 19.5M
+// edges with 1/x-distributed ends 29.5 ms, now 0.48.
+constexpr uint32_t kLookupRow = 96;
+__global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair, const int32_t *__restrict__ col,
+                                                  const int32_t *__restrict__ rp32, int64_t n, int64_t row_blocks,
+                                                  int32_t more_blocks, const int2 *__restrict__ sym_list,
+                                                  PrepScalars *S, int32_t *__restrict__ block_diff)
 {
     // After a duplicate the in-row sort leaves some slots unwritten; the
     // graph is rejected anyway, so skip the check rather than read them.
@@ -618,92 +643,109 @@ __global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair,
     __shared__ int s_diff;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    const int64_t r0 = block * kSortRows;
-    if (r0 >= n) return;   // the last row of a grid of two dimensions
-    const int nr = (int)(n - r0 < kSortRows ? n - r0 : kSortRows);
-    if (tid <= nr) s_start[tid] = rp32[r0 + tid];
+    if (block >= row_blocks + more_blocks) return;   // the last row of a grid of two dimensions
+    const bool first_piece = block < row_blocks;
+    // the first piece of the block's own rows, or the listed pieces in strides
+    const int64_t items = first_piece ? 1 : S->n_sym;
+    int64_t item = first_piece ? 0 : block - row_blocks;
+    if (item >= items) return;
     if (tid == 0) s_diff = 0;
-    __syncthreads();
-    // entry numbers are unsigned: steps beyond a row's or the last entry may pass 2^31
-    const uint32_t e1 = s_start[nr];
     bool bad = false;
     int diff = 0;   // entries above the diagonal minus entries below
     const int group = lane / kG, part = lane % kG;
-    for (uint32_t c0 = s_start[0] + wv * 64; c0 < e1; c0 += 256) {
-        const uint32_t e = c0 + lane;
-        const bool in = e < e1;
-        int2 p = make_int2(0, 0);
-        int32_t i = 0;
-        if (in) {
-            p = pair[e];
-            int lo = 0, hi = nr - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if ((uint32_t)s_start[mid] <= e) lo = mid; else hi = mid - 1;
-            }
-            i = (int32_t)(r0 + lo);
-        }
-        bool open = in && p.x > i;   // still to be found
-        diff += in ? (open ? 1 : -1) : 0;
-        uint32_t at = 0, re = 0;
-        if (open) {
-            at = rp32[p.x];
-            re = rp32[p.x + 1];
-        }
-        for (int round = 0; round < kRounds; ++round) {
-            const unsigned long long m = __ballot(open);
-            if (m == 0) break;
-            const int cnt = __popcll(m);
-            const int mine = (int)lanes_below(m);   // place in the list
-            if (open) s_list[wv][mine] = make_int4((int)at, (int)re, i, p.y);
-            wave_sync();
-            unsigned long long hit = 0;
-            for (int s0 = 0; s0 < cnt; s0 += 4 * kAhead) {
-                int4 w[kAhead];
-                int2 q[kAhead];
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    if (s0 + 4 * u >= cnt) break;
-                    const int s = s0 + 4 * u + group;
-                    w[u] = s_list[wv][s < cnt ? s : 0];
-                    q[u] = make_int2(-1, 0);
-                    const uint32_t x = (uint32_t)w[u].x + part;
-                    if (s < cnt && x < (uint32_t)w[u].y) q[u] = pair[x];
+    do {
+        const int2 p0 = first_piece ? make_int2((int)block, 0) : sym_list[item];
+        const int64_t r0 = (int64_t)p0.x * kSortRows;
+        const int nr = (int)(n - r0 < kSortRows ? n - r0 : kSortRows);
+        __syncthreads();   // the last piece's rows are done with
+        if (tid <= nr) s_start[tid] = rp32[r0 + tid];
+        __syncthreads();
+        // entry numbers are unsigned: steps beyond a row's or the last entry may pass 2^31
+        const uint32_t a0 = (uint32_t)s_start[0] + (uint32_t)p0.y * kSymEntries;
+        const uint32_t a1 = s_start[nr];
+        const uint32_t e1 = a1 - a0 > (uint32_t)kSymEntries ? a0 + kSymEntries : a1;
+        for (uint32_t c0 = a0 + wv * 64; c0 < e1; c0 += 256) {
+            const uint32_t e = c0 + lane;
+            const bool in = e < e1;
+            int2 p = make_int2(0, 0);
+            int32_t i = 0;
+            if (in) {
+                p = pair[e];
+                int lo = 0, hi = nr - 1;
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if ((uint32_t)s_start[mid] <= e) lo = mid; else hi = mid - 1;
                 }
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    if (s0 + 4 * u >= cnt) break;
-                    const unsigned long long h = __ballot(q[u].x == w[u].z && q[u].y == w[u].w);   // column -1 is none
-                    if ((mine >> 2) == (s0 >> 2) + u) hit = h;
-                }
+                i = (int32_t)(r0 + lo);
             }
+            bool open = in && p.x > i;   // still to be found
+            diff += in ? (open ? 1 : -1) : 0;
+            uint32_t at = 0, re = 0;
             if (open) {
-                at += kG;
-                if ((hit >> (kG * (mine & 3))) & ((1ull << kG) - 1ull)) open = false;
-                else if (at >= re) {
-                    open = false;
-                    bad = true;
+                at = rp32[p.x];
+                re = rp32[p.x + 1];
+            }
+            bool late = open && re - at > kLookupRow;   // for the binary search
+            open = open && !late;
+            for (int round = 0; round < kRounds; ++round) {
+                const unsigned long long m = __ballot(open);
+                if (m == 0) break;
+                const int cnt = __popcll(m);
+                const int mine = (int)lanes_below(m);   // place in the list
+                if (open) s_list[wv][mine] = make_int4((int)at, (int)re, i, p.y);
+                wave_sync();
+                unsigned long long hit = 0;
+                for (int s0 = 0; s0 < cnt; s0 += 4 * kAhead) {
+                    int4 w[kAhead];
+                    int2 q[kAhead];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        if (s0 + 4 * u >= cnt) break;
+                        const int s = s0 + 4 * u + group;
+                        w[u] = s_list[wv][s < cnt ? s : 0];
+                        q[u] = make_int2(-1, 0);
+                        const uint32_t x = (uint32_t)w[u].x + part;
+                        if (s < cnt && x < (uint32_t)w[u].y) q[u] = pair[x];
+                    }
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        if (s0 + 4 * u >= cnt) break;
+                        const unsigned long long h = __ballot(q[u].x == w[u].z && q[u].y == w[u].w);   // column -1 is none
+                        if ((mine >> 2) == (s0 >> 2) + u) hit = h;
+                    }
+                }
+                if (open) {
+                    at += kG;
+                    if ((hit >> (kG * (mine & 3))) & ((1ull << kG) - 1ull)) open = false;
+                    else if (at >= re) {
+                        open = false;
+                        bad = true;
+                    }
+                }
+                wave_sync();   // the list is written again
+            }
+            if (open || late) {
+                uint32_t lo = at, hi = re;
+                while (lo < hi) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if (col[mid] < i) lo = mid + 1; else hi = mid;
+                }
+                if (lo >= re) bad = true;
+                else {
+                    const int2 q = pair[lo];
+                    bad |= q.x != i || q.y != p.y;
                 }
             }
-            wave_sync();   // the list is written again
         }
-        if (open) {
-            uint32_t lo = at, hi = re;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (pair[mid].x < i) lo = mid + 1; else hi = mid;
-            }
-            if (lo >= re) bad = true;
-            else {
-                const int2 q = pair[lo];
-                bad |= q.x != i || q.y != p.y;
-            }
-        }
-    }
+        item += first_piece ? 1 : more_blocks;
+    } while (item < items);
     if (diff) atomicAdd(&s_diff, diff);
     if (__ballot(bad) != 0 && lane == 0) atomicOr(&S->flags, (unsigned)kAsymmetric);
     __syncthreads();
-    if (tid == 0) block_diff[block] = s_diff;
+    if (tid == 0) {
+        if (first_piece) block_diff[block] = s_diff;
+        else if (s_diff) atomicAdd(reinterpret_cast<unsigned long long *>(&S->up_minus_low), (unsigned long long)(long long)s_diff);
+    }
 }
 
 // The blocks' largest rows and partial sums into the scalars (diff null:
@@ -741,6 +783,7 @@ static int64_t grid_for(int64_t items)
 }
 
 int64_t long_row_slots(int64_t nnz) { return nnz / (kLongRow + 1); }
+int64_t symmetry_slots(int64_t nnz) { return nnz / kSymEntries; }
 
 hipError_t launch_prep(const PrepBuffers &B, hipStream_t s)
 {
@@ -772,7 +815,7 @@ hipError_t launch_prep(const PrepBuffers &B, hipStream_t s)
     const Grid2 rg = grid2(row_blocks(B.n), 256);
     const dim3 rb(rg.x, rg.y);
     hipLaunchKernelGGL(k_row_sort, rb, dim3(256), 0, s, B.pair_rows, B.first, B.kfirst, B.lstart, B.n, lg,
-                       B.scalars, B.row_ptr, B.rp32, B.long_rows, B.block_near, B.block_max, out);
+                       B.scalars, B.row_ptr, B.rp32, B.long_rows, B.block_near, B.block_max, B.sym_list, out);
     const int64_t max_long = long_row_slots(B.nnz);
     if (max_long > 0) {
         int32_t passes = 0;   // 4-bit digits of the largest column, rounded up to an even count
@@ -781,8 +824,12 @@ hipError_t launch_prep(const PrepBuffers &B, hipStream_t s)
         hipLaunchKernelGGL(k_long_row_sort, dim3((unsigned)(max_long < 512 ? max_long : 512)), dim3(kSortThreads), 0, s,
                            B.pair_rows, B.first, B.kfirst, B.lstart, B.n, lg, passes, B.long_rows, B.scalars, out);
     }
-    if (!B.bipartite)
-        hipLaunchKernelGGL(k_symmetry, rb, dim3(256), 0, s, B.pair, B.rp32, B.n, B.scalars, B.block_diff);
+    if (!B.bipartite) {
+        const int64_t more = symmetry_slots(B.nnz) < 1024 ? symmetry_slots(B.nnz) : 1024;
+        const Grid2 sg = grid2(row_blocks(B.n) + more, 256);
+        hipLaunchKernelGGL(k_symmetry, dim3(sg.x, sg.y), dim3(256), 0, s, B.pair, B.col, B.rp32, B.n, row_blocks(B.n),
+                           (int32_t)more, B.sym_list, B.scalars, B.block_diff);
+    }
     const int64_t g = (row_blocks(B.n) + 1023) / 1024;
     hipLaunchKernelGGL(k_prep_sums, dim3((unsigned)(g < 64 ? g : 64)), dim3(256), 0, s, B.block_max, B.block_near,
                        B.bipartite ? nullptr : B.block_diff, row_blocks(B.n), B.scalars);

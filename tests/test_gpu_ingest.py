@@ -221,3 +221,29 @@ def test_more_rows_than_one_grid_dimension(n):
         assert (row_ptr[a:b + 1] == at).all(), (a, b)
         at, a = at + m, b + 1
     assert a == n + 1
+
+
+@pytest.mark.parametrize("n,hub", [(300, 0), (9_001, 9_000)])
+def test_asymmetric_entries_in_every_piece(n, hub):
+    """Blocks of rows with more than 4,096 entries (a complete graph of 300, a hub
+    of 9,000) are checked in pieces: one entry changed or taken out anywhere in
+    them is found."""
+    if hub:
+        lo, hi = np.zeros(hub, np.int32), np.arange(1, hub + 1, dtype=np.int32)
+    else:
+        lo, hi = np.triu_indices(n, 1)
+    r, c = np.r_[lo, hi].astype(np.int32), np.r_[hi, lo].astype(np.int32)
+    v = np.random.default_rng(n).uniform(0.5, 1.0, lo.size).astype(np.float32)
+    v = np.r_[v, v]
+    with U.umap_layout_create(n, 2, r, c, v, A_DEF, B_DEF, 50, 5) as h:
+        _check(h, n, r, c, v, 50)
+    half = lo.size
+    for e in (0, half // 5, half // 2, half - 1, half, half + half // 3, 2 * half - 1):
+        case(f"n {n}, entry ({r[e]}, {c[e]})")
+        other = v.copy()
+        other[e] = np.nextafter(v[e], np.float32(1))
+        gone = np.delete(np.arange(r.size), e)
+        for rr, cc, vv in ((r, c, other), (r[gone], c[gone], v[gone])):
+            with pytest.raises(U.UmapLayoutError) as ei:
+                U.umap_layout_create(n, 2, rr, cc, vv, A_DEF, B_DEF, 50, 5)
+            assert ei.value.code == U.UMAP_E_ASYMMETRIC
