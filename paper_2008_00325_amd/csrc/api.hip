@@ -334,31 +334,32 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         B.n_cols = h->n_table;
         B.bipartite = table != nullptr;
         B.n_epochs = n_epochs;
-        const int64_t nb = ul::bucket_count(n), nc = ul::bucket_counters(n), nrb = ul::row_blocks(n),
+        const int64_t nb = ul::bucket_count(n, nnz), nc = ul::bucket_counters(n, nnz), nrb = ul::row_blocks(n),
                       n_long = ul::long_row_slots(nnz), n_sym = table ? 0 : ul::symmetry_slots(nnz);
-        size_t sbytes = 2 * need<uint32_t>(nc) + need<int32_t>(ul::kSubs * nb + 1) + need<int32_t>(nb + 1) +
+        size_t sbytes = 2 * need<uint32_t>(nc) + need<int32_t>(ul::kSubs * nb + 1) + 2 * need<int32_t>(nb + 1) +
                         need<uint32_t>(nb) + 3 * need<int32_t>(nrb) +
                         2 * need<int2>(nnz) + need<uint16_t>(nnz) + need<int32_t>(n) + need<int32_t>(n + 1) +
                         need<int32_t>(n_long) + need<int2>(n_sym) + need<ul::PrepScalars>(1);
         if (host_inputs) sbytes += 2 * need<int32_t>(nnz) + need<float>(nnz);
         Scratch scratch(sbytes, stream);
         Carver sc{scratch.base()};
-        B.bucket_n = sc.take<uint32_t>(nc);
+        B.bucket_n = sc.take<uint32_t>(nc);   // these three one after the other
+        B.scalars = sc.take<ul::PrepScalars>(1);
+        B.lstart = sc.take<int32_t>(n);
         B.cursor = sc.take<uint32_t>(nc);
         B.first = sc.take<int32_t>(ul::kSubs * nb + 1);
+        B.heavy_first = sc.take<int32_t>(nb + 1);
         B.kfirst = sc.take<int32_t>(nb + 1);
         B.kept_n = sc.take<uint32_t>(nb);
         B.pair = sc.take<int2>(nnz);
         B.pair_rows = sc.take<int2>(nnz);
         B.lrow = sc.take<uint16_t>(nnz);
-        B.lstart = sc.take<int32_t>(n);
         B.rp32 = sc.take<int32_t>(n + 1);
         B.long_rows = sc.take<int32_t>(n_long);
         B.sym_list = sc.take<int2>(n_sym);
         B.block_max = sc.take<int32_t>(nrb);
         B.block_near = sc.take<int32_t>(nrb);
         B.block_diff = sc.take<int32_t>(nrb);
-        B.scalars = sc.take<ul::PrepScalars>(1);
         if (host_inputs) {
             int32_t *dr = sc.take<int32_t>(nnz);
             int32_t *dc = sc.take<int32_t>(nnz);

@@ -26,7 +26,10 @@ struct PrepScalars {
     unsigned wmax_bits;   // bits of the largest kept candidate weight (> 0)
     int max_degree;
     int n_long;           // rows of the long-row list
-    int n_sym, unused;    // pieces of sym_list
+    int n_sym;            // pieces of sym_list
+    int n_heavy;          // chunks of buckets with more than
+    int heavy_above;      //   this many entries
+    int unused;
     unsigned long long near;   // tails within kHalo of their row
     long long up_minus_low;    // entries above minus entries below the diagonal
 };
@@ -68,23 +71,24 @@ struct PrepBuffers {
     int64_t n_cols;     // columns are in [0, n_cols); n unless bipartite
     bool bipartite;     // rows and columns are different vertex sets (no self loops, no symmetry)
     int32_t n_epochs;
-    // scratch (device); nb = bucket_count(n)
-    uint32_t *bucket_n;   // bucket_counters(n): candidates per bucket, a cache line apart
-    uint32_t *cursor;     // bucket_counters(n)
+    // scratch (device); nb = bucket_count(n, nnz); the first three one after the other
+    uint32_t *bucket_n;   // bucket_counters(n, nnz): candidates per bucket, a cache line apart
+    PrepScalars *scalars;
+    int32_t *lstart;      // n
+    uint32_t *cursor;     // bucket_counters(n, nnz)
     int32_t *first;       // kSubs nb + 1
+    int32_t *heavy_first; // nb + 1
     uint32_t *kept_n;     // nb
     int32_t *kfirst;      // nb + 1
     int2 *pair;           // nnz entries (col, value bits) by bucket, later in (row, col) order
     uint16_t *lrow;       // nnz, their rows in the bucket
     int2 *pair_rows;      // nnz, by row
-    int32_t *lstart;      // n
     int32_t *rp32;        // n + 1, row_ptr in 32 bits
     int32_t *long_rows;   // long_row_slots(nnz)
     int2 *sym_list;       // symmetry_slots(nnz): (block of rows, piece)
     int32_t *block_max;   // row_blocks(n), per-block parts of the scalars
     int32_t *block_near;  // row_blocks(n)
     int32_t *block_diff;  // row_blocks(n)
-    PrepScalars *scalars;
     // outputs (device)
     int64_t *row_ptr;   // n + 1
     int32_t *col;       // nnz (capacity)
@@ -96,8 +100,8 @@ struct PrepBuffers {
 // that the workgroups of one XCD (tiles are dealt round-robin) share counters
 // with each other only.
 constexpr int kSubs = 8;
-int64_t bucket_count(int64_t n);
-int64_t bucket_counters(int64_t n);
+int64_t bucket_count(int64_t n, int64_t nnz);
+int64_t bucket_counters(int64_t n, int64_t nnz);
 int64_t row_blocks(int64_t n);
 int64_t long_row_slots(int64_t nnz);
 int64_t symmetry_slots(int64_t nnz);

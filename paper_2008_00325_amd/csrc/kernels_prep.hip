@@ -9,7 +9,8 @@
 //   2. k_bucket_scatter: the candidates filed by bucket, a tile of 8K entries at
 //      a time, so that a bucket gets runs of a tile's entries
 //   3. k_bucket_rows: one workgroup per bucket drops what lies below
-//      w_max / n_epochs, counts its rows in LDS and files the rest by row
+//      w_max / n_epochs, counts its rows in LDS and files the rest by row; buckets
+//      of many entries (hubs) in chunks, by k_heavy_rows before and after it
 //   4. k_row_sort: 16 rows at a time sorted by column in LDS (rank sort; equal
 //      columns flag a duplicate); row_ptr, col, eps = w_max / val and the tails
 //      as 16-bit offsets written.  Rows of more than kLongRow entries by
@@ -88,10 +89,16 @@ __device__ __forceinline__ int32_t run_atomic_add(int32_t *ctr, int32_t key, boo
 
 // Buckets of consecutive rows: 2^lg rows each, at least kSortRows (the rows of a
 // k_row_sort block lie in one bucket) and at most 2^16 (an entry's row in its
-// bucket is a 16-bit number), about kBuckets of them where that allows.
+// bucket is a 16-bit number), about kBuckets of them where that allows.  2^8 rows
+// or more, unless there are then fewer buckets than workgroups fit the chip and they
+// get more than kBucketEntries entries each (a complete graph of 300 vertices: k_bucket_rows
+// 77 -> 12 us; 20,000 rows of 1,000: 467 -> 219; where there are more buckets, finer ones
+// only cost: 100,000 rows of 120 1048 -> 1105 us in all).
 constexpr int kSortRows = 32;
 constexpr int kBuckets = 1024;
-constexpr int kMinBucketLg = 8, kMaxBucketLg = 16;
+constexpr int kMinBucketLg = 5, kFewBucketLg = 8, kMaxBucketLg = 16;
+constexpr int64_t kBucketEntries = 16384;
+constexpr int kFewBuckets = 512;
 // counters of buckets lie a cache line apart: workgroups add to all of them
 constexpr int kPad = 32;
 constexpr int kTileThreads = 1024;
@@ -100,15 +107,29 @@ constexpr int kTile = kTileThreads * kTileItems;
 // rows of a bucket counted in LDS at a time
 constexpr int kBucketRows = 8192;
 
-int32_t bucket_lg(int64_t n)
+int32_t bucket_lg(int64_t n, int64_t nnz)
 {
-    int32_t lg = kMinBucketLg;
+    int32_t lg = kFewBucketLg;
     while (lg < kMaxBucketLg && (n >> lg) >= kBuckets) ++lg;
+    while (lg > kMinBucketLg && (n >> (lg - 1)) < kFewBuckets && (nnz << lg) > kBucketEntries * n) --lg;
     return lg;
 }
-int64_t bucket_count(int64_t n) { return (n + ((int64_t)1 << bucket_lg(n)) - 1) >> bucket_lg(n); }
-int64_t bucket_counters(int64_t n) { return kPad * kSubs * bucket_count(n); }
+int64_t bucket_count(int64_t n, int64_t nnz)
+{
+    const int32_t lg = bucket_lg(n, nnz);
+    return (n + ((int64_t)1 << lg) - 1) >> lg;
+}
+int64_t bucket_counters(int64_t n, int64_t nnz) { return kPad * kSubs * bucket_count(n, nnz); }
 int64_t row_blocks(int64_t n) { return (n + kSortRows - 1) / kSortRows; }
+
+// Buckets of many entries (those of hubs) are counted and filed in chunks by
+// workgroups of their own: a bucket of more than kHeavyEntries entries that also
+// has more than its part of the work were the chip to share all entries (two
+// workgroups per CU are resident).
+constexpr int64_t kHeavyEntries = 65536;
+constexpr uint32_t kHeavyChunk = 32768;
+constexpr int32_t kHeavyShare = 256;
+int64_t heavy_chunks(int64_t nnz) { return nnz > kHeavyEntries ? nnz / kHeavyChunk + kHeavyShare : 0; }
 // counter of part `sub` of bucket b
 __device__ __forceinline__ int64_t counter_at(int32_t sub, int32_t b, int32_t nb) { return ((int64_t)sub * nb + b) * kPad; }
 
@@ -160,20 +181,16 @@ __global__ __launch_bounds__(kTileThreads) void k_check(const int32_t *__restric
         if (s_n[b]) atomicAdd(&bucket_n[counter_at(blockIdx.x % kSubs, b, nb)], (uint32_t)s_n[b]);
 }
 
-// first[t] = n[0] + ... + n[t - 1] for t <= count (one block, loops over chunks).
-// COUNTERS: n[b kSubs + sub] is the counter of part sub of bucket b, and its
-// cursor starts at first[t]; else n[t] = in[t].
-template <bool COUNTERS>
-__global__ __launch_bounds__(kTileThreads) void k_bucket_scan(const uint32_t *__restrict__ in, int32_t count,
-                                                              int32_t *__restrict__ first, uint32_t *__restrict__ cursor)
+// Exclusive scan of get(0) .. get(count - 1) by one workgroup: put(t, the sum
+// before t) for t < count; returns the total.  s_wave: kTileThreads / 64 words.
+template <typename Get, typename Put>
+__device__ __forceinline__ int32_t scan_loop(int32_t count, int32_t *s_wave, Get get, Put put)
 {
-    __shared__ int32_t s_wave[kTileThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     int32_t carry = 0;
     for (int32_t base = 0; base < count; base += kTileThreads) {
         const int32_t t = base + tid;
-        const int64_t at = COUNTERS ? counter_at(t % kSubs, t / kSubs, count / kSubs) : t;
-        const int32_t v = t < count ? (int32_t)in[at] : 0;
+        const int32_t v = t < count ? get(t) : 0;
         int32_t x = v;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -188,14 +205,66 @@ __global__ __launch_bounds__(kTileThreads) void k_bucket_scan(const uint32_t *__
             before += k < wv ? s_wave[k] : 0;
             total += s_wave[k];
         }
-        if (t < count) {
-            first[t] = carry + before + x - v;
-            if (COUNTERS) cursor[at] = (uint32_t)(carry + before + x - v);
-        }
+        if (t < count) put(t, carry + before + x - v);
         carry += total;
         __syncthreads();
     }
-    if (tid == 0) first[count] = carry;
+    return carry;
+}
+
+// The candidates' counters (bucket b, part sub: b kSubs + sub in this order) ->
+// first[t], the entries before each, and the cursors that start there; then the
+// chunks of the heavy buckets: heavy_first[b] = chunks of the buckets before b.
+__global__ __launch_bounds__(kTileThreads) void k_bucket_starts(const uint32_t *__restrict__ in, int32_t nb,
+                                                                int32_t *__restrict__ first,
+                                                                uint32_t *__restrict__ cursor,
+                                                                int32_t *__restrict__ heavy_first, PrepScalars *S)
+{
+    __shared__ int32_t s_wave[kTileThreads / 64];
+    __shared__ int32_t s_large;
+    const int32_t count = kSubs * nb;
+    if (threadIdx.x == 0) s_large = 0;
+    __syncthreads();
+    const int32_t total = scan_loop(
+        count, s_wave,
+        [&](int32_t t) {
+            const int32_t v = (int32_t)in[counter_at(t % kSubs, t / kSubs, nb)];
+            if (v > kHeavyEntries / kSubs) s_large = 1;   // its bucket may be heavy
+            return v;
+        },
+        [&](int32_t t, int32_t before) {
+            first[t] = before;
+            cursor[counter_at(t % kSubs, t / kSubs, nb)] = (uint32_t)before;
+        });
+    if (threadIdx.x == 0) first[count] = total;
+    __syncthreads();   // s_large, first
+    int32_t chunks = 0;
+    int32_t above = INT32_MAX;   // no bucket is heavy
+    if (s_large) {
+        above = max((int32_t)kHeavyEntries, total / kHeavyShare);
+        chunks = scan_loop(
+            nb, s_wave,
+            [&](int32_t b) {
+                const int32_t m = first[(b + 1) * kSubs] - first[b * kSubs];
+                return m > above ? (int32_t)(((uint32_t)m + kHeavyChunk - 1) / kHeavyChunk) : 0;
+            },
+            [&](int32_t b, int32_t before) { heavy_first[b] = before; });
+    }
+    if (threadIdx.x == 0) {
+        heavy_first[nb] = chunks;
+        S->n_heavy = chunks;
+        S->heavy_above = above;
+    }
+}
+
+// kfirst[b] = kept entries of the buckets before b
+__global__ __launch_bounds__(kTileThreads) void k_kept_starts(const uint32_t *__restrict__ kept_n, int32_t nb,
+                                                              int32_t *__restrict__ kfirst)
+{
+    __shared__ int32_t s_wave[kTileThreads / 64];
+    const int32_t total = scan_loop(nb, s_wave, [&](int32_t b) { return (int32_t)kept_n[b]; },
+                                    [&](int32_t b, int32_t before) { kfirst[b] = before; });
+    if (threadIdx.x == 0) kfirst[nb] = total;
 }
 
 // A tile of entries filed by bucket: ranks in LDS counters, one reservation per
@@ -242,93 +311,148 @@ __global__ __launch_bounds__(kTileThreads) void k_bucket_scatter(const int32_t *
     }
 }
 
+// The entries [c0, c1) of a bucket whose rows lie in [a, a + m) of it and which are
+// kept, counted per row (s_n[row - a]).  Entry numbers are unsigned: a step beyond
+// the last entry may pass 2^31.
+constexpr int kEntriesAhead = 8;   // loads of a thread in flight
+__device__ __forceinline__ void count_entries(const int2 *__restrict__ pair, const uint16_t *__restrict__ lrow,
+                                              uint32_t c0, uint32_t c1, int32_t a, int32_t m, float thresh,
+                                              int32_t *s_n)
+{
+    for (; c0 < c1; c0 += kEntriesAhead * kTileThreads) {
+        uint32_t q[kEntriesAhead];
+        float v[kEntriesAhead];
+#pragma unroll
+        for (int u = 0; u < kEntriesAhead; ++u) {
+            const uint32_t e = c0 + u * kTileThreads + threadIdx.x;
+            q[u] = 0xFFFFFFFFu;
+            if (e < c1) {
+                q[u] = (uint32_t)lrow[e] - (uint32_t)a;
+                v[u] = __int_as_float(pair[e].y);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kEntriesAhead; ++u)
+            if (q[u] < (uint32_t)m && v[u] >= thresh) atomicAdd(&s_n[q[u]], 1);
+    }
+}
+
+// The same entries moved to out[s_n[row - a]++].
+__device__ __forceinline__ void file_entries(const int2 *__restrict__ pair, const uint16_t *__restrict__ lrow,
+                                             uint32_t c0, uint32_t c1, int32_t a, int32_t m, float thresh, int32_t *s_n,
+                                             int2 *__restrict__ out)
+{
+    for (; c0 < c1; c0 += kEntriesAhead * kTileThreads) {
+        uint32_t q[kEntriesAhead];
+        int2 p[kEntriesAhead];
+#pragma unroll
+        for (int u = 0; u < kEntriesAhead; ++u) {
+            const uint32_t e = c0 + u * kTileThreads + threadIdx.x;
+            q[u] = 0xFFFFFFFFu;
+            if (e < c1) {
+                q[u] = (uint32_t)lrow[e] - (uint32_t)a;
+                p[u] = pair[e];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kEntriesAhead; ++u)
+            if (q[u] < (uint32_t)m && __int_as_float(p[u].y) >= thresh) out[atomicAdd(&s_n[q[u]], 1)] = p[u];
+    }
+}
+
+__device__ __forceinline__ int32_t bucket_rows(int64_t row0, int64_t n, int32_t lg)
+{
+    return (int32_t)(n - row0 < ((int64_t)1 << lg) ? n - row0 : (int64_t)1 << lg);
+}
+
 // One workgroup per bucket: its kept entries counted per row in LDS and filed by
 // row into `out`, from the bucket's first slot on.  lstart[row] = the row's
 // first entry counted from there, kept_n[bucket] = its kept entries.  Buckets of
-// more rows than the counters hold take them kBucketRows at a time.
-__global__ __launch_bounds__(kTileThreads) void k_bucket_rows(const int2 *__restrict__ pair,
+// more rows than the counters hold take them kBucketRows at a time.  A heavy
+// bucket's rows were counted by k_heavy_rows<false> (in lstart), which files them
+// afterwards from `rcursor` on.
+__global__ __launch_bounds__(kTileThreads, 8) void k_bucket_rows(const int2 *__restrict__ pair,
                                                               const uint16_t *__restrict__ lrow,
                                                               const int32_t *__restrict__ first, int64_t n, int32_t lg,
                                                               int32_t n_epochs, const PrepScalars *S,
                                                               int2 *__restrict__ out, int32_t *__restrict__ lstart,
+                                                              int32_t *__restrict__ rcursor,
                                                               uint32_t *__restrict__ kept_n)
 {
-    constexpr int kAhead = 8;   // loads of a thread in flight
     __shared__ int32_t s_n[kBucketRows];
     __shared__ int32_t s_wave[kTileThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x;
     const float thresh = keep_threshold(S, n_epochs);
-    // unsigned: a step beyond the last entry may pass 2^31
     const uint32_t e0 = first[blockIdx.x * kSubs], e1 = first[(blockIdx.x + 1) * kSubs];
+    const bool heavy = e1 - e0 > (uint32_t)S->heavy_above;
     const int64_t row0 = (int64_t)blockIdx.x << lg;
-    const int32_t rows = (int32_t)(n - row0 < ((int64_t)1 << lg) ? n - row0 : (int64_t)1 << lg);
+    const int32_t rows = bucket_rows(row0, n, lg);
     int32_t done = 0;   // kept entries of the rows before
     for (int32_t a = 0; a < rows; a += kBucketRows) {
         const int32_t m = rows - a < kBucketRows ? rows - a : kBucketRows;
-        for (int32_t t = tid; t < m; t += kTileThreads) s_n[t] = 0;
+        for (int32_t t = tid; t < m; t += kTileThreads) s_n[t] = heavy ? lstart[row0 + a + t] : 0;
         __syncthreads();
-        for (uint32_t c0 = e0; c0 < e1; c0 += kAhead * kTileThreads) {
-            uint32_t q[kAhead];
-            float v[kAhead];
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const uint32_t e = c0 + u * kTileThreads + tid;
-                q[u] = 0xFFFFFFFFu;
-                if (e < e1) {
-                    q[u] = (uint32_t)lrow[e] - (uint32_t)a;
-                    v[u] = __int_as_float(pair[e].y);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u)
-                if (q[u] < (uint32_t)m && v[u] >= thresh) atomicAdd(&s_n[q[u]], 1);
-        }
+        if (!heavy) count_entries(pair, lrow, e0, e1, a, m, thresh, s_n);
         __syncthreads();
-        // exclusive scan of the m counters, kTileThreads at a time
-        for (int32_t b = 0; b < m; b += kTileThreads) {
-            const int32_t t = b + tid;
-            const int32_t v = t < m ? s_n[t] : 0;
-            int32_t x = v;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int32_t y = __shfl_up(x, off);
-                if (lane >= off) x += y;
-            }
-            if (lane == 63) s_wave[wv] = x;
-            __syncthreads();
-            int32_t before = 0, total = 0;
-#pragma unroll
-            for (int k = 0; k < kTileThreads / 64; ++k) {
-                before += k < wv ? s_wave[k] : 0;
-                total += s_wave[k];
-            }
-            if (t < m) {
-                const int32_t start = done + before + x - v;
-                s_n[t] = start;
-                lstart[row0 + a + t] = start;
-            }
-            done += total;
-            __syncthreads();
-        }
-        for (uint32_t c0 = e0; c0 < e1; c0 += kAhead * kTileThreads) {
-            uint32_t q[kAhead];
-            int2 p[kAhead];
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const uint32_t e = c0 + u * kTileThreads + tid;
-                q[u] = 0xFFFFFFFFu;
-                if (e < e1) {
-                    q[u] = (uint32_t)lrow[e] - (uint32_t)a;
-                    p[u] = pair[e];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u)
-                if (q[u] < (uint32_t)m && __int_as_float(p[u].y) >= thresh) out[e0 + atomicAdd(&s_n[q[u]], 1)] = p[u];
-        }
+        const int32_t before = done;
+        done += scan_loop(m, s_wave, [&](int32_t t) { return s_n[t]; },
+                          [&](int32_t t, int32_t x) {
+                              s_n[t] = before + x;
+                              lstart[row0 + a + t] = before + x;
+                              if (heavy) rcursor[row0 + a + t] = before + x;
+                          });
+        if (!heavy) file_entries(pair, lrow, e0, e1, a, m, thresh, s_n, out + e0);
         __syncthreads();
     }
     if (tid == 0) kept_n[blockIdx.x] = (uint32_t)done;
+}
+
+// The chunks of the heavy buckets, in strides over the grid.  Counting: their kept
+// entries per row added to row_n[row].  FILE: slots reserved from row_n[row] on (the
+// row's first entry in the bucket), one atomic per chunk and row, and the entries
+// filed there.  (A bucket taken by one
+// workgroup whatever its entries: 19.5M edges with 1/x-distributed ends 8.3 ms, now 0.25
+// in all three kernels; 200 rows of 50,000 16.8 ms, now 0.19.)
+template <bool FILE>
+__global__ __launch_bounds__(kTileThreads) void k_heavy_rows(const int2 *__restrict__ pair,
+                                                             const uint16_t *__restrict__ lrow,
+                                                             const int32_t *__restrict__ first,
+                                                             const int32_t *__restrict__ heavy_first, int64_t n,
+                                                             int32_t lg, int32_t nb, int32_t n_epochs,
+                                                             const PrepScalars *S, int32_t *__restrict__ row_n,
+                                                             int2 *__restrict__ out)
+{
+    __shared__ int32_t s_n[kBucketRows];
+    const int tid = threadIdx.x;
+    const int32_t items = S->n_heavy;
+    const float thresh = keep_threshold(S, n_epochs);
+    for (int32_t item = blockIdx.x; item < items; item += gridDim.x) {
+        // bucket b: the last with heavy_first[b] <= item (light ones have no chunks)
+        int32_t lo = 0, hi = nb - 1;
+        while (lo < hi) {
+            const int32_t mid = (lo + hi + 1) >> 1;
+            if (heavy_first[mid] <= item) lo = mid; else hi = mid - 1;
+        }
+        const uint32_t e0 = first[lo * kSubs], e1 = first[(lo + 1) * kSubs];
+        const uint32_t c0 = e0 + (uint32_t)(item - heavy_first[lo]) * kHeavyChunk;
+        const uint32_t c1 = e1 - c0 > kHeavyChunk ? c0 + kHeavyChunk : e1;
+        const int64_t row0 = (int64_t)lo << lg;
+        const int32_t rows = bucket_rows(row0, n, lg);
+        for (int32_t a = 0; a < rows; a += kBucketRows) {
+            const int32_t m = rows - a < kBucketRows ? rows - a : kBucketRows;
+            for (int32_t t = tid; t < m; t += kTileThreads) s_n[t] = 0;
+            __syncthreads();
+            count_entries(pair, lrow, c0, c1, a, m, thresh, s_n);
+            __syncthreads();
+            for (int32_t t = tid; t < m; t += kTileThreads)
+                if (s_n[t]) s_n[t] = atomicAdd(&row_n[row0 + a + t], s_n[t]);
+            __syncthreads();
+            if (FILE) {
+                file_entries(pair, lrow, c0, c1, a, m, thresh, s_n, out + e0);
+                __syncthreads();
+            }
+        }
+    }
 }
 
 // Rows longer than this are sorted by k_long_row_sort: the rank sort reads a
@@ -788,14 +912,16 @@ int64_t symmetry_slots(int64_t nnz) { return nnz / kSymEntries; }
 hipError_t launch_prep(const PrepBuffers &B, hipStream_t s)
 {
     const IngestShape sh{(uint32_t)B.n, (uint32_t)B.n_cols, B.bipartite ? 1 : 0};
-    const int32_t lg = bucket_lg(B.n);
-    const int32_t nb = (int32_t)bucket_count(B.n);
+    const int32_t lg = bucket_lg(B.n, B.nnz);
+    const int32_t nb = (int32_t)bucket_count(B.n, B.nnz);
     const size_t lds = sizeof(int32_t) * (size_t)nb;
     const int64_t tiles = (B.nnz + kTile - 1) / kTile;
-    // the bucket counters and the scalars start at zero (the cursors at the scan)
-    hipError_t e = launch_zero_u64(reinterpret_cast<unsigned long long *>(B.bucket_n), bucket_counters(B.n) / 2, s);
-    if (e != hipSuccess) return e;
-    e = launch_zero_u64(reinterpret_cast<unsigned long long *>(B.scalars), sizeof(PrepScalars) / 8, s);
+    const int64_t heavy = heavy_chunks(B.nnz) < 1024 ? heavy_chunks(B.nnz) : 1024;
+    // the bucket counters, the scalars and, for heavy buckets, the rows' counts start
+    // at zero (the cursors at the scan); they lie one after the other
+    char *const zero_end = heavy ? reinterpret_cast<char *>(B.lstart + B.n) : reinterpret_cast<char *>(B.scalars + 1);
+    hipError_t e = launch_zero_u64(reinterpret_cast<unsigned long long *>(B.bucket_n),
+                                   (zero_end - reinterpret_cast<char *>(B.bucket_n) + 7) / 8, s);
     if (e != hipSuccess) return e;
     if (tiles > 0) {
         // every block adds its counters to all buckets' once: two rounds of blocks
@@ -803,14 +929,21 @@ hipError_t launch_prep(const PrepBuffers &B, hipStream_t s)
         hipLaunchKernelGGL(k_check, dim3((unsigned)g), dim3(kTileThreads), lds, s, B.rows, B.cols, B.vals, B.nnz, sh, lg,
                            nb, B.bucket_n, B.scalars);
     }
-    hipLaunchKernelGGL((k_bucket_scan<true>), dim3(1), dim3(kTileThreads), 0, s, B.bucket_n, kSubs * nb, B.first,
-                       B.cursor);
+    hipLaunchKernelGGL(k_bucket_starts, dim3(1), dim3(kTileThreads), 0, s, B.bucket_n, nb, B.first, B.cursor,
+                       B.heavy_first, B.scalars);
     if (tiles > 0)
         hipLaunchKernelGGL(k_bucket_scatter, dim3((unsigned)tiles), dim3(kTileThreads), lds, s, B.rows, B.cols, B.vals,
                            B.nnz, sh, lg, nb, B.cursor, B.pair, B.lrow);
+    // (the rows' cursors of heavy buckets: rp32, which the row sort writes)
+    if (heavy)
+        hipLaunchKernelGGL((k_heavy_rows<false>), dim3((unsigned)heavy), dim3(kTileThreads), 0, s, B.pair, B.lrow, B.first,
+                           B.heavy_first, B.n, lg, nb, B.n_epochs, B.scalars, B.lstart, B.pair_rows);
     hipLaunchKernelGGL(k_bucket_rows, dim3((unsigned)nb), dim3(kTileThreads), 0, s, B.pair, B.lrow, B.first, B.n, lg,
-                       B.n_epochs, B.scalars, B.pair_rows, B.lstart, B.kept_n);
-    hipLaunchKernelGGL((k_bucket_scan<false>), dim3(1), dim3(kTileThreads), 0, s, B.kept_n, nb, B.kfirst, nullptr);
+                       B.n_epochs, B.scalars, B.pair_rows, B.lstart, B.rp32, B.kept_n);
+    if (heavy)
+        hipLaunchKernelGGL((k_heavy_rows<true>), dim3((unsigned)heavy), dim3(kTileThreads), 0, s, B.pair, B.lrow, B.first,
+                           B.heavy_first, B.n, lg, nb, B.n_epochs, B.scalars, B.rp32, B.pair_rows);
+    hipLaunchKernelGGL(k_kept_starts, dim3(1), dim3(kTileThreads), 0, s, B.kept_n, nb, B.kfirst);
     const SortedRows out{B.col, B.eps, B.pair, B.col16};
     const Grid2 rg = grid2(row_blocks(B.n), 256);
     const dim3 rb(rg.x, rg.y);

@@ -50,7 +50,7 @@ def _check(h, n, r, c, v, N, bipartite=False):
     assert st["max_degree"] == np.diff(want[0]).max() and st["nnz_kept"] == want[1].size
 
 
-def _hubs(n, hubs, degree, seed):
+def _hubs(n, hubs, degree, seed, rest=None):
     """`hubs` vertices joined to `degree` others each, and a sparse rest."""
     rng = np.random.default_rng(seed)
     lo, hi = [], []
@@ -60,7 +60,7 @@ def _hubs(n, hubs, degree, seed):
         t = t[t != h]
         lo.append(np.minimum(h, t))
         hi.append(np.maximum(h, t))
-    e = rng.integers(0, n, size=(2, 2 * n))
+    e = rng.integers(0, n, size=(2, 2 * n if rest is None else rest))
     e = e[:, e[0] != e[1]]
     lo.append(e.min(0))
     hi.append(e.max(0))
@@ -247,3 +247,27 @@ def test_asymmetric_entries_in_every_piece(n, hub):
             with pytest.raises(U.UmapLayoutError) as ei:
                 U.umap_layout_create(n, 2, rr, cc, vv, A_DEF, B_DEF, 50, 5)
             assert ei.value.code == U.UMAP_E_ASYMMETRIC
+
+
+@pytest.mark.parametrize("n,hubs,degree", [(300_000, 3, 65_000), (300_000, 5, 90_000), (9_000_001, 2, 140_000)])
+def test_buckets_taken_in_chunks(n, hubs, degree):
+    """Buckets of more than 65,536 entries (those of a hub) are counted and filed by
+    several workgroups, 32,768 entries each; in buckets of 16,384 rows in two parts."""
+    r, c, v = _hubs(n, hubs, degree, seed=degree, rest=400_000)
+    case(f"n {n}, {hubs} hubs of degree {degree}")
+    with U.umap_layout_create(n, 2, r, c, v, A_DEF, B_DEF, 200, 5) as h:
+        _check(h, n, r, c, v, 200)
+
+
+@pytest.mark.parametrize("n_new,k", [(1, 65_536), (1, 65_537), (2, 131_072), (40, 90_000)])
+def test_few_rows_taken_in_chunks(n_new, k):
+    n_table = 200_000
+    rng = np.random.default_rng(k)
+    c = np.concatenate([rng.permutation(n_table)[:k] for _ in range(n_new)]).astype(np.int32)
+    r = np.repeat(np.arange(n_new, dtype=np.int32), k)
+    v = rng.uniform(0.001, 1.0, r.size).astype(np.float32)
+    p = rng.permutation(r.size)
+    r, c, v = r[p], c[p], v[p]
+    case(f"bipartite {n_new} x {n_table}, {k} entries per row")
+    with U.umap_transform_create(n_new, synth.embedding_state(n_table, 2, 1), r, c, v, A_DEF, B_DEF, 100, 5) as h:
+        _check(h, n_new, r, c, v, 100, bipartite=True)
