@@ -334,7 +334,7 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         B.n_cols = h->n_table;
         B.bipartite = table != nullptr;
         B.n_epochs = n_epochs;
-        const int64_t nb = ul::bucket_count(n, nnz), nc = ul::bucket_counters(n, nnz), nrb = ul::row_blocks(n),
+        const int64_t nb = ul::bucket_count(n, nnz), nc = ul::bucket_counters(n, nnz), nrb = ul::row_blocks(n, nnz),
                       n_long = ul::long_row_slots(nnz), n_sym = table ? 0 : ul::symmetry_slots(nnz);
         size_t sbytes = 2 * need<uint32_t>(nc) + need<int32_t>(ul::kSubs * nb + 1) + 2 * need<int32_t>(nb + 1) +
                         need<uint32_t>(nb) + 3 * need<int32_t>(nrb) +

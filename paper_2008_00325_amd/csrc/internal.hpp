@@ -86,9 +86,9 @@ struct PrepBuffers {
     int32_t *rp32;        // n + 1, row_ptr in 32 bits
     int32_t *long_rows;   // long_row_slots(nnz)
     int2 *sym_list;       // symmetry_slots(nnz): (block of rows, piece)
-    int32_t *block_max;   // row_blocks(n), per-block parts of the scalars
-    int32_t *block_near;  // row_blocks(n)
-    int32_t *block_diff;  // row_blocks(n)
+    int32_t *block_max;   // row_blocks(n, nnz), per-block parts of the scalars
+    int32_t *block_near;  // row_blocks(n, nnz)
+    int32_t *block_diff;  // row_blocks(n, nnz)
     // outputs (device)
     int64_t *row_ptr;   // n + 1
     int32_t *col;       // nnz (capacity)
@@ -102,7 +102,7 @@ struct PrepBuffers {
 constexpr int kSubs = 8;
 int64_t bucket_count(int64_t n, int64_t nnz);
 int64_t bucket_counters(int64_t n, int64_t nnz);
-int64_t row_blocks(int64_t n);
+int64_t row_blocks(int64_t n, int64_t nnz);
 int64_t long_row_slots(int64_t nnz);
 int64_t symmetry_slots(int64_t nnz);
 hipError_t launch_prep(const PrepBuffers &B, hipStream_t s);

@@ -120,7 +120,14 @@ int64_t bucket_count(int64_t n, int64_t nnz)
     return (n + ((int64_t)1 << lg) - 1) >> lg;
 }
 int64_t bucket_counters(int64_t n, int64_t nnz) { return kPad * kSubs * bucket_count(n, nnz); }
-int64_t row_blocks(int64_t n) { return (n + kSortRows - 1) / kSortRows; }
+// Rows of a block of k_row_sort and k_symmetry: kSortRows, or kSortRowsDense in
+// graphs of long rows, where those fill a block and more blocks the chip (a complete
+// graph of 300 vertices: k_row_sort 179 us with 32 rows, now 30; 100,000 rows of 120,
+// which have blocks enough, 175).
+constexpr int kSortRowsDense = 4;
+constexpr int64_t kDenseRow = 128;
+int32_t sort_rows(int64_t n, int64_t nnz) { return nnz >= kDenseRow * n ? kSortRowsDense : kSortRows; }
+int64_t row_blocks(int64_t n, int64_t nnz) { return (n + sort_rows(n, nnz) - 1) / sort_rows(n, nnz); }
 
 // Buckets of many entries (those of hubs) are counted and filed in chunks by
 // workgroups of their own: a bucket of more than kHeavyEntries entries that also
@@ -477,13 +484,14 @@ struct SortedRows {
     int16_t *col16;    // col - row (null: bipartite)
 };
 
-// kSortRows rows per block.  src: the rows' entries in any order, from
+// ROWS rows per block.  src: the rows' entries in any order, from
 // first[bucket kSubs] + lstart[row] on; out: in (row, col) order.  Rank sort: an
 // entry's slot is the number of smaller columns in its row, read from LDS four
 // at a time (the rows are padded to multiples of four there); the entries are
 // put in order in LDS and written in runs.  A slot left empty is a duplicate.
 // (26.7M entries, 1M rows: 475 us reading the row entry by entry and writing
 // each entry at its slot, 446 us with 16 rows per block, now 375.)
+template <int ROWS>
 __global__ __launch_bounds__(256) void k_row_sort(const int2 *__restrict__ src, const int32_t *__restrict__ first,
                                                   const int32_t *__restrict__ kfirst,
                                                   const int32_t *__restrict__ lstart, int64_t n, int32_t lg,
@@ -492,25 +500,25 @@ __global__ __launch_bounds__(256) void k_row_sort(const int2 *__restrict__ src, 
                                                   int32_t *__restrict__ block_near, int32_t *__restrict__ block_max,
                                                   int2 *__restrict__ sym_list, SortedRows out)
 {
-    __shared__ __align__(16) int32_t s_col[kRowTile + 4 * kSortRows];   // columns by padded row
+    __shared__ __align__(16) int32_t s_col[kRowTile + 4 * ROWS];   // columns by padded row
     __shared__ int2 s_out[kRowTile];
     __shared__ uint8_t s_row[kRowTile];
-    __shared__ int32_t s_start[kSortRows + 1], s_pad[kSortRows + 1];
+    __shared__ int32_t s_start[ROWS + 1], s_pad[ROWS + 1];
     __shared__ unsigned s_flags, s_near;
     __shared__ int32_t s_piece;
     const int tid = threadIdx.x;
     const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    const int64_t r0 = block * kSortRows;
+    const int64_t r0 = block * ROWS;
     if (r0 >= n) return;   // the last row of a grid of two dimensions
-    const int nr = (int)(n - r0 < kSortRows ? n - r0 : kSortRows);
+    const int nr = (int)(n - r0 < ROWS ? n - r0 : ROWS);
     const int64_t b = r0 >> lg;
     const int32_t dst = kfirst[b];
     const int2 *const in = src + first[b * kSubs];
     const float w_max = __uint_as_float(S->wmax_bits);
     // the rows' first entries, as uniform values (scalar loads) and in LDS
-    int32_t ustart[kSortRows];
+    int32_t ustart[ROWS];
 #pragma unroll
-    for (int k = 0; k < kSortRows; ++k) ustart[k] = k < nr ? lstart[r0 + k] : INT32_MAX;
+    for (int k = 0; k < ROWS; ++k) ustart[k] = k < nr ? lstart[r0 + k] : INT32_MAX;
     if (tid <= nr) {
         const int64_t r = r0 + tid;
         // past the last row of a bucket: the bucket's kept entries
@@ -523,12 +531,13 @@ __global__ __launch_bounds__(256) void k_row_sort(const int2 *__restrict__ src, 
     }
     if (tid == 0) s_flags = s_near = 0;
     __syncthreads();
-    if (tid < 64) {   // kSortRows < 64
+    static_assert(ROWS < 64, "a lane per row");
+    if (tid < 64) {
         const int32_t len = tid < nr ? s_start[tid + 1] - s_start[tid] : 0;
         // the rows' places in s_col
         int32_t x = (len + 3) & ~3;
 #pragma unroll
-        for (int off = 1; off < 2 * kSortRows; off <<= 1) {
+        for (int off = 1; off < 2 * ROWS; off <<= 1) {
             const int32_t y = __shfl_up(x, off);
             if (tid >= off) x += y;
         }
@@ -575,7 +584,7 @@ __global__ __launch_bounds__(256) void k_row_sort(const int2 *__restrict__ src, 
             // the last row that starts at or before t (it is not empty)
             int r = -1;
 #pragma unroll
-            for (int k = 0; k < kSortRows; ++k) r += ustart[k] - t0 <= t;
+            for (int k = 0; k < ROWS; ++k) r += ustart[k] - t0 <= t;
             row[u] = r;
             if (t < m) s_col[s_pad[r] - pad0 + t - (s_start[r] - t0)] = p[u].x;
         }
@@ -745,14 +754,15 @@ __global__ __launch_bounds__(kSortThreads) void k_long_row_sort(const int2 *__re
 // entry, now 486 (26.7M edges in local order 693 -> 274).  Rows of more than
 // kLookupRow entries go to the binary search at once, which reads the columns
 // alone.
-// A block takes up to kSymEntries entries of its kSortRows rows; the further
+// A block takes up to kSymEntries entries of its rows; the further
 // pieces of long or dense rows are listed by k_row_sort and taken by blocks of
 // their own, so that no block has a long row to itself: 9M edges of a complete
 // graph of 3,000 vertices, where each block had 32 rows, 4444 us, now 500; 19.5M
 // edges with 1/x-distributed ends 29.5 ms, now 0.48.
 constexpr uint32_t kLookupRow = 96;
 __global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair, const int32_t *__restrict__ col,
-                                                  const int32_t *__restrict__ rp32, int64_t n, int64_t row_blocks,
+                                                  const int32_t *__restrict__ rp32, int64_t n, int32_t rows,
+                                                  int64_t row_blocks,
                                                   int32_t more_blocks, const int2 *__restrict__ sym_list,
                                                   PrepScalars *S, int32_t *__restrict__ block_diff)
 {
@@ -779,8 +789,8 @@ __global__ __launch_bounds__(256) void k_symmetry(const int2 *__restrict__ pair,
     const int group = lane / kG, part = lane % kG;
     do {
         const int2 p0 = first_piece ? make_int2((int)block, 0) : sym_list[item];
-        const int64_t r0 = (int64_t)p0.x * kSortRows;
-        const int nr = (int)(n - r0 < kSortRows ? n - r0 : kSortRows);
+        const int64_t r0 = (int64_t)p0.x * rows;
+        const int nr = (int)(n - r0 < rows ? n - r0 : rows);
         __syncthreads();   // the last piece's rows are done with
         if (tid <= nr) s_start[tid] = rp32[r0 + tid];
         __syncthreads();
@@ -945,9 +955,11 @@ hipError_t launch_prep(const PrepBuffers &B, hipStream_t s)
                            B.heavy_first, B.n, lg, nb, B.n_epochs, B.scalars, B.rp32, B.pair_rows);
     hipLaunchKernelGGL(k_kept_starts, dim3(1), dim3(kTileThreads), 0, s, B.kept_n, nb, B.kfirst);
     const SortedRows out{B.col, B.eps, B.pair, B.col16};
-    const Grid2 rg = grid2(row_blocks(B.n), 256);
-    const dim3 rb(rg.x, rg.y);
-    hipLaunchKernelGGL(k_row_sort, rb, dim3(256), 0, s, B.pair_rows, B.first, B.kfirst, B.lstart, B.n, lg,
+    const int32_t per_block = sort_rows(B.n, B.nnz);
+    const int64_t blocks = row_blocks(B.n, B.nnz);
+    const Grid2 rg = grid2(blocks, 256);
+    auto *const sort = per_block == kSortRows ? k_row_sort<kSortRows> : k_row_sort<kSortRowsDense>;
+    hipLaunchKernelGGL(sort, dim3(rg.x, rg.y), dim3(256), 0, s, B.pair_rows, B.first, B.kfirst, B.lstart, B.n, lg,
                        B.scalars, B.row_ptr, B.rp32, B.long_rows, B.block_near, B.block_max, B.sym_list, out);
     const int64_t max_long = long_row_slots(B.nnz);
     if (max_long > 0) {
@@ -959,13 +971,13 @@ hipError_t launch_prep(const PrepBuffers &B, hipStream_t s)
     }
     if (!B.bipartite) {
         const int64_t more = symmetry_slots(B.nnz) < 1024 ? symmetry_slots(B.nnz) : 1024;
-        const Grid2 sg = grid2(row_blocks(B.n) + more, 256);
-        hipLaunchKernelGGL(k_symmetry, dim3(sg.x, sg.y), dim3(256), 0, s, B.pair, B.col, B.rp32, B.n, row_blocks(B.n),
-                           (int32_t)more, B.sym_list, B.scalars, B.block_diff);
+        const Grid2 sg = grid2(blocks + more, 256);
+        hipLaunchKernelGGL(k_symmetry, dim3(sg.x, sg.y), dim3(256), 0, s, B.pair, B.col, B.rp32, B.n, per_block,
+                           blocks, (int32_t)more, B.sym_list, B.scalars, B.block_diff);
     }
-    const int64_t g = (row_blocks(B.n) + 1023) / 1024;
+    const int64_t g = (blocks + 1023) / 1024;
     hipLaunchKernelGGL(k_prep_sums, dim3((unsigned)(g < 64 ? g : 64)), dim3(256), 0, s, B.block_max, B.block_near,
-                       B.bipartite ? nullptr : B.block_diff, row_blocks(B.n), B.scalars);
+                       B.bipartite ? nullptr : B.block_diff, blocks, B.scalars);
     return hipGetLastError();
 }
 

@@ -223,11 +223,11 @@ def test_more_rows_than_one_grid_dimension(n):
     assert a == n + 1
 
 
-@pytest.mark.parametrize("n,hub", [(300, 0), (9_001, 9_000)])
+@pytest.mark.parametrize("n,hub", [(300, 0), (1_100, 0), (9_001, 9_000)])
 def test_asymmetric_entries_in_every_piece(n, hub):
-    """Blocks of rows with more than 4,096 entries (a complete graph of 300, a hub
-    of 9,000) are checked in pieces: one entry changed or taken out anywhere in
-    them is found."""
+    """Blocks of rows with more than 4,096 entries (4 rows of a complete graph of
+    1,100, 32 rows with a hub of 9,000) are checked in pieces: one entry changed or
+    taken out anywhere in them is found."""
     if hub:
         lo, hi = np.zeros(hub, np.int32), np.arange(1, hub + 1, dtype=np.int32)
     else:
@@ -271,3 +271,18 @@ def test_few_rows_taken_in_chunks(n_new, k):
     case(f"bipartite {n_new} x {n_table}, {k} entries per row")
     with U.umap_transform_create(n_new, synth.embedding_state(n_table, 2, 1), r, c, v, A_DEF, B_DEF, 100, 5) as h:
         _check(h, n_new, r, c, v, 100, bipartite=True)
+
+
+@pytest.mark.parametrize("n,deg", [(200, 127), (200, 128), (257, 140), (258, 200), (1_003, 500), (1_003, 520)])
+def test_dense_graphs(n, deg):
+    """Blocks of 4 rows from 128 entries per row on: circulant graphs of `deg` entries
+    per row (one more where n is even and deg odd), and rows of 513 and more."""
+    i, half = np.arange(n), deg // 2
+    lo = np.concatenate([i] * half + ([i[: n // 2]] if deg % 2 else []))
+    hi = np.concatenate([(i + q) % n for q in range(1, half + 1)] + ([i[: n // 2] + n // 2] if deg % 2 else []))
+    v = np.random.default_rng(n).uniform(0.001, 1.0, lo.size).astype(np.float32)
+    p = np.random.default_rng(deg).permutation(2 * lo.size)
+    r, c, v = np.r_[lo, hi][p].astype(np.int32), np.r_[hi, lo][p].astype(np.int32), np.r_[v, v][p]
+    case(f"circulant n {n}, {deg} entries per row")
+    with U.umap_layout_create(n, 2, r, c, v, A_DEF, B_DEF, 400, 5) as h:
+        _check(h, n, r, c, v, 400)
