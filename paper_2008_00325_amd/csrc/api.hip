@@ -1090,18 +1090,21 @@ int umap_trustworthiness(const float *X, int64_t n, int32_t d, const float *Y, i
         int32_t *cnt = cv.take<int32_t>(nk);
         unsigned long long *sum = cv.take<unsigned long long>(2);
         unsigned *flags = reinterpret_cast<unsigned *>(sum + 1);
-        UL_HIP(ul::launch_zero_u64(sum, 2, s));
-        UL_HIP(ul::launch_trustworthiness(X, n, d, Y, dim, k, split_bytes ? split : nullptr, nx, nbr, thr, cnt, sum,
-                                          flags, s));
         unsigned long long hsum = 0;
         unsigned hflags = 0;
         char *const hb = reinterpret_cast<char *>(scratch.host());
-        UL_HIP(hipMemcpyAsync(hb, sum, sizeof hsum, hipMemcpyDeviceToHost, s));
-        UL_HIP(hipMemcpyAsync(hb + sizeof hsum, flags, sizeof hflags, hipMemcpyDeviceToHost, s));
-        UL_HIP(hipStreamSynchronize(s));
-        memcpy(&hsum, hb, sizeof hsum);
-        memcpy(&hflags, hb + sizeof hsum, sizeof hflags);
-        if (hflags) return fail(UMAP_E_INVAL, "the embedding has non-finite coordinates");
+        auto pass = [&](void *parts) {
+            UL_HIP(ul::launch_zero_u64(sum, 2, s));
+            UL_HIP(ul::launch_trustworthiness(X, n, d, Y, dim, k, parts, nx, nbr, thr, cnt, sum, flags, s));
+            UL_HIP(hipMemcpyAsync(hb, sum, sizeof hsum, hipMemcpyDeviceToHost, s));
+            UL_HIP(hipMemcpyAsync(hb + sizeof hsum, flags, sizeof hflags, hipMemcpyDeviceToHost, s));
+            UL_HIP(hipStreamSynchronize(s));
+            memcpy(&hsum, hb, sizeof hsum);
+            memcpy(&hflags, hb + sizeof hsum, sizeof hflags);
+        };
+        pass(split_bytes ? split : nullptr);
+        if (hflags == ul::kTrustFarPoint) pass(nullptr);
+        if (hflags & ul::kTrustBadEmbedding) return fail(UMAP_E_INVAL, "the embedding has non-finite coordinates");
         const double nn = (double)n, kk = (double)k;
         *out = 1.0 - 2.0 / (nn * kk * (2.0 * nn - 3.0 * kk - 1.0)) * (double)hsum;
         return UMAP_OK;

@@ -221,7 +221,10 @@ int64_t trust_padded(int64_t n);
 size_t trust_split_bytes(int64_t n, int32_t d);
 // Scratch, with np = trust_padded(n): split (or null), nx[np], nbr[np k],
 // thr[np k], cnt[np k] (slot s of point i at s np + i), sum[1] and flags[1]
-// (both zeroed by the caller).
+// (both zeroed by the caller).  With kTrustFarPoint raised the sum is not to be
+// used: some point is too far out for the split points' ranks (split null: it is
+// never raised).
+enum TrustFlag : unsigned { kTrustBadEmbedding = 1u, kTrustFarPoint = 2u };
 hipError_t launch_trustworthiness(const float *X, int64_t n, int32_t d, const float *Y, int32_t dim, int32_t k,
                                   void *split, float *nx, int32_t *nbr, float *thr, int32_t *cnt,
                                   unsigned long long *sum, unsigned *flags, hipStream_t s);

@@ -18,7 +18,8 @@
 //     of 128 x 128 on the bf16 matrix cores, compared in registers with the
 //     neighbour thresholds of both points: only the counts r(i, j) - 1 leave the
 //     chip, never the n x n distances.  (k_tw_rank: every pair twice, fp32
-//     matrix instructions on X itself; only where the parts would not fit.)
+//     matrix instructions on X itself; only where the parts would not fit or
+//     the points' norms come near fp32's range.)
 //  5. k_tw_penalty: the penalties' sum.
 #include "internal.hpp"
 #include "launch_sizes.hpp"
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(256) void k_tw_thresholds(const float *__restrict__
         if (j < 0 || j >= n) {
             if (lane == 0) {
                 thr[s * np + i] = -INFINITY;
-                atomicOr(flags, 1u);
+                atomicOr(flags, (unsigned)kTrustBadEmbedding);
             }
             continue;
         }
@@ -459,10 +460,17 @@ __device__ __forceinline__ uint32_t bf16_bits(float x)
     return (r & 0x7F80u) == 0x7F80u ? b >> 16 : r;
 }
 
+// Squared norms up to here leave every distance, threshold and partial sum finite.
+constexpr float kPairNormMax = 2.1e37f;   // below 2^128 / 16
+
 // One wave per point of the padded panels: its parts and its squared norm
-// (+infinity for the points past n, so that nothing counts them).
+// (+infinity for the points past n, so that nothing counts them).  A point that is
+// not finite or further out than kPairNormMax raises kTrustFarPoint: k_tw_rank_pairs
+// counts by the signs of differences, which infinities and NaN do not order, and
+// k_tw_rank takes such inputs.
 __global__ __launch_bounds__(256) void k_tw_split(const float *__restrict__ X, int64_t n, int32_t d, int32_t steps,
-                                                  uint4 *__restrict__ P, float *__restrict__ nx)
+                                                  uint4 *__restrict__ P, float *__restrict__ nx,
+                                                  unsigned *__restrict__ flags)
 {
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kWave;
     const int lane = (int)(threadIdx.x % kWave);
@@ -495,7 +503,10 @@ __global__ __launch_bounds__(256) void k_tw_split(const float *__restrict__ X, i
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
-    if (lane == 0) nx[i] = i < n ? sq : INFINITY;
+    if (lane == 0) {
+        nx[i] = i < n ? sq : INFINITY;
+        if (i < n && !(sq <= kPairNormMax)) atomicOr(flags, (unsigned)kTrustFarPoint);
+    }
 }
 
 // the next float above x (x itself where it is not finite)
@@ -509,7 +520,7 @@ __device__ __forceinline__ float next_up(float x)
 // word per threshold and the words' bits are counted, two instructions per
 // comparison.  (A compare into a scalar mask is followed by two wait states
 // before the mask can be added: twice the cycles.)  x and t are not both
-// infinite: x is a distance or +infinity, t finite or -infinity.
+// infinite: x is a distance or +infinity, t finite or -infinity (kPairNormMax).
 __device__ __forceinline__ uint32_t push_less(uint32_t bits, float x, float t)
 {
     return __builtin_amdgcn_alignbit(bits, __float_as_uint(x - t), 31);
@@ -520,8 +531,10 @@ __global__ __launch_bounds__(kPairThreads, 2) void k_tw_rank_pairs(const uint4 *
                                                           int32_t steps, int64_t span, int32_t k,
                                                           const float *__restrict__ nx,
                                                           const int32_t *__restrict__ nbr,
-                                                          const float *__restrict__ thr, int32_t *__restrict__ cnt)
+                                                          const float *__restrict__ thr, int32_t *__restrict__ cnt,
+                                                          const unsigned *__restrict__ flags)
 {
+    if (*flags & kTrustFarPoint) return;   // the caller takes k_tw_rank
     constexpr int kOperand = kPanel * kUnits;                       // units per panel and step
     constexpr int kTrBytes = 4 * kTrCols * kTrStride * 4;           // transposed pieces of the four waves
     constexpr int kThBytes = 4 * KS * kPanel * 4;                   // thresholds and neighbours, rows' and columns'
@@ -761,12 +774,12 @@ size_t trust_split_bytes(int64_t n, int32_t d)
 
 template <int KS>
 static void launch_pairs(const uint4 *P, int64_t n, int64_t np, int32_t steps, int32_t k, const float *nx,
-                         const int32_t *nbr, const float *thr, int32_t *cnt, hipStream_t s)
+                         const int32_t *nbr, const float *thr, int32_t *cnt, const unsigned *flags, hipStream_t s)
 {
     const int64_t panels = np / kPanel;
     const int64_t span = panel_span(panels);
     hipLaunchKernelGGL((k_tw_rank_pairs<KS>), dim3((unsigned)panel_blocks(panels, span)), dim3(kPairThreads), 0, s, P, n, np,
-                       steps, span, k, nx, nbr, thr, cnt);
+                       steps, span, k, nx, nbr, thr, cnt, flags);
 }
 
 template <int DIM>
@@ -785,7 +798,7 @@ hipError_t launch_trustworthiness(const float *X, int64_t n, int32_t d, const fl
     const int32_t steps = (d + kFeat - 1) / kFeat;
     if (split)
         hipLaunchKernelGGL(k_tw_split, dim3((unsigned)(np / 4)), dim3(256), 0, s, X, n, d, steps,
-                           static_cast<uint4 *>(split), nx);
+                           static_cast<uint4 *>(split), nx, flags);
     else
         hipLaunchKernelGGL(k_tw_norms, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, X, n, d, nx);
     hipError_t e = hipSuccess;
@@ -806,9 +819,9 @@ hipError_t launch_trustworthiness(const float *X, int64_t n, int32_t d, const fl
     if (split) {
         const uint4 *const P = static_cast<const uint4 *>(split);
         if (k <= 8)
-            launch_pairs<8>(P, n, np, steps, k, nx, nbr, thr, cnt, s);
+            launch_pairs<8>(P, n, np, steps, k, nx, nbr, thr, cnt, flags, s);
         else
-            launch_pairs<kCountPiece>(P, n, np, steps, k, nx, nbr, thr, cnt, s);
+            launch_pairs<kCountPiece>(P, n, np, steps, k, nx, nbr, thr, cnt, flags, s);
     } else if (k <= 16) {
         launch_rank<16, 4>(X, n, d, k, np, nx, nbr, thr, cnt, s);
     } else if (k <= 32) {

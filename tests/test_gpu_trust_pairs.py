@@ -118,3 +118,31 @@ def test_far_and_non_finite_embedding():
     with pytest.raises(U.UmapLayoutError) as ei:
         U.umap_trustworthiness(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), k)
     assert ei.value.code == U.UMAP_E_INVAL
+
+
+@pytest.mark.parametrize("n,d,k", [(300, 6, 5), (1000, 40, 15), (515, 33, 40)])
+@pytest.mark.parametrize("what", ["inf", "-inf", "nan", "far", "inf and nan", "all far"])
+def test_far_and_non_finite_points(monkeypatch, n, d, k, what):
+    """Input points that are not finite, or whose squared norms or distances leave
+    fp32's range, give the ranks of the fp32 kernels."""
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    Y = X[:, :2] + 0.1 * rng.standard_normal((n, 2)).astype(np.float32)
+    if "inf" in what:
+        X[7, d // 2] = np.float32(what.split()[0])
+        X[n - 1, 0] = np.inf
+    if "nan" in what:
+        X[130, 1] = np.nan
+    if what == "far":
+        X[5] = 1e19          # distances overflow, no coordinate does
+        X[n - 2, 2] = 3e38
+        X[9, 0] = 4.7e18     # a finite norm close to the limit
+    if what == "all far":
+        X *= np.float32(3e18)
+    case(f"points {what} n {n} d {d} k {k}")
+    pairs, plain = _both(monkeypatch, X, Y, k)
+    assert pairs == plain
+    if what != "all far":    # a few points out of place, nothing else
+        ok = X.copy()
+        ok[~(np.abs(X) < 1e10).all(axis=1)] = 50.0
+        assert abs(pairs - O.trustworthiness(ok, Y, k)) <= 10.0 / n
