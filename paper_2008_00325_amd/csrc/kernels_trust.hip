@@ -10,12 +10,12 @@
 // and add nothing.
 //
 //  1. k_tw_split: every input row as three bf16 parts per feature, and |x_i|^2
-//     (k_tw_norms where the parts would not fit).
+//     (k_tw_pack: as it is, up to 16 features; k_tw_norms where neither fits).
 //  2. k_tw_embed_knn: one wavefront per point, a brute-force scan of the
 //     embedding keeping the k best (distance, index) pairs sorted across lanes.
 //  3. k_tw_thresholds: input distance from i to each embedding neighbour.
 //  4. k_tw_rank_pairs: the input distances of every pair of points once, as tiles
-//     of 128 x 128 on the bf16 matrix cores, compared in registers with the
+//     of 128 x 128 on the matrix cores, compared in registers with the
 //     neighbour thresholds of both points: only the counts r(i, j) - 1 leave the
 //     chip, never the n x n distances.  (k_tw_rank: every pair twice, fp32
 //     matrix instructions on X itself; only where the parts would not fit or
@@ -418,15 +418,24 @@ static void launch_rank(const float *X, int64_t n, int32_t d, int32_t k, int64_t
 //
 // Each fp32 feature is split into three bf16 values whose sum it is (8 + 8 + 8
 // bits), and a dot product is the sum of the six products of parts down to 2^-16
-// of the leading one, in fp32 accumulators; what is left out is below 2^-24 of
-// the product, the fp32 rounding of one term.  Six bf16 instructions of 32
-// features take 96 matrix-core cycles where the fp32 ones take 256.
-// 70,000 x 784, k = 15: 28.3 ms where k_tw_rank takes 85.0; 20,000 x 300, k = 30:
-// 2.5 against 5.6.  Against 64-bit sums the dot products' error is that of the
-// fp32 chain or less (image-like points, 800 features: 2.3e-7 of |x| |y| against
-// 2.8e-7; 32 features 2.5e-8 against 5.6e-8).  The matrix cores are busy a third of the time, the VALU
-// (counting) a quarter, LDS two fifths: two waves per SIMD (registers) do not
-// cover the operands' way from the Infinity Cache.
+// of the leading one; what is left out is below 2^-25 of the product, half the fp32
+// rounding of one term.  Six bf16 instructions of 32 features take 96 matrix-core
+// cycles where the fp32 ones take 256.
+// The bf16 instructions cut what they add off toward zero, at the size of the
+// accumulator or of the largest product.  So the leading products of 32 features
+// (exact in fp32 each) and the others are summed apart, from zero, and added to the
+// running sums as rounded fp32 numbers.  (All six accumulated in one chain over all
+// features: 29.1 ms instead of 31.1 at 70,000 x 784, but every dot product low by
+// 1.2e-8 of |x| |y| on average, and T at 32,000 x 784 5e-8 off 64-bit sums, now 3e-9
+// as with the fp32 instructions.)  The dot products' error against 64-bit sums is below
+// that of the fp32 chain from 16 features on (root mean square, of |x| |y|: 32
+// image-like features 2.2e-8 against 5.1e-8, 784 6.9e-8 against 2.3e-7; 24 features of
+// scales 1e-3 .. 1e3 3.6e-8 against 4.7e-8).  Fewer features of different scales would
+// lose (8: 3.9e-8 against 3.7e-8): up to kPackFeat the points stay fp32 and the products
+// are the fp32 instructions', in k_tw_rank's order.
+// 70,000 x 784, k = 15: @@ ms where k_tw_rank takes 85.0.  The matrix cores are busy a
+// third of the time, the VALU (counting) a quarter, LDS two fifths: two waves per SIMD
+// (registers) do not cover the operands' way from the Infinity Cache.
 //
 // A block multiplies 128 points (rows) with tiles of 128 points on and above the
 // diagonal and counts each distance for both of its points.  The split points
@@ -440,8 +449,10 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kPanel = 128;
-constexpr int kUnits = 12;
+constexpr int kUnits = 12;                 // of a point and step
 constexpr int kFeat = 32;                  // features per step
+constexpr int kPackUnits = 4;              // of a point of up to
+constexpr int kPackFeat = 16;              //   this many features, as they are
 constexpr int kCountPiece = 16;            // thresholds counted at a time
 constexpr int kTrStride = 68;              // floats per column of a transposed piece
 constexpr int kTrCols = 16;
@@ -451,6 +462,9 @@ __device__ __forceinline__ int unit_slot(int u, int r)
     const int t = u + ((r >> 2) & 3);
     return t < kUnits ? t : t - kUnits;
 }
+
+// The unit of features 4 u .. 4 u + 3 of packed point r.
+__device__ __forceinline__ int pack_slot(int u, int r) { return (u + (r >> 2)) & (kPackUnits - 1); }
 
 // bf16 of x, to nearest even (toward zero where that would overflow)
 __device__ __forceinline__ uint32_t bf16_bits(float x)
@@ -509,6 +523,31 @@ __global__ __launch_bounds__(256) void k_tw_split(const float *__restrict__ X, i
     }
 }
 
+// Up to kPackFeat features: one thread per point of the padded panels (otherwise as
+// k_tw_split; the norm in k_tw_norms' order).
+__global__ __launch_bounds__(256) void k_tw_pack(const float *__restrict__ X, int64_t n, int32_t d, int64_t np,
+                                                 uint4 *__restrict__ P, float *__restrict__ nx,
+                                                 unsigned *__restrict__ flags)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= np) return;
+    const int r = (int)(i % kPanel);
+    float sq = 0.0f;
+#pragma unroll
+    for (int u = 0; u < kPackUnits; ++u) {
+        float v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            v[q] = i < n && 4 * u + q < d ? X[i * d + 4 * u + q] : 0.0f;
+            sq = fmaf(v[q], v[q], sq);
+        }
+        P[i * kPackUnits + pack_slot(u, r)] =
+            make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
+    }
+    nx[i] = i < n ? sq : INFINITY;
+    if (i < n && !(sq <= kPairNormMax)) atomicOr(flags, (unsigned)kTrustFarPoint);
+}
+
 // the next float above x (x itself where it is not finite)
 __device__ __forceinline__ float next_up(float x)
 {
@@ -526,7 +565,7 @@ __device__ __forceinline__ uint32_t push_less(uint32_t bits, float x, float t)
     return __builtin_amdgcn_alignbit(bits, __float_as_uint(x - t), 31);
 }
 
-template <int KS>
+template <int KS, bool PACK>
 __global__ __launch_bounds__(kPairThreads, 2) void k_tw_rank_pairs(const uint4 *__restrict__ P, int64_t n, int64_t np,
                                                           int32_t steps, int64_t span, int32_t k,
                                                           const float *__restrict__ nx,
@@ -535,7 +574,7 @@ __global__ __launch_bounds__(kPairThreads, 2) void k_tw_rank_pairs(const uint4 *
                                                           const unsigned *__restrict__ flags)
 {
     if (*flags & kTrustFarPoint) return;   // the caller takes k_tw_rank
-    constexpr int kOperand = kPanel * kUnits;                       // units per panel and step
+    constexpr int kOperand = kPanel * (PACK ? kPackUnits : kUnits); // units per panel and step
     constexpr int kTrBytes = 4 * kTrCols * kTrStride * 4;           // transposed pieces of the four waves
     constexpr int kThBytes = 4 * KS * kPanel * 4;                   // thresholds and neighbours, rows' and columns'
     constexpr int kOpBytes = 2 * kOperand * 16 > kTrBytes + kThBytes ? 2 * kOperand * 16 : kTrBytes + kThBytes;
@@ -568,7 +607,7 @@ __global__ __launch_bounds__(kPairThreads, 2) void k_tw_rank_pairs(const uint4 *
     // units of this lane's fragments: point li of a 16-point group, features 8 g .. 8 g + 7
     int off[3];
 #pragma unroll
-    for (int p = 0; p < 3; ++p) off[p] = li * kUnits + unit_slot(4 * p + g, li);
+    for (int p = 0; p < 3; ++p) off[p] = PACK ? li * kPackUnits + pack_slot(g, li) : li * kUnits + unit_slot(4 * p + g, li);
     const v4u *const rowsP = reinterpret_cast<const v4u *>(P) + I * steps * kOperand + tid;
 
     for (int64_t J = J0; J < J1; ++J) {
@@ -603,26 +642,58 @@ __global__ __launch_bounds__(kPairThreads, 2) void k_tw_rank_pairs(const uint4 *
                 ra[v] = rowsP[next + v * 256];
                 ca[v] = colsP[next + v * 256];
             }
-            v8bf a[4][3];
+            if constexpr (PACK) {
+                float4 a[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+                for (int t = 0; t < 4; ++t)
+                    a[t] = __builtin_bit_cast(float4, s_op[(wr + 16 * t) * kPackUnits + off[0]]);
 #pragma unroll
-                for (int p = 0; p < 3; ++p)
-                    a[t][p] = __builtin_bit_cast(v8bf, s_op[(wr + 16 * t) * kUnits + off[p]]);
+                for (int u = 0; u < 4; ++u) {
+                    const float4 b = __builtin_bit_cast(float4, s_op[kOperand + (wc + 16 * u) * kPackUnits + off[0]]);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                v8bf b[3];
+                    for (int t = 0; t < 4; ++t) {
+                        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].x, b.x, acc[t][u], 0, 0, 0);
+                        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].y, b.y, acc[t][u], 0, 0, 0);
+                        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].z, b.z, acc[t][u], 0, 0, 0);
+                        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].w, b.w, acc[t][u], 0, 0, 0);
+                    }
+                }
+            } else {
+                // two rows of result tiles at a time, each pair of tiles finished before
+                // the next (the scheduler would keep all of them open, and spill)
 #pragma unroll
-                for (int p = 0; p < 3; ++p)
-                    b[p] = __builtin_bit_cast(v8bf, s_op[kOperand + (wc + 16 * u) * kUnits + off[p]]);
-                // smallest products first; the four result tiles in turn, so that
-                // no instruction waits for the one before it
-                constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};
+                for (int t0 = 0; t0 < 4; t0 += 2) {
+                    v8bf a[2][3];
 #pragma unroll
-                for (int q = 0; q < 6; ++q)
+                    for (int t = 0; t < 2; ++t)
 #pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t][kA[q]], b[kB[q]], acc[t][u], 0, 0, 0);
+                        for (int p = 0; p < 3; ++p)
+                            a[t][p] = __builtin_bit_cast(v8bf, s_op[(wr + 16 * (t0 + t)) * kUnits + off[p]]);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        v8bf b[3];
+#pragma unroll
+                        for (int p = 0; p < 3; ++p)
+                            b[p] = __builtin_bit_cast(v8bf, s_op[kOperand + (wc + 16 * u) * kUnits + off[p]]);
+                        // smallest products first; the two tiles in turn
+                        constexpr int kA[5] = {2, 0, 1, 1, 0}, kB[5] = {0, 2, 1, 0, 1};
+                        const v4f zero = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+                        v4f rest[2] = {zero, zero}, lead[2];
+#pragma unroll
+                        for (int q = 0; q < 5; ++q)
+#pragma unroll
+                            for (int t = 0; t < 2; ++t)
+                                rest[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t][kA[q]], b[kB[q]], rest[t], 0, 0, 0);
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) {
+                            acc[t0 + t][u] += rest[t];
+                            lead[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t][0], b[0], zero, 0, 0, 0);
+                        }
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) acc[t0 + t][u] += lead[t];
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
             }
         }
         // distances: lane (g, li) holds row 16 t + 4 g + e, column 16 u + li
@@ -768,17 +839,17 @@ int64_t trust_padded(int64_t n) { return (n + kPanel - 1) / kPanel * kPanel; }
 size_t trust_split_bytes(int64_t n, int32_t d)
 {
     const int64_t steps = ((int64_t)d + kFeat - 1) / kFeat;
-    const int64_t bytes = trust_padded(n) * steps * kUnits * 16;
+    const int64_t bytes = trust_padded(n) * (d <= kPackFeat ? kPackUnits : steps * kUnits) * 16;
     return bytes <= kTrustSplitBytes ? (size_t)bytes : 0;
 }
 
-template <int KS>
+template <int KS, bool PACK>
 static void launch_pairs(const uint4 *P, int64_t n, int64_t np, int32_t steps, int32_t k, const float *nx,
                          const int32_t *nbr, const float *thr, int32_t *cnt, const unsigned *flags, hipStream_t s)
 {
     const int64_t panels = np / kPanel;
     const int64_t span = panel_span(panels);
-    hipLaunchKernelGGL((k_tw_rank_pairs<KS>), dim3((unsigned)panel_blocks(panels, span)), dim3(kPairThreads), 0, s, P, n, np,
+    hipLaunchKernelGGL((k_tw_rank_pairs<KS, PACK>), dim3((unsigned)panel_blocks(panels, span)), dim3(kPairThreads), 0, s, P, n, np,
                        steps, span, k, nx, nbr, thr, cnt, flags);
 }
 
@@ -796,7 +867,11 @@ hipError_t launch_trustworthiness(const float *X, int64_t n, int32_t d, const fl
 {
     const int64_t np = trust_padded(n);
     const int32_t steps = (d + kFeat - 1) / kFeat;
-    if (split)
+    const bool pack = d <= kPackFeat;
+    if (split && pack)
+        hipLaunchKernelGGL(k_tw_pack, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s, X, n, d, np,
+                           static_cast<uint4 *>(split), nx, flags);
+    else if (split)
         hipLaunchKernelGGL(k_tw_split, dim3((unsigned)(np / 4)), dim3(256), 0, s, X, n, d, steps,
                            static_cast<uint4 *>(split), nx, flags);
     else
@@ -818,10 +893,9 @@ hipError_t launch_trustworthiness(const float *X, int64_t n, int32_t d, const fl
                        s, cnt, nk);
     if (split) {
         const uint4 *const P = static_cast<const uint4 *>(split);
-        if (k <= 8)
-            launch_pairs<8>(P, n, np, steps, k, nx, nbr, thr, cnt, flags, s);
-        else
-            launch_pairs<kCountPiece>(P, n, np, steps, k, nx, nbr, thr, cnt, flags, s);
+        auto *const pairs = k <= 8 ? (pack ? launch_pairs<8, true> : launch_pairs<8, false>)
+                                   : (pack ? launch_pairs<kCountPiece, true> : launch_pairs<kCountPiece, false>);
+        pairs(P, n, np, steps, k, nx, nbr, thr, cnt, flags, s);
     } else if (k <= 16) {
         launch_rank<16, 4>(X, n, d, k, np, nx, nbr, thr, cnt, s);
     } else if (k <= 32) {

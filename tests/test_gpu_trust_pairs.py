@@ -146,3 +146,56 @@ def test_far_and_non_finite_points(monkeypatch, n, d, k, what):
         ok = X.copy()
         ok[~(np.abs(X) < 1e10).all(axis=1)] = 50.0
         assert abs(pairs - O.trustworthiness(ok, Y, k)) <= 10.0 / n
+
+
+@pytest.mark.parametrize("n,d,dim,k", [(700, 1, 1, 5), (1003, 2, 2, 15), (900, 3, 3, 30), (1500, 8, 2, 15), (1201, 15, 4, 8),
+                                       (2000, 16, 2, 16)])
+@pytest.mark.parametrize("scaled", [False, True])
+def test_few_features_equal_the_fp32_kernels(monkeypatch, n, d, dim, k, scaled):
+    """Up to 16 features the pairs' products are the fp32 kernels', term by term."""
+    rng = np.random.default_rng(n + d)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    if scaled:
+        X *= (10.0 ** rng.uniform(-3, 3, d)).astype(np.float32)
+    Y = np.resize(X, (n, dim)) + (0.1 * rng.standard_normal((n, dim))).astype(np.float32)
+    case(f"few features n {n} d {d} dim {dim} k {k} scaled {scaled}")
+    pairs, plain = _both(monkeypatch, X, Y, k)
+    assert pairs == plain
+
+
+@pytest.mark.parametrize("d", [17, 32, 33, 300, 784])
+def test_ranks_are_not_biased(monkeypatch, d):
+    """Sums cut off toward zero make every dot product of non-negative features too
+    small, and T too large, at every draw.  Over eight draws of image-like points the
+    mean of T's distance from 64-bit sums is within four of its standard errors of
+    zero, or as near as the fp32 kernels'."""
+    import torch
+
+    n, k = 6000, 15
+    off = []
+    for seed in range(8):
+        g = torch.Generator(device="cuda").manual_seed(100 * d + seed)
+        z = torch.randn(n, 2, generator=g, device="cuda")
+        w = torch.randn(2, d, generator=g, device="cuda")
+        x = (0.4 + 0.5 * torch.sin(0.3 * z @ w + 6.0 * torch.rand(d, generator=g, device="cuda"))
+             + 0.05 * torch.randn(n, d, generator=g, device="cuda")).clamp(0, 1).contiguous()
+        y = (z + 0.05 * torch.randn(n, 2, generator=g, device="cuda")).contiguous()
+        case(f"bias d {d} seed {seed}")
+        t = U.umap_trustworthiness(x, y, k)
+        x64, y64 = x.double(), y.double()
+        nx, own = (x64 * x64).sum(1), torch.arange(n, device="cuda")
+        dy = (y64[:, None, 0] - y64[None, :, 0]) ** 2 + (y64[:, None, 1] - y64[None, :, 1]) ** 2
+        dy[own, own] = np.inf
+        nbr = torch.topk(dy, k, dim=1, largest=False).indices
+        dx = nx[:, None] + nx[None, :] - 2.0 * (x64 @ x64.T.contiguous())
+        dx[own, own] = np.inf
+        thr = torch.gather(dx, 1, nbr)
+        pen = sum(int(((dx < thr[:, q, None]).sum(1) + 1 - k).clamp_min(0).sum()) for q in range(k))
+        unit = 2.0 / (n * k * (2.0 * n - 3.0 * k - 1.0))
+        monkeypatch.setenv("UMAP_LAYOUT_FAULT", "split")
+        plain = U.umap_trustworthiness(x, y, k)
+        monkeypatch.delenv("UMAP_LAYOUT_FAULT")
+        off.append(((t - (1.0 - unit * pen)) / unit, (plain - (1.0 - unit * pen)) / unit))
+    pairs, plain = np.array(off).T
+    print("units off:", np.round(pairs), "fp32 kernels", np.round(plain), flush=True)
+    assert abs(pairs.mean()) <= abs(plain.mean()) + 4.0 * pairs.std(ddof=1) / np.sqrt(pairs.size)
