@@ -433,7 +433,7 @@ static void launch_rank(const float *X, int64_t n, int32_t d, int32_t k, int64_t
 // scales 1e-3 .. 1e3 3.6e-8 against 4.7e-8).  Fewer features of different scales would
 // lose (8: 3.9e-8 against 3.7e-8): up to kPackFeat the points stay fp32 and the products
 // are the fp32 instructions', in k_tw_rank's order.
-// 70,000 x 784, k = 15: @@ ms where k_tw_rank takes 85.0.  The matrix cores are busy a
+// 70,000 x 784, k = 15: 29.5 ms where k_tw_rank takes 85.0.  The matrix cores are busy a
 // third of the time, the VALU (counting) a quarter, LDS two fifths: two waves per SIMD
 // (registers) do not cover the operands' way from the Infinity Cache.
 //
