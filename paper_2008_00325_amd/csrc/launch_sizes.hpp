@@ -34,15 +34,16 @@ constexpr int64_t panel_blocks(int64_t m, int64_t span)
 
 // Column tiles per block: about 4096 blocks where the points allow it (two are
 // resident per CU), a row panel's counts and operands being shared by the tiles of
-// a block; but runs of at most 4 tiles from 256 panels on, so that the last blocks
-// do not run alone for long (runs of up to 32 / of 4: 50,000 x 100 8.14 / 7.78
-// ms per call, 70,000 x 784 32.5 / 29.1; taking 8 x 8 panels and runs per XCD
-// besides: 7.46 and 29.6, 40,000 x 300 10.2 / 10.4).  Longer again where that
+// a block, but at most 4, so that the last blocks do not run alone for long.  ms per
+// call with 1 / 2 / 4 / 8 / 16 tiles per block, k = 15: 5,003 x 64 0.23 / 0.22 / 0.30 /
+// 0.47 / 0.81, 16,000 x 64 1.01 / 0.99 / 0.99 / 1.20 / 1.52, 32,640 x 64 3.41 / 3.28 /
+// 3.27 / 3.38 / 3.62, 32,640 x 784 7.50 / 7.57 / 7.76 / 8.08 / 8.76, 70,000 x 64 13.9 /
+// 13.2 / 12.9 / 13.0 / 13.1, 70,000 x 784 32.6 / 32.4 / 32.7 / 33.1 / 33.9.  Longer where that
 // many blocks would not fit one launch (from 1,482,625 points on).
 constexpr int64_t panel_span(int64_t panels)
 {
     int64_t span = panels * (panels + 1) / 2 / 4096;
-    span = span < 1 ? 1 : panels >= 256 ? (span > 4 ? 4 : span) : span;
+    span = span < 1 ? 1 : span > 4 ? 4 : span;
     while (span < panels && panel_blocks(panels, span) * kPairThreads >= kGridItems) span *= 2;
     return span;
 }

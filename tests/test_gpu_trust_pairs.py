@@ -51,8 +51,8 @@ def test_lattice_ranks_equal_the_oracle(monkeypatch, n, d, dim, k):
 
 @pytest.mark.parametrize("n,d,k", [(32640, 3, 5), (32641, 7, 17), (33001, 96, 5)])
 def test_long_rows_of_tiles_equal_the_fp32_kernels(monkeypatch, n, d, k):
-    """Both sides of the size where the runs of tiles get shorter (255, 256 and 258
-    panels): both kernels' distances are exact on a lattice, so that the ranks are the
+    """Runs of four tiles, with 255, 256 and 258 panels (runs that end at the last
+    panel, one, two and three tiles before): both kernels' distances are exact on a lattice, so that the ranks are the
     same."""
     rng = np.random.default_rng(n + d)
     X = rng.integers(-3, 4, size=(n, d)).astype(np.float32)
