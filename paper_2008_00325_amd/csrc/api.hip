@@ -18,6 +18,7 @@
 #include "umap_layout.h"
 #include "device_memory.hpp"
 #include "internal.hpp"
+#include "launch_sizes.hpp"
 
 namespace {
 
@@ -206,6 +207,7 @@ struct umap_layout {
     int32_t *col = nullptr;
     int16_t *col16 = nullptr;               // col - row in 16 bits (a fit whose deltas all fit)
     bool col16_ok = false;
+    bool halo = false;                      // enough tails within kHalo of their rows
     float *eps = nullptr;
     int32_t *part = nullptr;
     ul::WaveDesc *desc = nullptr;
@@ -423,11 +425,8 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
         if (h->n_waves < 1) h->n_waves = 1;
         if (h->n_waves > max_waves) throw HipFailure{hipErrorInvalidValue, "wave count exceeds the arena"};
         UL_HIP(ul::launch_partition(h->row_ptr, 0, n, dim, cost, h->part, h->desc, h->n_waves, h->head, stream));
-        // a fit's tails are read as 16-bit offsets from their rows where they all
-        // fit and at least half lie within the halo that the kernels of 1-2
-        // components stage with them (a shuffled graph gets nothing from the
-        // halo's LDS)
-        h->col16_ok = !table && kept > 0 && !(S.flags & ul::kWide) && 2 * (int64_t)S.near >= kept;
+        h->col16_ok = !table && kept > 0 && !(S.flags & ul::kWide);
+        h->halo = !table && ul::halo_pays((int64_t)S.near, kept, n, dim);
         float ms = 0;
         UL_HIP(hipEventElapsedTime(&ms, h->ev[0], h->ev[1]));
         h->st.prep_ms = ms;
@@ -467,7 +466,7 @@ int run_epochs_impl(umap_layout *h, uint64_t seed, int32_t first, int32_t last, 
                     h->n_waves,     1 << h->lg_phases,       h->lg_phases, h->rec,
                     h->rec_count,   h->overflow,  fault_records() ? (int64_t)0 : (int64_t)-1,
                     h->delta,       h->col16_ok ? h->col16 : nullptr,
-                    one_launch ? 1 : 0};
+                    one_launch ? 1 : 0, h->halo ? 1 : 0};
     // the wave kernels store a sample's offset inside its table range and a
     // sampled edge's offset inside its wave in 24 bits (a wave holds fewer
     // than kWaveCost + max_degree edges), and address a wave's record slots

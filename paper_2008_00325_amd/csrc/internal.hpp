@@ -132,8 +132,9 @@ struct WaveGraph {
     unsigned *overflow;       // set when a record did not fit its range slot
     int64_t cap_limit;        // < 0: none; else record slots per range are cut to it (failure injection)
     long long *delta;         // n x dim fixed-point partial sums between launches
-    const int16_t *col16;     // col - row in 16 bits (a fit whose tails all fit and mostly lie near), else null
+    const int16_t *col16;     // col - row in 16 bits (a fit whose tails all fit), else null
     int32_t one_launch;       // the draw launch applies the negative samples itself (no records, no range launches)
+    int32_t halo;             // rows around a wave's own are staged for the tails (see halo_pays)
 };
 
 // First record slot of wave w (edges from e0): every wave gets

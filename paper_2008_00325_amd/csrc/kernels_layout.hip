@@ -204,7 +204,8 @@ __device__ __forceinline__ uint32_t range_base(uint32_t p, int32_t lg, uint32_t 
 // FIT: the tails and negatives index the moving layout itself (a fit: near
 // tails from LDS, self draws skipped, both shares of the attraction); else they
 // index a frozen table (a transform).  C16: the tails are read as 16-bit
-// offsets from their rows (G.col16), 2 bytes per edge instead of 4.  FUSED:
+// offsets from their rows (G.col16), 2 bytes per edge instead of 4.  HALO: rows
+// around the wave's own are staged for the tails that lie there (G.halo).  FUSED:
 // the epoch is one launch (G.one_launch) and each negative's repulsion is
 // applied here; a separate instance, so that the record-filing kernel of
 // several ranges carries none of its registers (at 8 components the draw
@@ -213,15 +214,14 @@ __device__ __forceinline__ uint32_t range_base(uint32_t p, int32_t lg, uint32_t 
 // sums take one add per component and edge; one per component and term made
 // an epoch of 50K points in 10 components 65 us (28 now), of 100K points in 3
 // components 40 us (29 now), while at 2 components the gathers bound it.
-template <int DIM, int NQ, bool FIT, bool C16, bool FUSED>
+template <int DIM, int NQ, bool FIT, bool C16, bool HALO, bool FUSED>
 __global__ __launch_bounds__(256) void k_epoch_draw(EpochArgs A, WaveGraph G)
 {
     constexpr int CAP = rows_cap(DIM);
     constexpr int S = lds_stride<DIM>();
     __shared__ long long s_acc[kWavesPerBlock][CAP * S];
-    // a halo only where most tails lie close to their rows (the C16 graphs); a
-    // transform's tails index the frozen table
-    constexpr int kHaloW = FIT && C16 ? draw_halo<DIM>() : 0;
+    // a transform's tails index the frozen table: no halo
+    constexpr int kHaloW = FIT && HALO ? draw_halo<DIM>() : 0;
     __shared__ float s_y[kWavesPerBlock][(CAP + 2 * kHaloW) * S];   // the wave's rows of E_n and halos
     __shared__ uint32_t s_rec[FUSED ? 1 : kWavesPerBlock][FUSED ? 1 : kMaxPhases];
     __shared__ uint2 s_q[kWavesPerBlock][kQueue];
@@ -595,13 +595,26 @@ int32_t phase_log2(int64_t n, int32_t dim)
     return lg_bytes < lg_rows ? lg_bytes : lg_rows;
 }
 
-template <int DIM, int NQ, bool FIT, bool C16>
+template <int DIM, int NQ, bool FIT, bool C16, bool HALO>
 static void launch_draw(int64_t grid, const EpochArgs &A, const WaveGraph &G, hipStream_t s)
 {
-    if (G.one_launch)
-        hipLaunchKernelGGL((k_epoch_draw<DIM, NQ, FIT, C16, true>), dim3((unsigned)grid), dim3(256), 0, s, A, G);
-    else
-        hipLaunchKernelGGL((k_epoch_draw<DIM, NQ, FIT, C16, false>), dim3((unsigned)grid), dim3(256), 0, s, A, G);
+    auto *const draw = G.one_launch ? k_epoch_draw<DIM, NQ, FIT, C16, HALO, true>
+                                    : k_epoch_draw<DIM, NQ, FIT, C16, HALO, false>;
+    hipLaunchKernelGGL(draw, dim3((unsigned)grid), dim3(256), 0, s, A, G);
+}
+
+// The 16-bit tail stream is compiled for the common widths (1-4 components), the
+// halo where there is one (1-2).
+template <int DIM, int NQ>
+static void launch_draw(int64_t grid, const EpochArgs &A, const WaveGraph &G, hipStream_t s)
+{
+    constexpr bool kTails16 = DIM <= 4, kHalos = draw_halo<DIM>() > 0;
+    const bool c16 = kTails16 && G.col16, halo = kHalos && G.halo;
+    if (!A.same_table) launch_draw<DIM, NQ, false, false, false>(grid, A, G, s);
+    else if (c16 && halo) launch_draw<DIM, NQ, true, kTails16, kHalos>(grid, A, G, s);
+    else if (c16) launch_draw<DIM, NQ, true, kTails16, false>(grid, A, G, s);
+    else if (halo) launch_draw<DIM, NQ, true, false, kHalos>(grid, A, G, s);
+    else launch_draw<DIM, NQ, true, false, false>(grid, A, G, s);
 }
 
 template <int DIM, int NQ>
@@ -615,19 +628,7 @@ static hipError_t launch_epoch_dq(int kernel, const EpochArgs &A, const WaveGrap
     }
     const int64_t blocks = (G.n_waves + kWavesPerBlock - 1) / kWavesPerBlock;
     const int64_t grid = ((blocks + 7) / 8) * 8;
-    // the 16-bit tail stream is compiled for the common widths (1-4 components)
-    if constexpr (DIM <= 4) {
-        if (A.same_table && G.col16) {
-            launch_draw<DIM, NQ, true, true>(grid, A, G, s);
-            for (int32_t p = 0; !G.one_launch && p < G.n_phases; ++p)
-                hipLaunchKernelGGL((k_epoch_repulse<DIM>), dim3((unsigned)grid), dim3(256), 0, s, A, G, p);
-            return hipGetLastError();
-        }
-    }
-    if (A.same_table)
-        launch_draw<DIM, NQ, true, false>(grid, A, G, s);
-    else
-        launch_draw<DIM, NQ, false, false>(grid, A, G, s);
+    launch_draw<DIM, NQ>(grid, A, G, s);
     for (int32_t p = 0; !G.one_launch && p < G.n_phases; ++p)
         hipLaunchKernelGGL((k_epoch_repulse<DIM>), dim3((unsigned)grid), dim3(256), 0, s, A, G, p);
     return hipGetLastError();

@@ -48,4 +48,17 @@ constexpr int64_t panel_span(int64_t panels)
     return span;
 }
 
+// ---- draw kernel at 1-2 components ----
+// Whether the 64 rows on each side of a wave's own are staged for the tails that lie
+// there: `near` of `kept` tails are within 64 rows of theirs.  A staged row is an LDS
+// read instead of a gather, for more LDS per workgroup.  us per epoch at 2 components
+// without / with (k = 15 graphs in local order, a share of the tails anywhere): 1M
+// vertices, all near 574 / 567, 1 % far 589 / 583, 50 % 670 / 657, 90 % 722 / 715, 95 %
+// 726 / 723, 98 % 726 / 726; 500,000 201 / 197, 50 % far 229 / 225; 140,000 to 300,000
+// the same; 40,000 18.9 / 19.6, 20,000 11.1 / 11.7 (there the table is in every L2).
+constexpr bool halo_pays(int64_t near, int64_t kept, int64_t n, int32_t dim)
+{
+    return kept > 0 && 16 * near >= kept && n * dim * (int64_t)sizeof(float) >= (int64_t)1 << 20;
+}
+
 }  // namespace ul

@@ -16,6 +16,11 @@ int main()
         } else if (!strcmp(what, "grid")) {   // blocks of 256 threads -> the grid's dimensions
             const ul::Grid2 g = ul::grid2(x, 256);
             printf("%" PRIu32 " %" PRIu32 "\n", g.x, g.y);
+        } else if (!strcmp(what, "halo")) {   // near, kept, n, components -> whether a halo is staged
+            int64_t kept, n;
+            int32_t dim;
+            if (scanf("%" SCNd64 " %" SCNd64 " %" SCNd32, &kept, &n, &dim) != 3) return 1;
+            printf("%d\n", ul::halo_pays(x, kept, n, dim) ? 1 : 0);
         } else {
             return 1;
         }

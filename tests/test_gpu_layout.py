@@ -464,9 +464,9 @@ def test_single_epoch_dims_and_rates(dim, R, N):
 @pytest.mark.parametrize("dim", list(range(1, 17)))
 def test_every_width_both_kernels(dim):
     # every embedding width on a locally ordered graph (all tails within +-64
-    # rows): the wave kernels stage halo rows at 1-2 components and read other
-    # tails from global memory, and pad the LDS rows of even widths from 4 on;
-    # one epoch of each kernel must match the oracle and each other bit for bit
+    # rows; too small for halo rows, which test_tail_reading_bits covers): 16-bit
+    # tails at 1-4 components, padded LDS rows at even widths from 4 on; one
+    # epoch of each kernel must match the oracle and each other bit for bit
     n, N, R = 4001, 60, 5
     print(f"[gpu case] width {dim}", flush=True)
     ids, dist = synth.window_knn(n, 15, synth.cluster_bounds(n, 2), seed=40 + dim)

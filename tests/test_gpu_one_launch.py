@@ -101,3 +101,28 @@ def test_row_ranges_on_both_sides_of_the_work_line():
             assert np.array_equal(got[r0:r1].view(np.uint32), full[r0:r1].view(np.uint32))
             assert np.array_equal(got[:r0].view(np.uint32), E[:r0].view(np.uint32))
             assert np.array_equal(got[r1:].view(np.uint32), E[r1:].view(np.uint32))
+
+
+def _banded(n, per_row, reach, far, seed):
+    """Tails within `reach` rows of their rows, `far` random edges besides."""
+    rng = np.random.default_rng(seed)
+    i = np.repeat(np.arange(n, dtype=np.int64), per_row)
+    j = i + rng.integers(1, reach + 1, i.size)
+    i, j = i[j < n], j[j < n]
+    e = np.sort(rng.integers(0, n, size=(2, far)), axis=0)
+    key = np.unique(np.concatenate([i * n + j, (e[0] * n + e[1])[e[0] != e[1]]]))
+    lo, hi = (key // n).astype(np.int32), (key % n).astype(np.int32)
+    v = rng.uniform(0.05, 1.0, lo.size).astype(np.float32)
+    return np.r_[lo, hi], np.r_[hi, lo], np.r_[v, v]
+
+
+# every way the draw kernel reads a fit's tails, in one launch and with records (from 786,433 x 2 on and 27M terms)
+@pytest.mark.parametrize("n,per_row", [(300_001, 2), (800_003, 4)])
+@pytest.mark.parametrize("reach,far,what", [(64, 0, "16-bit tails and halo"), (64, 1, "halo, one far edge"),
+                                            (3_000, 0, "16-bit tails, no halo"), (200_000, 0, "neither")])
+@pytest.mark.parametrize("dim", [1, 2, 3])
+def test_tail_reading_bits(n, per_row, reach, far, what, dim):
+    r, c, v = _banded(n, per_row, reach, 40 * far, seed=n % 1000 + reach)
+    N = 20
+    with U.umap_layout_create(n, dim, r, c, v, A_DEF, B_DEF, N, 5) as h:
+        _both_kernels(h, synth.embedding_state(n, dim, 9, 10.0), N, f"{what}: {n} x {dim}")

@@ -47,3 +47,13 @@ def test_row_blocks_fit_a_launch(sizes):
         assert x * 256 < GRID_ITEMS and y < 2**16
         assert -(-n // 32) <= x * y < -(-n // 32) + y
         assert (y == 1) == (n <= 2**29 - 32)
+
+
+def test_halo_rule(sizes):
+    """A far edge or a tenth of them does not cost a large local graph its halo."""
+    kept = 26_700_000
+    asked = {(kept, kept, 1_000_000, 2): 1, (kept - 2, kept, 1_000_000, 2): 1, (9 * kept // 10, kept, 1_000_000, 1): 1,
+             (kept // 10, kept, 1_000_000, 2): 1, (kept // 17, kept, 1_000_000, 2): 0, (0, kept, 1_000_000, 2): 0,
+             (kept, kept, 131_072, 2): 1, (kept, kept, 131_071, 2): 0, (0, 0, 1_000_000, 2): 0}
+    got = sizes([f"halo {near} {k} {n} {dim}" for near, k, n, dim in asked])
+    assert [g for (g,) in got] == list(asked.values())
