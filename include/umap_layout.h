@@ -196,11 +196,12 @@ int umap_layout_epoch_ms(const umap_layout *h, float *out_ms, int32_t capacity);
  * while the handle uses it. */
 int umap_layout_set_stream(umap_layout *h, void *stream);
 
-/* umap_layout_destroy -- give back all device memory of the handle (waits for
- * its stream).  NULL is a no-op.  The library keeps freed blocks of handles and
- * of its blocking calls' scratch for later ones: at most 4 GiB per process, the
- * ones not needed during the last 64 allocations freed, all of them when an
- * allocation fails. */
+/* umap_layout_destroy -- end the handle (waits for its stream).  The library keeps
+ * freed blocks of handles and of its blocking calls' scratch for later ones: at
+ * most 4 GiB per process, the ones not needed during the last 64 allocations
+ * freed, all of them when an allocation fails.  With NULL there is no handle to
+ * end, and all kept blocks are freed: a program that is done with layouts for a
+ * while gives the memory to others so. */
 void umap_layout_destroy(umap_layout *h);
 
 /* umap_layout_last_error -- message of the last failing call on this thread

@@ -104,7 +104,7 @@ class Scratch {
 public:
     explicit Scratch(hipStream_t s) : stream_(s) {}
     Scratch(size_t bytes, hipStream_t s) : stream_(s) { UL_HIP(take(bytes)); }
-    hipError_t take(size_t bytes) { return ul::take_block(bytes, &block_); }
+    hipError_t take(size_t bytes) { return ul::take_block(bytes, ul::Held::kByCall, &block_); }
     ~Scratch() { give(); }
     Scratch(const Scratch &) = delete;
     Scratch &operator=(const Scratch &) = delete;
@@ -303,7 +303,7 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
                        need<int32_t>((size_t)n_phases * max_waves) + need<long long>(nd) + need<unsigned>(1) +
                        need<float>(nd) + need<float>(table_elems);
         if (fault_alloc()) throw HipFailure{hipErrorOutOfMemory, "hipMalloc(arena) [injected]"};
-        UL_HIP(ul::take_block(bytes, &h->arena));
+        UL_HIP(ul::take_block(bytes, ul::Held::kByHandle, &h->arena));
         Carver cv{static_cast<char *>(h->arena.ptr)};
         h->row_ptr = cv.take<int64_t>(n + 1);
         h->col = cv.take<int32_t>(nnz);
@@ -904,7 +904,10 @@ int umap_layout_set_mode(umap_layout *h, int32_t mode)
 
 void umap_layout_destroy(umap_layout *h)
 {
-    if (!h) return;
+    if (!h) {
+        ul::free_kept_blocks();
+        return;
+    }
     (void)hipSetDevice(h->device);
     h->release();
     delete h;

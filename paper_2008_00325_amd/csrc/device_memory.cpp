@@ -34,50 +34,65 @@ void free_block(DeviceBlock *b)
     *b = DeviceBlock{};
 }
 
-void drop(Store &s, size_t i)
+// Takes block i out of the store (the mutex is held).
+DeviceBlock remove(Store &s, size_t i)
 {
-    s.bytes -= s.kept[i].block.bytes;
-    free_block(&s.kept[i].block);
+    const DeviceBlock b = s.kept[i].block;
+    s.bytes -= b.bytes;
     s.kept.erase(s.kept.begin() + (ptrdiff_t)i);
+    return b;
+}
+
+// Frees kept blocks for which `which(store, block)` holds, one at a time and not under
+// the mutex: freeing can wait for the device, and other threads' calls with it.
+template <typename Which>
+void free_where(Which which)
+{
+    Store &s = store();
+    for (;;) {
+        DeviceBlock b;
+        {
+            std::lock_guard<std::mutex> lock(s.mu);
+            for (size_t i = 0; i < s.kept.size() && !b.ptr; ++i)
+                if (which(s, s.kept[i])) b = remove(s, i);
+        }
+        if (!b.ptr) return;
+        free_block(&b);
+    }
 }
 
 }  // namespace
 
-hipError_t take_block(size_t bytes, DeviceBlock *out)
+hipError_t take_block(size_t bytes, Held held, DeviceBlock *out)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
+    // the smallest that fits: a handle's block not much larger than asked for, a
+    // call's at most twice that (small ones: any up to 1 MB)
+    size_t most = held == Held::kByHandle ? bytes + bytes / 8 : 2 * bytes;
+    if (most < (size_t)1 << 20) most = (size_t)1 << 20;
     Store &s = store();
     {
         std::lock_guard<std::mutex> lock(s.mu);
         ++s.takes;
-        // the smallest that fits, not more than twice what is asked for (small ones: any up to 1 MB)
         size_t best = s.kept.size();
         for (size_t i = 0; i < s.kept.size(); ++i) {
             const DeviceBlock &b = s.kept[i].block;
-            if (b.device != dev || b.bytes < bytes || (b.bytes > 2 * bytes && b.bytes > ((size_t)1 << 20))) continue;
+            if (b.device != dev || b.bytes < bytes || b.bytes > most) continue;
             if (best == s.kept.size() || b.bytes < s.kept[best].block.bytes) best = i;
         }
-        if (best < s.kept.size()) {
-            *out = s.kept[best].block;
-            s.bytes -= out->bytes;
-            s.kept.erase(s.kept.begin() + (ptrdiff_t)best);
-        }
-        for (size_t i = s.kept.size(); i-- > 0;)
-            if (s.takes - s.kept[i].given > kKeptTakes) drop(s, i);
-        if (out->ptr) return hipSuccess;
+        if (best < s.kept.size()) *out = remove(s, best);
     }
+    free_where([](const Store &st, const Kept &k) { return st.takes - k.given > kKeptTakes; });
+    if (out->ptr) return hipSuccess;
     DeviceBlock b;
     b.device = dev;
     b.bytes = bytes;
     e = hipMalloc(&b.ptr, bytes > 0 ? bytes : 1);
     if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
         (void)hipGetLastError();
-        {
-            std::lock_guard<std::mutex> lock(s.mu);
-            while (!s.kept.empty()) drop(s, s.kept.size() - 1);
-        }
+        free_kept_blocks();
         e = hipMalloc(&b.ptr, bytes > 0 ? bytes : 1);
     }
     if (e != hipSuccess) return e;
@@ -98,16 +113,21 @@ void give_block(DeviceBlock *b, bool reuse)
         return;
     }
     Store &s = store();
-    std::lock_guard<std::mutex> lock(s.mu);
     try {
+        std::lock_guard<std::mutex> lock(s.mu);
         s.kept.push_back(Kept{*b, s.takes});
+        s.bytes += b->bytes;
     } catch (...) {
         free_block(b);
         return;
     }
-    s.bytes += b->bytes;
     *b = DeviceBlock{};
-    while (s.bytes > kKeptBytes) drop(s, 0);   // the one handed back first
+    free_where([](const Store &st, const Kept &) { return st.bytes > kKeptBytes; });   // the one handed back first
+}
+
+void free_kept_blocks()
+{
+    free_where([](const Store &, const Kept &) { return true; });
 }
 
 }  // namespace ul

@@ -28,9 +28,14 @@ struct DeviceBlock {
 };
 constexpr size_t kHostBytes = 256;
 
-hipError_t take_block(size_t bytes, DeviceBlock *out);
+// A handle keeps its block for as long as the caller keeps the handle, so it gets
+// one at most an eighth larger than it needs; a call's scratch at most twice.
+enum class Held { kByHandle, kByCall };
+hipError_t take_block(size_t bytes, Held held, DeviceBlock *out);
 // Hands a block back: no work that uses it may be pending.  `reuse` false: the
 // device may be in an error state, the memory is freed.
 void give_block(DeviceBlock *b, bool reuse);
+// Frees every kept block.
+void free_kept_blocks();
 
 }  // namespace ul

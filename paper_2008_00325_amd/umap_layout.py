@@ -322,8 +322,12 @@ def umap_layout_set_rows(h: Handle, row_first: int, row_last: int) -> None:
     _check(lib().umap_layout_set_rows(h.ptr, row_first, row_last))
 
 
-def umap_layout_destroy(h: Handle) -> None:
-    h.close()
+def umap_layout_destroy(h: Handle | None) -> None:
+    """End the handle; with None free the device blocks that the library keeps."""
+    if h is None:
+        lib().umap_layout_destroy(None)
+    else:
+        h.close()
 
 
 def umap_layout_debug_active(h: Handle, epoch: int) -> np.ndarray:

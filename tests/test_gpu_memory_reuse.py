@@ -89,11 +89,46 @@ def test_kept_memory_is_bounded():
     assert sum(held) <= (4 << 30) + (64 << 20)
     # and given back as other sizes are asked for
     small = np.array([0, 1], np.int32)
-    for _ in range(40):
-        with U.umap_layout_create(2, 1, small, small[::-1].copy(), np.ones(2, np.float32), A_DEF, B_DEF, 3, 5):
-            pass
     before = torch.cuda.mem_get_info()[0]
     for _ in range(80):
         with U.umap_layout_create(2, 1, small, small[::-1].copy(), np.ones(2, np.float32), A_DEF, B_DEF, 3, 5):
             pass
-    assert torch.cuda.mem_get_info()[0] >= before
+    assert sum(held) > 1 << 30 and torch.cuda.mem_get_info()[0] >= before + sum(held) - (64 << 20)
+
+
+def _empty_handle(n):
+    empty = np.zeros(0, np.int32)
+    return U.umap_layout_create(n, 4, empty, empty, np.zeros(0, np.float32), A_DEF, B_DEF, 10, 5)
+
+
+def test_kept_memory_is_given_back_when_asked():
+    import torch
+
+    torch.cuda.synchronize()
+    U.umap_layout_destroy(None)
+    base = torch.cuda.mem_get_info()[0]
+    h = _empty_handle(15_000_000)
+    size = base - torch.cuda.mem_get_info()[0]
+    assert size > 1 << 30
+    h.close()
+    assert base - torch.cuda.mem_get_info()[0] >= size // 2   # kept
+    U.umap_layout_destroy(None)
+    assert base - torch.cuda.mem_get_info()[0] <= 64 << 20
+    with _empty_handle(1000) as h:                            # and the library goes on
+        U.umap_layout_init(h, 1)
+
+
+def test_a_handle_does_not_hold_much_more_than_it_needs():
+    import torch
+
+    torch.cuda.synchronize()
+    U.umap_layout_destroy(None)
+    base = torch.cuda.mem_get_info()[0]
+    with _empty_handle(6_000_000):
+        U.umap_layout_destroy(None)
+        need = base - torch.cuda.mem_get_info()[0]
+    U.umap_layout_destroy(None)
+    _empty_handle(10_000_000).close()                         # leaves a block of 10/6 of that
+    with _empty_handle(6_000_000):
+        U.umap_layout_destroy(None)
+        assert base - torch.cuda.mem_get_info()[0] <= need + need // 8 + (64 << 20)
