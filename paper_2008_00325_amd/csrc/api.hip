@@ -58,7 +58,8 @@ int hip_fail(const HipFailure &f)
 // launch of epoch K report a device error (nothing is launched in either
 // case); UMAP_LAYOUT_FAULT=records gives the wavefront kernel no record slots,
 // so every negative sample overflows and the epochs are redone;
-// UMAP_LAYOUT_FAULT=split gives the trustworthiness no room for the points' parts.
+// UMAP_LAYOUT_FAULT=split gives the trustworthiness no room for the points' parts;
+// UMAP_LAYOUT_FAULT=host makes the scratch's bookkeeping run out of host memory.
 bool fault_alloc()
 {
     const char *f = getenv("UMAP_LAYOUT_FAULT");
@@ -75,6 +76,12 @@ bool fault_split()
 {
     const char *f = getenv("UMAP_LAYOUT_FAULT");
     return f && strcmp(f, "split") == 0;
+}
+
+bool fault_host()
+{
+    const char *f = getenv("UMAP_LAYOUT_FAULT");
+    return f && strcmp(f, "host") == 0;
 }
 
 int fault_launch_epoch()
@@ -104,7 +111,11 @@ class Scratch {
 public:
     explicit Scratch(hipStream_t s) : stream_(s) {}
     Scratch(size_t bytes, hipStream_t s) : stream_(s) { UL_HIP(take(bytes)); }
-    hipError_t take(size_t bytes) { return ul::take_block(bytes, ul::Held::kByCall, &block_); }
+    hipError_t take(size_t bytes)
+    {
+        if (fault_host()) throw std::bad_alloc();
+        return ul::take_block(bytes, ul::Held::kByCall, &block_);
+    }
     ~Scratch() { give(); }
     Scratch(const Scratch &) = delete;
     Scratch &operator=(const Scratch &) = delete;
@@ -747,6 +758,8 @@ int umap_layout_get(const umap_layout *h, float *out)
         return UMAP_OK;
     } catch (const HipFailure &f) {
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
 }
 
@@ -761,6 +774,8 @@ int umap_layout_get_device(const umap_layout *h, float *dev_out)
         return UMAP_OK;
     } catch (const HipFailure &f) {
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
 }
 
@@ -775,6 +790,8 @@ int umap_layout_set_embedding(umap_layout *h, const float *host)
         return UMAP_OK;
     } catch (const HipFailure &f) {
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
 }
 
@@ -794,6 +811,8 @@ int umap_layout_get_graph(const umap_layout *h, int64_t *row_ptr, int32_t *col, 
         return UMAP_OK;
     } catch (const HipFailure &f) {
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
 }
 
@@ -826,6 +845,8 @@ int umap_layout_set_stream(umap_layout *h, void *stream)
         UL_HIP(hipStreamSynchronize(h->stream));
     } catch (const HipFailure &f) {
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
     h->stream = static_cast<hipStream_t>(stream);
     return UMAP_OK;
@@ -858,6 +879,8 @@ int umap_layout_epoch_ms(const umap_layout *h, float *out_ms, int32_t capacity)
         return h->timed;
     } catch (const HipFailure &f) {
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
 }
 
@@ -890,6 +913,8 @@ int umap_layout_set_rows(umap_layout *h, int64_t row_first, int64_t row_last)
         return UMAP_OK;
     } catch (const HipFailure &f) {
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
 }
 
@@ -904,12 +929,15 @@ int umap_layout_set_mode(umap_layout *h, int32_t mode)
 
 void umap_layout_destroy(umap_layout *h)
 {
-    if (!h) {
-        ul::free_kept_blocks();
-        return;
+    try {
+        if (!h) {
+            ul::free_kept_blocks();
+            return;
+        }
+        (void)hipSetDevice(h->device);
+        h->release();
+    } catch (...) {   // nothing to report it with
     }
-    (void)hipSetDevice(h->device);
-    h->release();
     delete h;
 }
 
@@ -931,6 +959,8 @@ int umap_layout_debug_active(const umap_layout *h, int32_t epoch, uint8_t *out)
     } catch (const HipFailure &f) {
         if (d) (void)hipFreeAsync(d, h->stream);
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
 }
 
@@ -956,6 +986,8 @@ int umap_layout_debug_negatives(const umap_layout *h, uint64_t seed, int32_t epo
     } catch (const HipFailure &f) {
         if (d) (void)hipFreeAsync(d, h->stream);
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
 }
 
@@ -985,6 +1017,8 @@ int umap_fuzzy_graph_device(int64_t n, int32_t k, const int32_t *knn_ids, const 
         return UMAP_OK;
     } catch (const HipFailure &f) {
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
 }
 
@@ -1112,6 +1146,8 @@ int umap_trustworthiness(const float *X, int64_t n, int32_t d, const float *Y, i
         return UMAP_OK;
     } catch (const HipFailure &f) {
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
 }
 
@@ -1123,6 +1159,8 @@ int umap_probe_copy(const void *src, void *dst, int64_t bytes, void *stream)
         return UMAP_OK;
     } catch (const HipFailure &f) {
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
 }
 
@@ -1139,6 +1177,8 @@ int umap_probe_gather(const void *table, int64_t entries, int64_t threads, int32
         return UMAP_OK;
     } catch (const HipFailure &f) {
         return hip_fail(f);
+    } catch (...) {
+        return fail(UMAP_E_NOMEM, "unexpected host failure");
     }
 }
 

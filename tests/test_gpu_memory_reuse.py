@@ -132,3 +132,22 @@ def test_a_handle_does_not_hold_much_more_than_it_needs():
     with _empty_handle(6_000_000):
         U.umap_layout_destroy(None)
         assert base - torch.cuda.mem_get_info()[0] <= need + need // 8 + (64 << 20)
+
+
+def test_host_failure_in_every_call_with_scratch(monkeypatch):
+    """A C++ exception that is no HIP failure ends as a status code."""
+    import torch
+
+    ids = torch.tensor([[1], [0]], dtype=torch.int32, device="cuda")
+    dist = torch.ones(2, 1, device="cuda")
+    i4, v4 = torch.empty(4, dtype=torch.int32, device="cuda"), torch.empty(4, device="cuda")
+    x = torch.randn(40, 3, device="cuda")
+    y = x[:, :2].contiguous()
+    monkeypatch.setenv("UMAP_LAYOUT_FAULT", "host")
+    for call in (lambda: U.umap_fuzzy_graph_device(2, 1, ids, dist, i4, i4, v4), lambda: U.umap_trustworthiness(x, y, 3),
+                 lambda: _empty_handle(10)):
+        with pytest.raises(U.UmapLayoutError) as ei:
+            call()
+        assert ei.value.code == U.UMAP_E_NOMEM
+    monkeypatch.delenv("UMAP_LAYOUT_FAULT")
+    assert 0.0 <= U.umap_trustworthiness(x, y, 3) <= 1.0
