@@ -48,6 +48,7 @@ struct HipFailure {
 
 int hip_fail(const HipFailure &f)
 {
+    (void)hipGetLastError();   // reported here, and not by the next launch's check again
     if (f.err == hipErrorOutOfMemory || f.err == hipErrorMemoryAllocation)
         return fail(UMAP_E_NOMEM, "device allocation failed (%s): %s", f.what, hipGetErrorString(f.err));
     return fail(UMAP_E_DEVICE, "HIP call failed (%s): %s", f.what, hipGetErrorString(f.err));

@@ -151,3 +151,20 @@ def test_host_failure_in_every_call_with_scratch(monkeypatch):
         assert ei.value.code == U.UMAP_E_NOMEM
     monkeypatch.delenv("UMAP_LAYOUT_FAULT")
     assert 0.0 <= U.umap_trustworthiness(x, y, 3) <= 1.0
+
+
+def test_small_calls_after_one_that_does_not_fit():
+    """An allocation that fails leaves no error behind for the next call's launches."""
+    import torch
+
+    empty = np.zeros(0, np.int32)
+    free = torch.cuda.mem_get_info()[0]
+    with pytest.raises(U.UmapLayoutError) as ei:
+        U.umap_layout_create(2**31 - 1, 16, empty, empty, np.zeros(0, np.float32), A_DEF, B_DEF, 10, 5)
+    assert ei.value.code == U.UMAP_E_NOMEM
+    x = torch.randn(400, 3, device="cuda")
+    y = x[:, :2].contiguous()
+    assert 0.0 <= U.umap_trustworthiness(x, y, 3) <= 1.0
+    with _empty_handle(1000) as h:
+        U.umap_layout_run(h, 1)
+    assert torch.cuda.mem_get_info()[0] >= free - (64 << 20)
