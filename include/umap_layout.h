@@ -325,14 +325,15 @@ int umap_layout_set_rows(umap_layout *h, int64_t row_first, int64_t row_last);
  *   out  host double, receives T.
  * Distances are fp32 (input distances as |x_i|^2 + |x_j|^2 - 2 x_i . x_j with
  * the dot products on the matrix cores: up to 16 features fp32 products, beyond
- * each feature as the sum of three bf16 parts, and fp32 sums): a pair closer to a tie than fp32
- * resolves can rank differently from an exact evaluation, each such pair
- * moving T by about 1 / (n^2 k).  X is not checked: distances that are not
- * finite, or whose sums leave fp32's range, come after all others (in an order of
- * their own); such inputs take fp32 products instead.  Errors: UMAP_E_INVAL (arguments, a non-finite
- * embedding), UMAP_E_NOMEM, UMAP_E_DEVICE.  Takes scratch of about 12 n k bytes
- * and 6 n d for the parts (64 n up to 16 features), without them where that exceeds 16 GiB or does not fit
- * (see umap_layout_destroy); runs on `stream` (NULL: null stream).  Blocking.
+ * each feature as the sum of three bf16 parts, and fp32 sums): a pair closer to
+ * a tie than fp32 resolves can rank differently from an exact evaluation, each
+ * such pair moving T by about 1 / (n^2 k).  X is not checked: distances that are
+ * not finite, or whose sums leave fp32's range, come after all others (in an
+ * order of their own); such inputs take fp32 products instead.  Errors:
+ * UMAP_E_INVAL (arguments, a non-finite embedding), UMAP_E_NOMEM, UMAP_E_DEVICE.
+ * Takes scratch of about 12 n k bytes and 6 n d for the parts (64 n up to 16
+ * features), without them where that exceeds 16 GiB or does not fit (see
+ * umap_layout_destroy); runs on `stream` (NULL: null stream).  Blocking.
  */
 int umap_trustworthiness(const float *X, int64_t n, int32_t d, const float *Y, int32_t dim, int32_t k, double *out,
                          void *stream);

@@ -11,19 +11,19 @@
 //   3. k_bucket_rows: one workgroup per bucket drops what lies below
 //      w_max / n_epochs, counts its rows in LDS and files the rest by row; buckets
 //      of many entries (hubs) in chunks, by k_heavy_rows before and after it
-//   4. k_row_sort: 16 rows at a time sorted by column in LDS (rank sort; equal
-//      columns flag a duplicate); row_ptr, col, eps = w_max / val and the tails
-//      as 16-bit offsets written.  Rows of more than kLongRow entries by
-//      k_long_row_sort, a stable radix sort, one workgroup per row
+//   4. k_row_sort: 32 rows at a time (4 in dense graphs) sorted by column in LDS
+//      (rank sort; equal columns flag a duplicate); row_ptr, col, eps = w_max / val
+//      and the tails as 16-bit offsets written.  Rows of more than kLongRow entries
+//      by k_long_row_sort, a stable radix sort, one workgroup per row
 //   5. k_symmetry (not for a bipartite graph): each kept (i, j, v) must have
 //      a (j, i) with bit-equal v
 //   6. wave partition for the epoch kernel
 //
 // Entries move in runs: a count and a scatter with one global atomic and three
 // 4-byte stores per entry at random rows took 1343 us on a shuffled graph of
-// 777,777 rows (23.3M entries), where steps 2 and 3 take 164 and 193; a rank sort
-// from memory and a pass for the offsets 470 us, step 4 276.  (1M rows in local
-// order: 836 -> 115 + 221 us, 470 -> 375 us.)  Steps 3 and 4 are bound by the
+// 777,777 rows (23.3M entries), where steps 2 and 3 take 165 and 204; a rank sort
+// from memory and a pass for the offsets 470 us, step 4 271.  (1M rows in local
+// order: 836 -> 111 + 240 us, 470 -> 370 us.)  Steps 3 and 4 are bound by the
 // latency of a workgroup's chain of loads, step 2 by its streams.
 #include "internal.hpp"
 #include "launch_sizes.hpp"
