@@ -59,30 +59,13 @@ int hip_fail(const HipFailure &f)
 // launch of epoch K report a device error (nothing is launched in either
 // case); UMAP_LAYOUT_FAULT=records gives the wavefront kernel no record slots,
 // so every negative sample overflows and the epochs are redone;
-// UMAP_LAYOUT_FAULT=split gives the trustworthiness no room for the points' parts;
+// UMAP_LAYOUT_FAULT=split gives the trustworthiness no room for the points' parts,
+// UMAP_LAYOUT_FAULT=pairs has it take them however few points there are;
 // UMAP_LAYOUT_FAULT=host makes the scratch's bookkeeping run out of host memory.
-bool fault_alloc()
+bool fault_is(const char *what)
 {
     const char *f = getenv("UMAP_LAYOUT_FAULT");
-    return f && strcmp(f, "alloc") == 0;
-}
-
-bool fault_records()
-{
-    const char *f = getenv("UMAP_LAYOUT_FAULT");
-    return f && strcmp(f, "records") == 0;
-}
-
-bool fault_split()
-{
-    const char *f = getenv("UMAP_LAYOUT_FAULT");
-    return f && strcmp(f, "split") == 0;
-}
-
-bool fault_host()
-{
-    const char *f = getenv("UMAP_LAYOUT_FAULT");
-    return f && strcmp(f, "host") == 0;
+    return f && strcmp(f, what) == 0;
 }
 
 int fault_launch_epoch()
@@ -114,7 +97,7 @@ public:
     Scratch(size_t bytes, hipStream_t s) : stream_(s) { UL_HIP(take(bytes)); }
     hipError_t take(size_t bytes)
     {
-        if (fault_host()) throw std::bad_alloc();
+        if (fault_is("host")) throw std::bad_alloc();
         return ul::take_block(bytes, ul::Held::kByCall, &block_);
     }
     ~Scratch() { give(); }
@@ -314,7 +297,7 @@ int create_common(umap_layout **out, int64_t n, int32_t dim, const int32_t *rows
                        need<uint32_t>(record_slots) +
                        need<int32_t>((size_t)n_phases * max_waves) + need<long long>(nd) + need<unsigned>(1) +
                        need<float>(nd) + need<float>(table_elems);
-        if (fault_alloc()) throw HipFailure{hipErrorOutOfMemory, "hipMalloc(arena) [injected]"};
+        if (fault_is("alloc")) throw HipFailure{hipErrorOutOfMemory, "hipMalloc(arena) [injected]"};
         UL_HIP(ul::take_block(bytes, ul::Held::kByHandle, &h->arena));
         Carver cv{static_cast<char *>(h->arena.ptr)};
         h->row_ptr = cv.take<int64_t>(n + 1);
@@ -472,11 +455,11 @@ int run_epochs_impl(umap_layout *h, uint64_t seed, int32_t first, int32_t last, 
     A.key_lo = (uint32_t)seed;
     A.key_hi = (uint32_t)(seed >> 32);
     // (injected record failures need the records' path)
-    const bool one_launch = h->lg_phases == 0 || (!fault_records() && ul::one_launch_epoch(h->n_table, h->dim, h->row_edges,
+    const bool one_launch = h->lg_phases == 0 || (!fault_is("records") && ul::one_launch_epoch(h->n_table, h->dim, h->row_edges,
                                                                                         h->neg_rate));
     ul::WaveGraph G{h->row_ptr,     h->col,       h->eps,    h->head,      h->part,      h->desc,
                     h->n_waves,     1 << h->lg_phases,       h->lg_phases, h->rec,
-                    h->rec_count,   h->overflow,  fault_records() ? (int64_t)0 : (int64_t)-1,
+                    h->rec_count,   h->overflow,  fault_is("records") ? (int64_t)0 : (int64_t)-1,
                     h->delta,       h->col16_ok ? h->col16 : nullptr,
                     one_launch ? 1 : 0, h->halo ? 1 : 0};
     // the wave kernels store a sample's offset inside its table range and a
@@ -1110,7 +1093,8 @@ int umap_trustworthiness(const float *X, int64_t n, int32_t d, const float *Y, i
         if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return fail(UMAP_E_DEVICE, "no HIP device available");
         const size_t np = (size_t)ul::trust_padded(n), nk = np * (size_t)k;
         const size_t rest = need<float>(np) + 2 * need<int32_t>(nk) + need<float>(nk) + need<unsigned long long>(2);
-        size_t split_bytes = fault_split() ? 0 : ul::trust_split_bytes(n, d);
+        const bool pairs = fault_is("pairs") || (!fault_is("split") && ul::pairs_pay(n, d, k));
+        size_t split_bytes = pairs ? ul::trust_split_bytes(n, d) : 0;
         Scratch scratch(s);
         hipError_t taken = scratch.take(need<char>(split_bytes) + rest);
         if (taken != hipSuccess && split_bytes) {   // no room for the parts: the kernels on X itself

@@ -18,8 +18,8 @@
 //     of 128 x 128 on the matrix cores, compared in registers with the
 //     neighbour thresholds of both points: only the counts r(i, j) - 1 leave the
 //     chip, never the n x n distances.  (k_tw_rank: every pair twice, fp32
-//     matrix instructions on X itself; only where the parts would not fit or
-//     the points' norms come near fp32's range.)
+//     matrix instructions on X itself; for few points (pairs_pay), where the
+//     parts would not fit, or where the points' norms come near fp32's range.)
 //  5. k_tw_penalty: the penalties' sum.
 #include "internal.hpp"
 #include "launch_sizes.hpp"

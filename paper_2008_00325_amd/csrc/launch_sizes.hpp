@@ -48,6 +48,19 @@ constexpr int64_t panel_span(int64_t panels)
     return span;
 }
 
+// Whether the ranks come from every pair once, in tiles of 128 x 128, rather than from
+// the fp32 kernel, which takes them row by row: a tile's counting is a long chain (the longer
+// the more neighbours) that few tiles do not hide, while the fp32 kernel's time grows
+// with the features.  us per call, pairs / fp32: k = 15, 500 x 8 152 / 79, 2,048 x 8 135 /
+// 96, 2,560 x 64 152 / 128, 3,072 x 64 154 / 141, 2,048 x 300 176 / 162, 2,560 x 300 184 / 201,
+// 1,024 x 784 243 / 233, 1,280 x 784 248 / 252; k = 64, 500 x 8 481 / 176, 2,560 x 64 399 /
+// 401, 2,560 x 300 459 / 523, 1,536 x 784 629 / 636; k = 5, 2,048 x 64 90 / 78, 2,560 x 64
+// 92 / 99, 640 x 300 103 / 109, 250 x 784 130 / 193.
+constexpr bool pairs_pay(int64_t n, int32_t d, int32_t k)
+{
+    return n + (k <= 8 ? 7 : 2) * (int64_t)d > 2600;
+}
+
 // ---- draw kernel at 1-2 components ----
 // Whether the 64 rows on each side of a wave's own are staged for the tails that lie
 // there: `near` of `kept` tails are within 64 rows of theirs.  A staged row is an LDS

@@ -21,6 +21,10 @@ int main()
             int32_t dim;
             if (scanf("%" SCNd64 " %" SCNd64 " %" SCNd32, &kept, &n, &dim) != 3) return 1;
             printf("%d\n", ul::halo_pays(x, kept, n, dim) ? 1 : 0);
+        } else if (!strcmp(what, "ranks")) {   // points, features, neighbours -> whether every pair is taken once
+            int32_t d, k;
+            if (scanf("%" SCNd32 " %" SCNd32, &d, &k) != 2) return 1;
+            printf("%d\n", ul::pairs_pay(x, d, k) ? 1 : 0);
         } else {
             return 1;
         }

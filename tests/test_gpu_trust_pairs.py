@@ -26,10 +26,12 @@ def _both(monkeypatch, X, Y, k):
 
     torch.cuda.set_device(0)
     x, y = torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda()
+    monkeypatch.setenv("UMAP_LAYOUT_FAULT", "pairs")    # however few points
     pairs = U.umap_trustworthiness(x, y, k)
     monkeypatch.setenv("UMAP_LAYOUT_FAULT", "split")
     plain = U.umap_trustworthiness(x, y, k)
     monkeypatch.delenv("UMAP_LAYOUT_FAULT")
+    assert U.umap_trustworthiness(x, y, k) in (pairs, plain)
     return pairs, plain
 
 

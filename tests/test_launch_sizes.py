@@ -57,3 +57,10 @@ def test_halo_rule(sizes):
              (kept, kept, 131_072, 2): 1, (kept, kept, 131_071, 2): 0, (0, 0, 1_000_000, 2): 0}
     got = sizes([f"halo {near} {k} {n} {dim}" for near, k, n, dim in asked])
     assert [g for (g,) in got] == list(asked.values())
+
+
+def test_few_points_are_ranked_row_by_row(sizes):
+    asked = {(500, 8, 64): 0, (500, 784, 15): 0, (2_000, 300, 64): 0, (2_584, 8, 15): 0, (2_585, 8, 15): 1, (2_000, 784, 64): 1,
+             (500, 300, 5): 0, (501, 300, 5): 1, (250, 784, 8): 1, (5_003, 64, 15): 1, (70_000, 784, 15): 1}
+    got = sizes([f"ranks {n} {d} {k}" for n, d, k in asked])
+    assert [g for (g,) in got] == list(asked.values())
