@@ -378,7 +378,7 @@ __device__ __forceinline__ int32_t bucket_rows(int64_t row0, int64_t n, int32_t 
 // more rows than the counters hold take them kBucketRows at a time.  A heavy
 // bucket's rows were counted by k_heavy_rows<false> (in lstart), which files them
 // afterwards from `rcursor` on.
-__global__ __launch_bounds__(kTileThreads, 8) void k_bucket_rows(const int2 *__restrict__ pair,
+__global__ __launch_bounds__(kTileThreads) void k_bucket_rows(const int2 *__restrict__ pair,
                                                               const uint16_t *__restrict__ lrow,
                                                               const int32_t *__restrict__ first, int64_t n, int32_t lg,
                                                               int32_t n_epochs, const PrepScalars *S,
@@ -395,21 +395,28 @@ __global__ __launch_bounds__(kTileThreads, 8) void k_bucket_rows(const int2 *__r
     const int64_t row0 = (int64_t)blockIdx.x << lg;
     const int32_t rows = bucket_rows(row0, n, lg);
     int32_t done = 0;   // kept entries of the rows before
-    for (int32_t a = 0; a < rows; a += kBucketRows) {
-        const int32_t m = rows - a < kBucketRows ? rows - a : kBucketRows;
-        for (int32_t t = tid; t < m; t += kTileThreads) s_n[t] = heavy ? lstart[row0 + a + t] : 0;
-        __syncthreads();
-        if (!heavy) count_entries(pair, lrow, e0, e1, a, m, thresh, s_n);
-        __syncthreads();
-        const int32_t before = done;
-        done += scan_loop(m, s_wave, [&](int32_t t) { return s_n[t]; },
-                          [&](int32_t t, int32_t x) {
-                              s_n[t] = before + x;
-                              lstart[row0 + a + t] = before + x;
-                              if (heavy) rcursor[row0 + a + t] = before + x;
-                          });
-        if (!heavy) file_entries(pair, lrow, e0, e1, a, m, thresh, s_n, out + e0);
-        __syncthreads();
+    if (heavy) {        // (a loop of its own: in the other it cost registers and 14 us at 1M rows)
+        done = scan_loop(rows, s_wave, [&](int32_t t) { return lstart[row0 + t]; },
+                         [&](int32_t t, int32_t before) {
+                             lstart[row0 + t] = before;
+                             rcursor[row0 + t] = before;
+                         });
+    } else {
+        for (int32_t a = 0; a < rows; a += kBucketRows) {
+            const int32_t m = rows - a < kBucketRows ? rows - a : kBucketRows;
+            for (int32_t t = tid; t < m; t += kTileThreads) s_n[t] = 0;
+            __syncthreads();
+            count_entries(pair, lrow, e0, e1, a, m, thresh, s_n);
+            __syncthreads();
+            const int32_t before = done;
+            done += scan_loop(m, s_wave, [&](int32_t t) { return s_n[t]; },
+                              [&](int32_t t, int32_t x) {
+                                  s_n[t] = before + x;
+                                  lstart[row0 + a + t] = before + x;
+                              });
+            file_entries(pair, lrow, e0, e1, a, m, thresh, s_n, out + e0);
+            __syncthreads();
+        }
     }
     if (tid == 0) kept_n[blockIdx.x] = (uint32_t)done;
 }
