@@ -21,9 +21,9 @@
 //
 // Entries move in runs: a count and a scatter with one global atomic and three
 // 4-byte stores per entry at random rows took 1343 us on a shuffled graph of
-// 777,777 rows (23.3M entries), where steps 2 and 3 take 165 and 204; a rank sort
+// 777,777 rows (23.3M entries), where steps 2 and 3 take 163 and 202; a rank sort
 // from memory and a pass for the offsets 470 us, step 4 271.  (1M rows in local
-// order: 836 -> 111 + 240 us, 470 -> 370 us.)  Steps 3 and 4 are bound by the
+// order: 836 -> 110 + 231 us, 470 -> 368 us.)  Steps 3 and 4 are bound by the
 // latency of a workgroup's chain of loads, step 2 by its streams.
 #include "internal.hpp"
 #include "launch_sizes.hpp"
