@@ -215,8 +215,9 @@ hipError_t launch_probe_gather(const void *table, int64_t entries, int64_t threa
                                hipStream_t s);
 
 // ---- trustworthiness (kernels_trust.hip) ----
-// The ranks come from the points split into bf16 parts (trust_split_bytes; 0
-// beyond kTrustSplitBytes: from fp32 products of X itself, every pair twice).
+// The ranks come from the points split into bf16 parts, or packed as they are up to
+// 16 features (trust_split_bytes; 0 beyond kTrustSplitBytes), every pair once, or
+// from fp32 products of X itself, every pair twice (split null).
 constexpr int64_t kTrustSplitBytes = (int64_t)16 << 30;
 int64_t trust_padded(int64_t n);
 size_t trust_split_bytes(int64_t n, int32_t d);
